@@ -190,6 +190,15 @@ hipError_t launch_deposit(const Geom& g, const SpeciesDev& s, const PrevDev& pre
 hipError_t launch_jfinal(const Geom& g, unsigned long long* acc, float* const J[3], const double scale[3],
                          int zero_acc, hipStream_t st);
 
+// tile-wise deposit of the split path (pic_tile.hip): particles in any memory
+// order, visited through `list`, an index list of the tiling t by the old
+// cells (launch_tile_list; off: its key offsets)
+TileGeom deposit_tiling(const int n[3]);
+hipError_t launch_deposit_tiles(const Geom& g, const TileGeom& t, const SpeciesDev& s, const PrevDev& prev,
+                                const int* list, const int* off, unsigned long long* acc, hipStream_t st);
+hipError_t launch_tile_list(const Geom& g, const TileGeom& t, const int* cell, const int* d_count, int max_count,
+                            int* hist, int* list, int* tmp, int* sums, hipStream_t st);
+
 // sort (pic_sort.hip): src -> dst, new count into d_count and d_sorted, tile
 // ranges into toff (t.ntiles + 1 entries); hist, rank, sums are scratch.
 // depth: 0 = level order inside a tile (level: scratch of max_count ints),

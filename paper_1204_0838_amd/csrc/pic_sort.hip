@@ -124,6 +124,11 @@ inline int count_threads(int n, int stride) {
     return (n + blk - 1) / blk * stride;
 }
 
+__global__ void __launch_bounds__(256) k_zero_hist(int* __restrict__ hist, int n) {
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < n) hist[i] = 0;
+}
+
 // Columns over particles [*d_begin, *d_count) (d_begin null: from 0).
 __global__ void __launch_bounds__(256) k_sort_count(Geom g, TileGeom t, SortDiv sd, const int* __restrict__ cell,
                                                     const int* __restrict__ d_begin, const int* __restrict__ d_count,
@@ -676,6 +681,26 @@ hipError_t launch_sort(const Geom& g, const TileGeom& t, const SpeciesDev& src, 
     hipLaunchKernelGGL(k_sort_finish, dim3(1), dim3(1), 0, st, hist, nkeys, d_count, d_sorted);
     hipLaunchKernelGGL(k_tile_offsets, dim3((t.ntiles + 1 + 255) / 256), dim3(256), 0, st, hist, t.tcells, t.ntiles,
                        toff);
+    return hipGetLastError();
+}
+
+// The tile-wise order of particles by the cells in `cell`, as a list of
+// indices: list[off[t tcells] .. off[(t + 1) tcells]) are tile t's particles
+// in level order (hist is left holding off).  Nothing else is moved.
+hipError_t launch_tile_list(const Geom& g, const TileGeom& t, const int* cell, const int* d_count, int max_count,
+                            int* hist, int* list, int* tmp, int* sums, hipStream_t st) {
+    const int nkeys = t.ntiles * t.tcells, n = nkeys + 1, nb = (n + 1023) / 1024;
+    const int stride = count_stride(t, 0), ncol = count_threads(max_count, stride);
+    const SortDiv sd = make_sortdiv(g, t);
+    hipLaunchKernelGGL(k_zero_hist, dim3((n + 255) / 256), dim3(256), 0, st, hist, n);
+    hipLaunchKernelGGL(k_sort_count, dim3((ncol + 255) / 256), dim3(256), 0, st, g, t, sd, cell, nullptr, d_count,
+                       stride, 0, hist, list);
+    hipLaunchKernelGGL(k_scan_reduce, dim3(nb), dim3(1024), 0, st, hist, n, sums);
+    hipLaunchKernelGGL(k_scan_sums, dim3(1), dim3(1024), 0, st, sums, nb);
+    hipLaunchKernelGGL(k_scan_apply, dim3(nb), dim3(1024), 0, st, hist, n, sums, hist);
+    hipLaunchKernelGGL(k_sort_scatter, dim3((max_count + 255) / 256), dim3(256), 0, st, g, t, sd, cell, tmp, d_count,
+                       list, hist, nullptr, 0);
+    hipLaunchKernelGGL(k_sort_levels, dim3(t.ntiles), dim3(kLevelThreads), 0, st, hist, t.tcells, tmp, list);
     return hipGetLastError();
 }
 

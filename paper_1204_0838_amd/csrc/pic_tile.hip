@@ -187,6 +187,48 @@ __device__ __forceinline__ void keep_particle(const SpeciesDev& s, int p, const 
     }
 }
 
+// Add the non-zero LDS current of a tile at t0 (its region starting `lo`
+// cells before it) to the global accumulator.
+template <int NT>
+__device__ __forceinline__ void flush_current(const Geom& g, const int t0[3], int lo, int jx, int jpl, int jr,
+                                              const unsigned long long* Jl, unsigned long long* __restrict__ acc) {
+    for (int i = threadIdx.x; i < 3 * jr; i += NT) {
+        const unsigned long long v = Jl[i];
+        if (v == 0ull) continue;   // (the padding of each plane stays zero)
+        const int comp = i / jr;
+        const int k = i - comp * jr;
+        const int lz = k / jpl;
+        const int rr = k - lz * jpl;
+        const int ly = rr / jx;
+        const int lx = rr - ly * jx;
+        int gx = t0[0] - lo + lx, gy = t0[1] - lo + ly, gz = t0[2] - lo + lz;
+        gx = wrap_any(gx, g.n[0]);
+        gy = wrap_any(gy, g.n[1]);
+        gz = wrap_any(gz, g.n[2]);
+        atomicAdd(acc + ((size_t)comp * g.ncell + gx + g.n[0] * (gy + g.n[1] * gz)), v);
+    }
+}
+
+// LDS current of one particle that moved from local cell lc (>= -guard of its
+// tile) along the axes A (esirkepov<true> into the tile's region).
+__device__ __forceinline__ void deposit_lds(unsigned long long* Jl, const int lc[3], int guard, const int jstride[3],
+                                            int jr, const Axis5 A[3], float wq) {
+    LdsEmit em;
+    em.base = Jl + ((lc[0] + guard + 1) + (lc[1] + guard + 1) * jstride[1] + (lc[2] + guard + 1) * jstride[2]);
+    em.jx = jstride[1];
+    em.jpl = jstride[2];
+    em.jr = jr;
+    // backward crossing: the transverse extra slot moves from +4 to -1
+    // slots, the own-axis one from +3 to -1
+    em.dxm = A[0].base < -1 ? -5 : 0;
+    em.dxp = A[0].base < -1 ? -4 : 0;
+    em.dym = A[1].base < -1 ? -5 * jstride[1] : 0;
+    em.dyp = A[1].base < -1 ? -4 * jstride[1] : 0;
+    em.dzm = A[2].base < -1 ? -5 * jstride[2] : 0;
+    em.dzp = A[2].base < -1 ? -4 * jstride[2] : 0;
+    esirkepov<true>(A, wq, em);
+}
+
 // Body of the fused step for one tile (the whole workgroup cooperates).
 // TX, TY, TZ > 0 and GD >= 0 fix the tile shape and guard at compile time:
 // every LDS stride is then a constant and each particle's current atomics
@@ -343,40 +385,11 @@ __device__ __forceinline__ void tile_body(const Geom& g, const TileGeom& t, int 
         Axis5 A[3];
 #pragma unroll
         for (int d = 0; d < 3; ++d) axis5(unwrap_shift(c1[d] - c[d], g.n[d]), o0[d], o[d], A[d]);
-        LdsEmit em;
-        em.base = Jl + ((lc[0] + guard + 1) + (lc[1] + guard + 1) * jstride[1] + (lc[2] + guard + 1) * jstride[2]);
-        em.jx = jstride[1];
-        em.jpl = jstride[2];
-        em.jr = jr;
-        // backward crossing: the transverse extra slot moves from +4 to -1
-        // slots, the own-axis one from +3 to -1
-        em.dxm = A[0].base < -1 ? -5 : 0;
-        em.dxp = A[0].base < -1 ? -4 : 0;
-        em.dym = A[1].base < -1 ? -5 * jstride[1] : 0;
-        em.dyp = A[1].base < -1 ? -4 * jstride[1] : 0;
-        em.dzm = A[2].base < -1 ? -5 * jstride[2] : 0;
-        em.dzp = A[2].base < -1 ? -4 * jstride[2] : 0;
-        esirkepov<true>(A, wq, em);
+        deposit_lds(Jl, lc, guard, jstride, jr, A, wq);
     }
     if (errs) atomicOr(d_err, errs);
     __syncthreads();
-    // flush the non-zero LDS current into the global accumulator
-    const int lo = guard + 2;
-    for (int i = threadIdx.x; i < 3 * jr; i += NT) {
-        const unsigned long long v = Jl[i];
-        if (v == 0ull) continue;   // (the padding of each plane stays zero)
-        const int comp = i / jr;
-        const int k = i - comp * jr;
-        const int lz = k / jpl;
-        const int rr = k - lz * jpl;
-        const int ly = rr / jx;
-        const int lx = rr - ly * jx;
-        int gx = t0[0] - lo + lx, gy = t0[1] - lo + ly, gz = t0[2] - lo + lz;
-        gx = wrap_any(gx, g.n[0]);
-        gy = wrap_any(gy, g.n[1]);
-        gz = wrap_any(gz, g.n[2]);
-        atomicAdd(acc + ((size_t)comp * g.ncell + gx + g.n[0] * (gy + g.n[1] * gz)), v);
-    }
+    flush_current<NT>(g, t0, guard + 2, jx, jpl, jr, Jl, acc);
 }
 
 template <int NT, int TX = 0, int TY = 0, int TZ = 0, int GD = -1, bool GATHER = false>
@@ -418,6 +431,72 @@ __global__ void __launch_bounds__(NT) k_batch_tile(const InstDesc* __restrict__ 
     else
         tile_body<NT, TX, TY, TZ, GD>(g, t, d.guard, f, s, s, d.toff, d.acc, d.err, d.rest_n, d.rank, lds_u64,
                                       ft - tile_begin[lo]);
+}
+
+// Deposit of the split path, tile by tile.  The particles stay in the
+// caller's memory order; `list` names each tile's particles by their old
+// cells (so the LDS region needs no guard: 8x8x8 cells, 59 KB, two
+// workgroups per CU).  A particle's 144-300 contributions go to LDS, and the
+// tile's region to the global accumulator once: global 64-bit atomics, which
+// bound the one-thread-per-particle form (k_deposit), drop from ~200 to ~3
+// per particle at 4 particles per cell (75x50x44 cells, 6.6e5 particles: 3827
+// -> 68 us, plus 75 us for the index list; atomics and deposit arithmetic in
+// LDS bound it now).
+constexpr int kDepTile = 8, kDepThreads = 512;
+
+__global__ void __launch_bounds__(kDepThreads) k_deposit_tiles(Geom g, TileGeom t, SpeciesDev s, PrevDev prev,
+                                                               const int* __restrict__ list,
+                                                               const int* __restrict__ off,
+                                                               unsigned long long* __restrict__ acc) {
+    constexpr int jx = kDepTile + 5, jpl = cur_plane(jx, jx), jr = jpl * jx;
+    __shared__ unsigned long long Jl[3 * jr];
+    const int tile = xcd_tile(blockIdx.x, t.ntiles, t.nt[0]);
+    if (tile >= t.ntiles) return;
+    const int pb = off[tile * t.tcells], n = off[(tile + 1) * t.tcells] - pb;
+    if (n == 0) return;
+    const int tz = tile / (t.nt[0] * t.nt[1]);
+    const int tr = tile - tz * t.nt[0] * t.nt[1];
+    const int ty = tr / t.nt[0];
+    const int t0[3] = {(tr - ty * t.nt[0]) * t.T[0], ty * t.T[1], tz * t.T[2]};
+    for (int i = threadIdx.x; i < 3 * jr; i += kDepThreads) Jl[i] = 0ull;
+    __syncthreads();
+    const int jstride[3] = {1, jx, jpl};
+    for (int q = threadIdx.x; q < n; q += kDepThreads) {
+        const int p = list[pb + q];
+        const int cell0 = prev.cell[p], cell1 = s.cell[p];   // (cell0 is valid: it has a key)
+        if ((unsigned)cell1 >= (unsigned)g.ncell) continue;
+        int c0[3], c1[3];
+        decompose(g, cell0, c0);
+        decompose(g, cell1, c1);
+        const float o0[3] = {prev.off[0][p], prev.off[1][p], prev.off[2][p]};
+        const float o1[3] = {s.off[0][p], s.off[1][p], s.off[2][p]};
+        if (!moved(c0, c1, o0, o1)) continue;
+        Axis5 A[3];
+        const int lc[3] = {c0[0] - t0[0], c0[1] - t0[1], c0[2] - t0[2]};
+#pragma unroll
+        for (int d = 0; d < 3; ++d) axis5(unwrap_shift(c1[d] - c0[d], g.n[d]), o0[d], o1[d], A[d]);
+        deposit_lds(Jl, lc, 0, jstride, jr, A, s.mq * s.w[p]);
+    }
+    __syncthreads();
+    flush_current<kDepThreads>(g, t0, 2, jx, jpl, jr, Jl, acc);
+}
+
+TileGeom deposit_tiling(const int n[3]) {
+    TileGeom t;
+    for (int a = 0; a < 3; ++a) {
+        t.T[a] = std::min(kDepTile, n[a]);
+        t.nt[a] = (n[a] + t.T[a] - 1) / t.T[a];
+    }
+    t.ntiles = t.nt[0] * t.nt[1] * t.nt[2];
+    t.tcells = t.T[0] * t.T[1] * t.T[2];
+    return t;
+}
+
+hipError_t launch_deposit_tiles(const Geom& g, const TileGeom& t, const SpeciesDev& s, const PrevDev& prev,
+                                const int* list, const int* off, unsigned long long* acc, hipStream_t st) {
+    hipLaunchKernelGGL(k_deposit_tiles, dim3(xcd_blocks(t.ntiles, t.nt[0])), dim3(kDepThreads), 0, st, g, t, s, prev,
+                       list, off, acc);
+    return hipGetLastError();
 }
 
 // The rest pass, after the tile kernel: the particles on the species' rest
