@@ -2,6 +2,7 @@
 // workspace layout, context state and the launch sequences of each call.
 #include <math.h>
 #include <stdarg.h>
+#include <stddef.h>
 #include <stdio.h>
 #include <string.h>
 
@@ -22,7 +23,7 @@ constexpr size_t kAlign = 256;
 constexpr int kKillMargin = 3;   // window cells behind which particles are removed
 constexpr size_t kMaxLds = 160 * 1024;
 constexpr int kDiagBins = 2048;                                   // most spectrum bins
-constexpr size_t kDiagWords = 64;                                 // reduction words of the diagnostics
+constexpr size_t kDiagWords = 64;                                 // reduction words of the diagnostics (after the bins)
 // The split path deposits a species of more than kDepositTilesMin + ncell / 128
 // particles (host bound) tile by tile through LDS, a smaller one with one
 // thread per particle and global atomics.  Measured, direct against tile-wise:
@@ -976,6 +977,9 @@ pic_status batch_one_step(pic_batch* b) {
 // helpers of the run diagnostics
 namespace {
 
+// partials of the two-stage reductions: the spectrum's bins, idle outside pic_spectrum
+double* diag_partials(pic_ctx* c) { return reinterpret_cast<double*>(c->ws + c->L.diag); }
+
 double* diag_words(pic_ctx* c) {
     return reinterpret_cast<double*>(c->ws + c->L.diag) + 2 * kDiagBins;
 }
@@ -1223,7 +1227,7 @@ pic_status pic_continuity(pic_ctx* c, int32_t s, double* resid, double* max_abs_
                                 c->desc.d[0] / c->desc.d[2], c->j_filtered, &sm->contmax,
                                 c->stream));
     FieldPtrs f = fields_of(c);
-    HIPCHK(c, launch_diag_fields(c->g, f.E, f.B, c->f.J, 1.0, sm->red, &sm->jmax, c->stream));
+    HIPCHK(c, launch_diag_fields(c->g, f.E, f.B, c->f.J, 1.0, sm->red, &sm->jmax, diag_partials(c), c->stream));
     unsigned long long cm = 0;
     unsigned int jm = 0;
     HIPCHK(c, hipMemcpyAsync(&cm, &sm->contmax, 8, hipMemcpyDeviceToHost, c->stream));
@@ -1261,7 +1265,7 @@ pic_status pic_continuity_noalloc(pic_ctx* c, int32_t s, double* resid, double* 
                                 c->desc.d[0] / c->desc.d[2], c->j_filtered, &head->contmax,
                                 c->stream));
     FieldPtrs f = fields_of(c);
-    HIPCHK(c, launch_diag_fields(c->g, f.E, f.B, c->f.J, 1.0, head->red, &head->jmax, c->stream));
+    HIPCHK(c, launch_diag_fields(c->g, f.E, f.B, c->f.J, 1.0, head->red, &head->jmax, diag_partials(c), c->stream));
     unsigned long long cm = 0;
     unsigned int jm = 0;
     HIPCHK(c, hipMemcpyAsync(&cm, &head->contmax, 8, hipMemcpyDeviceToHost, c->stream));
@@ -1279,33 +1283,29 @@ pic_status pic_continuity_noalloc(pic_ctx* c, int32_t s, double* resid, double* 
 pic_status pic_reduce(pic_ctx* c, pic_diag* out) {
     if (!c || !out) return PIC_EINVAL;
     Small* sm = small_of(c);
-    HIPCHK(c, hipMemsetAsync(sm->red, 0, sizeof sm->red, c->stream));
-    HIPCHK(c, hipMemsetAsync(&sm->live, 0, 8, c->stream));
-    HIPCHK(c, hipMemsetAsync(&sm->jmax, 0, 4, c->stream));
+    static_assert(offsetof(Small, pad1) - offsetof(Small, red) == 52, "red, live, contmax, jmax lie together");
+    HIPCHK(c, launch_zero_u64(reinterpret_cast<unsigned long long*>(sm->red), (sizeof(Small) - offsetof(Small, red)) / 8,
+                              c->stream));
     const double dv = c->desc.d[0] * c->desc.d[1] * c->desc.d[2];
     for (int32_t s = 0; s < (int32_t)c->sp.size(); ++s) {
         Species& sp = c->sp[s];
         HIPCHK(c, launch_diag_particles(c->g, dev_of(c, sp), sp.user.q, sp.user.m, dv, &sm->count[s], (int)sp.bound,
-                                        sm->red, &sm->live, c->stream));
+                                        sm->red, &sm->live, diag_partials(c), c->stream));
     }
     FieldPtrs f = fields_of(c);
-    HIPCHK(c, launch_diag_fields(c->g, f.E, f.B, c->f.J, dv, sm->red, &sm->jmax, c->stream));
-    double red[4];
-    unsigned long long live = 0;
-    unsigned int jm = 0;
-    HIPCHK(c, hipMemcpyAsync(red, sm->red, sizeof red, hipMemcpyDeviceToHost, c->stream));
-    HIPCHK(c, hipMemcpyAsync(&live, &sm->live, 8, hipMemcpyDeviceToHost, c->stream));
-    HIPCHK(c, hipMemcpyAsync(&jm, &sm->jmax, 4, hipMemcpyDeviceToHost, c->stream));
+    HIPCHK(c, launch_diag_fields(c->g, f.E, f.B, c->f.J, dv, sm->red, &sm->jmax, diag_partials(c), c->stream));
+    Small h;   // results and error flags in one copy
+    HIPCHK(c, hipMemcpyAsync(&h, sm, sizeof h, hipMemcpyDeviceToHost, c->stream));
     HIPCHK(c, hipStreamSynchronize(c->stream));
     float j;
-    memcpy(&j, &jm, 4);
-    out->charge = red[0];
-    out->e_kin = red[1];
-    out->e_field = red[2];
+    memcpy(&j, &h.jmax, 4);
+    out->charge = h.red[0];
+    out->e_kin = h.red[1];
+    out->e_field = h.red[2];
     out->max_abs_J = j;
-    out->n_particles = (int64_t)live;
+    out->n_particles = (int64_t)h.live;
     out->step = c->step;
-    return device_errors(c);
+    return h.err ? device_errors(c) : PIC_OK;
 }
 
 pic_status pic_sync(pic_ctx* c) {
@@ -1616,29 +1616,37 @@ pic_status pic_spectrum(pic_ctx* c, int32_t s, int32_t quantity, double lo, doub
     if (quantity != 0 && quantity != 1) return fail(c, PIC_EINVAL, "spectrum quantity must be 0 (gamma-1) or 1 (u_x)");
     if (nbins < 1 || nbins > kDiagBins) return fail(c, PIC_EINVAL, "spectrum bins outside 1..%d", kDiagBins);
     if (!(hi > lo) || !isfinite(lo) || !isfinite(hi)) return fail(c, PIC_EINVAL, "spectrum range must have hi > lo");
-    double* charge = reinterpret_cast<double*>(c->ws + c->L.diag);
-    unsigned long long* count = reinterpret_cast<unsigned long long*>(charge + kDiagBins);
-    HIPCHK(c, launch_zero_u64(reinterpret_cast<unsigned long long*>(charge), 2 * kDiagBins, c->stream));
+    // charge[nbins], count[nbins], then the error flags: one copy brings all
+    double* charge = diag_partials(c);
+    unsigned long long* count = reinterpret_cast<unsigned long long*>(charge + nbins);
+    HIPCHK(c, launch_zero_u64(reinterpret_cast<unsigned long long*>(charge), 2 * (int64_t)nbins, c->stream));
     Species& sp = c->sp[s];
     const double dv = c->desc.d[0] * c->desc.d[1] * c->desc.d[2];
     HIPCHK(c, launch_spectrum(c->g, dev_of(c, sp), &small_of(c)->count[s], (int)sp.bound, quantity, lo, hi, nbins,
                               fabs(sp.user.q) * dv, charge, count, c->stream));
-    HIPCHK(c, hipMemcpyAsync(host_charge, charge, (size_t)nbins * 8, hipMemcpyDeviceToHost, c->stream));
-    if (host_count) HIPCHK(c, hipMemcpyAsync(host_count, count, (size_t)nbins * 8, hipMemcpyDeviceToHost, c->stream));
-    return device_errors(c);
+    HIPCHK(c, launch_flag_word(&small_of(c)->err, count + nbins, c->stream));
+    std::vector<uint64_t> h(2 * (size_t)nbins + 1);
+    HIPCHK(c, hipMemcpyAsync(h.data(), charge, h.size() * 8, hipMemcpyDeviceToHost, c->stream));
+    HIPCHK(c, hipStreamSynchronize(c->stream));
+    memcpy(host_charge, h.data(), (size_t)nbins * 8);
+    if (host_count) memcpy(host_count, h.data() + nbins, (size_t)nbins * 8);
+    return h.back() ? device_errors(c) : PIC_OK;
 }
 
 pic_status pic_beam_moments(pic_ctx* c, int32_t s, double ux_min, pic_beam_diag* out) {
     PICCHK(check_species(c, s));
     if (!out) return PIC_EINVAL;
     double* sums = diag_words(c);
-    HIPCHK(c, launch_zero_u64(reinterpret_cast<unsigned long long*>(sums), 13, c->stream));
     Species& sp = c->sp[s];
     HIPCHK(c, launch_beam_moments(c->g, dev_of(c, sp), &small_of(c)->count[s], (int)sp.bound, ux_min, c->desc.d[1],
-                                  c->desc.d[2], sums, c->stream));
-    double h[13];
+                                  c->desc.d[2], sums, diag_partials(c), c->stream));
+    HIPCHK(c, launch_flag_word(&small_of(c)->err, reinterpret_cast<unsigned long long*>(sums + 13), c->stream));
+    double h[14];   // the sums and the error flags
     HIPCHK(c, hipMemcpyAsync(h, sums, sizeof h, hipMemcpyDeviceToHost, c->stream));
-    PICCHK(device_errors(c));
+    HIPCHK(c, hipStreamSynchronize(c->stream));
+    uint64_t flags;
+    memcpy(&flags, h + 13, 8);
+    if (flags) PICCHK(device_errors(c));
     const double dv = c->desc.d[0] * c->desc.d[1] * c->desc.d[2];
     memset(out, 0, sizeof *out);
     out->count = (int64_t)h[12];
@@ -1674,9 +1682,12 @@ pic_status pic_select_particles(pic_ctx* c, int32_t s, double ux_min, int64_t ca
     const pic_species_bufs& o = sp.alt;
     HIPCHK(c, launch_select(c->g, dev_of(c, sp), &small_of(c)->count[s], (int)sp.bound, ux_min, o.cell, o.off[0],
                             o.u[0], o.id, counter, c->stream));
-    int nsel = 0;
-    HIPCHK(c, hipMemcpyAsync(&nsel, counter, sizeof(int), hipMemcpyDeviceToHost, c->stream));
-    PICCHK(device_errors(c));
+    HIPCHK(c, launch_flag_word(&small_of(c)->err, reinterpret_cast<unsigned long long*>(counter) + 1, c->stream));
+    uint64_t h[2];   // the counter and the error flags
+    HIPCHK(c, hipMemcpyAsync(h, counter, sizeof h, hipMemcpyDeviceToHost, c->stream));
+    HIPCHK(c, hipStreamSynchronize(c->stream));
+    if (h[1]) PICCHK(device_errors(c));
+    const int nsel = (int)h[0];
     if (n_selected) *n_selected = nsel;
     const int64_t k = nsel < cap ? nsel : cap;
     if (k > 0) {
@@ -1700,11 +1711,10 @@ pic_status pic_select_particles(pic_ctx* c, int32_t s, double ux_min, int64_t ca
 pic_status pic_field_moments(pic_ctx* c, int32_t transverse_only, double* host_out) {
     if (!c || !host_out) return PIC_EINVAL;
     double* sums = diag_words(c) + 24;
-    HIPCHK(c, launch_zero_u64(reinterpret_cast<unsigned long long*>(sums), 3, c->stream));
     const int mask = transverse_only ? 0x36 : 0x3f;   // E_y, E_z, B_y, B_z or all six
     FieldPtrs f = fields_of(c);
     HIPCHK(c, launch_field_moments(c->g, f.E, f.B, mask, c->desc.d[0], c->desc.d[0] * c->desc.d[1] * c->desc.d[2],
-                                   sums, c->stream));
+                                   sums, diag_partials(c), c->stream));
     HIPCHK(c, hipMemcpyAsync(host_out, sums, 3 * 8, hipMemcpyDeviceToHost, c->stream));
     HIPCHK(c, hipStreamSynchronize(c->stream));
     return PIC_OK;

@@ -4,20 +4,17 @@
 // beam moments for the normalised transverse emittance, the selection of
 // accelerated particles with their tags (collection phase space), and the
 // first moments of the electromagnetic energy along x (the laser centroid,
-// Section 3.3).  Each kernel streams its inputs once; sums use FP64 atomics
-// after a wavefront reduction (histograms: per-workgroup LDS bins first).
+// Section 3.3).  Each kernel streams its inputs once; sums are two-stage
+// (pic_block_sum.h), histograms use per-workgroup LDS bins.
+#include <algorithm>
+
+#include "pic_block_sum.h"
 #include "pic_internal.h"
 #include "pic_particle_ops.h"
 
 namespace pic {
 
 namespace {
-
-__device__ __forceinline__ double wsum(double v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-    return v;
-}
 
 // Window x index of storage x index i.
 __device__ __forceinline__ int window_x(const Geom& g, int i) {
@@ -30,6 +27,7 @@ __device__ __forceinline__ int window_x(const Geom& g, int i) {
 // absorbing layer (removed at the next step).
 __device__ __forceinline__ bool live_cell(const Geom& g, int cl) {
     if ((unsigned)cl >= (unsigned)g.ncell) return false;
+    if (!g.window && !g.pml) return true;
     int c[3];
     decompose(g, cl, c);
     return !particle_killed(g, c);
@@ -56,56 +54,102 @@ __global__ void __launch_bounds__(256) k_axis_line(Geom g, const float* __restri
 
 constexpr int kMaxBins = 2048;
 
-__global__ void __launch_bounds__(256) k_spectrum(Geom g, SpeciesDev s, const int* __restrict__ d_count, int quantity,
-                                                  double lo, double hi, int nbins, double qdv,
-                                                  double* __restrict__ charge, unsigned long long* __restrict__ count) {
+// Most of a plasma's particles fall into a few bins (its thermal bulk), where
+// one LDS atomic per particle serialises: each thread adds runs of equal bins
+// in registers, and the workgroup keeps `copies` histograms (its wavefronts
+// spread over them) as far as they fit into kMaxBins bins together.  One
+// workgroup per CU, so that a bin gets at most 256 global atomics.
+__global__ void __launch_bounds__(kSumThreads) k_spectrum(Geom g, SpeciesDev s, const int* __restrict__ d_count,
+                                                          int quantity, double lo, double hi, int nbins, int copies,
+                                                          double qdv, double* __restrict__ charge,
+                                                          unsigned long long* __restrict__ count) {
     __shared__ double hq[kMaxBins];
-    __shared__ unsigned long long hc[kMaxBins];
-    for (int b = threadIdx.x; b < nbins; b += blockDim.x) {
+    __shared__ unsigned int hc[kMaxBins];
+    for (int b = threadIdx.x; b < nbins * copies; b += kSumThreads) {
         hq[b] = 0.0;
-        hc[b] = 0ull;
+        hc[b] = 0u;
     }
     __syncthreads();
     const int n = *d_count;
-    for (int p = blockIdx.x * blockDim.x + threadIdx.x; p < n; p += gridDim.x * blockDim.x) {
-        if (!live_cell(g, s.cell[p])) continue;
-        const double a = s.u[0][p];
-        double val;
-        if (quantity == 0) {
-            const double b = s.u[1][p], c = s.u[2][p];
-            const double u2 = a * a + b * b + c * c;
-            val = u2 / (sqrt(1.0 + u2) + 1.0);   // gamma - 1 without cancellation
-        } else {
-            val = a;
+    const int step = gridDim.x * kSumThreads;
+    const int mine = ((int)(threadIdx.x >> 6) % copies) * nbins;
+    int run = -1;
+    double rq = 0.0;
+    unsigned int rc = 0u;
+    constexpr int U = 4;
+    for (int64_t p0 = (int64_t)blockIdx.x * kSumThreads + threadIdx.x; p0 < n; p0 += (int64_t)U * step) {
+        int cl[U];
+        float a[U], bb[U], cc[U], wt[U];
+#pragma unroll
+        for (int k = 0; k < U; ++k) {
+            const int64_t p = p0 + (int64_t)k * step;
+            const bool in = p < n;
+            cl[k] = in ? s.cell[p] : -1;
+            a[k] = in ? s.u[0][p] : 0.0f;
+            bb[k] = in && quantity == 0 ? s.u[1][p] : 0.0f;
+            cc[k] = in && quantity == 0 ? s.u[2][p] : 0.0f;
+            wt[k] = in ? s.w[p] : 0.0f;
         }
-        const double t = (val - lo) / (hi - lo) * (double)nbins;
-        const double idx = floor(t);
-        if (!(t >= 0.0) || !(idx < (double)nbins)) continue;
-        const int k = (int)idx;
-        atomicAdd(&hq[k], qdv * (double)s.w[p]);
-        atomicAdd(&hc[k], 1ull);
+#pragma unroll
+        for (int k = 0; k < U; ++k) {
+            if (!live_cell(g, cl[k])) continue;
+            const double ua = a[k];
+            double val;
+            if (quantity == 0) {
+                const double b = bb[k], c = cc[k];
+                const double u2 = ua * ua + b * b + c * c;
+                val = u2 / (sqrt(1.0 + u2) + 1.0);   // gamma - 1 without cancellation
+            } else {
+                val = ua;
+            }
+            const double t = (val - lo) / (hi - lo) * (double)nbins;
+            const double idx = floor(t);
+            if (!(t >= 0.0) || !(idx < (double)nbins)) continue;
+            const int bin = (int)idx;
+            if (bin != run) {
+                if (rc) {
+                    unsafeAtomicAdd(&hq[mine + run], rq);
+                    atomicAdd(&hc[mine + run], rc);
+                }
+                run = bin;
+                rq = 0.0;
+                rc = 0u;
+            }
+            rq += qdv * (double)wt[k];
+            ++rc;
+        }
+    }
+    if (rc) {
+        unsafeAtomicAdd(&hq[mine + run], rq);
+        atomicAdd(&hc[mine + run], rc);
     }
     __syncthreads();
-    for (int b = threadIdx.x; b < nbins; b += blockDim.x) {
-        if (hc[b]) {
-            atomicAdd(charge + b, hq[b]);
-            atomicAdd(count + b, hc[b]);
+    for (int b = threadIdx.x; b < nbins; b += kSumThreads) {
+        double q = 0.0;
+        unsigned int c = 0u;
+        for (int k = 0; k < copies; ++k) {
+            q += hq[k * nbins + b];
+            c += hc[k * nbins + b];
+        }
+        if (c) {
+            unsafeAtomicAdd(charge + b, q);
+            atomicAdd(count + b, (unsigned long long)c);
         }
     }
 }
 
 // sums: [0] w, [1] w u_x, then for y (2..6) and z (7..11): w r, w r^2, w p, w p^2, w p r; [12] count
-__global__ void __launch_bounds__(256) k_beam_moments(Geom g, SpeciesDev s, const int* __restrict__ d_count,
-                                                      double ux_min, double dy, double dz, double* __restrict__ sums) {
+__global__ void __launch_bounds__(kSumThreads) k_beam_moments(Geom g, SpeciesDev s, const int* __restrict__ d_count,
+                                                              double ux_min, double dy, double dz,
+                                                              double* __restrict__ part) {
     double acc[13];
 #pragma unroll
     for (int k = 0; k < 13; ++k) acc[k] = 0.0;
     const int n = *d_count;
-    for (int p = blockIdx.x * blockDim.x + threadIdx.x; p < n; p += gridDim.x * blockDim.x) {
+    for (int64_t p = (int64_t)blockIdx.x * kSumThreads + threadIdx.x; p < n; p += (int64_t)gridDim.x * kSumThreads) {
         const int cl = s.cell[p];
-        if (!live_cell(g, cl)) continue;
-        const double ux = s.u[0][p];
-        if (!(ux > ux_min)) continue;
+        const double ux = s.u[0][p];   // (loaded together with the cell)
+        if (!(ux > ux_min) || !live_cell(g, cl)) continue;
         const int j = (cl / g.n[0]) % g.n[1], k = cl / g.nxy;
         const double w = s.w[p];
         const double r[2] = {((double)j + (double)s.off[1][p]) * dy, ((double)k + (double)s.off[2][p]) * dz};
@@ -122,11 +166,14 @@ __global__ void __launch_bounds__(256) k_beam_moments(Geom g, SpeciesDev s, cons
         }
         acc[12] += 1.0;
     }
-#pragma unroll
-    for (int k = 0; k < 13; ++k) {
-        const double v = wsum(acc[k]);
-        if ((threadIdx.x & 63) == 0 && v != 0.0) atomicAdd(sums + k, v);
-    }
+    block_partials<13>(acc, part);
+}
+
+// sums[k] = the combined partials
+template <int K>
+__global__ void __launch_bounds__(64 * K) k_sums_out(const double* __restrict__ part, int nb,
+                                                     double* __restrict__ sums) {
+    combine_partials<K, K>(part, nb, [&](int k, double v) { sums[k] = v; });
 }
 
 // Compaction of the particles with u_x > ux_min: their cell, x offset, u_x
@@ -160,15 +207,19 @@ __global__ void __launch_bounds__(256) k_select(Geom g, SpeciesDev s, const int*
 }
 
 // sums: [0] e dV, [1] e x dV, [2] e x^2 dV, e = F^2 / 2 of each used component
-__global__ void __launch_bounds__(256) k_field_moments(Geom g, const float* __restrict__ F0,
-                                                       const float* __restrict__ F1, const float* __restrict__ F2,
-                                                       const float* __restrict__ F3, const float* __restrict__ F4,
-                                                       const float* __restrict__ F5, int mask, double dx, double dv,
-                                                       double* __restrict__ sums) {
+__global__ void __launch_bounds__(kSumThreads) k_field_moments(Geom g, const float* __restrict__ F0,
+                                                               const float* __restrict__ F1,
+                                                               const float* __restrict__ F2,
+                                                               const float* __restrict__ F3,
+                                                               const float* __restrict__ F4,
+                                                               const float* __restrict__ F5, int mask, double dx,
+                                                               double dv, double* __restrict__ part) {
     const float* F[6] = {F0, F1, F2, F3, F4, F5};
     const double stag[6] = {0.5, 0.0, 0.0, 0.0, 0.5, 0.5};
     double m0 = 0.0, m1 = 0.0, m2 = 0.0;
-    for (int idx = blockIdx.x * blockDim.x + threadIdx.x; idx < g.ncell; idx += gridDim.x * blockDim.x) {
+    for (int64_t i = (int64_t)blockIdx.x * kSumThreads + threadIdx.x; i < g.ncell;
+         i += (int64_t)gridDim.x * kSumThreads) {
+        const int idx = (int)i;
         const int xw = window_x(g, idx % g.n[0]);
 #pragma unroll
         for (int c = 0; c < 6; ++c) {
@@ -181,14 +232,12 @@ __global__ void __launch_bounds__(256) k_field_moments(Geom g, const float* __re
             m2 += e * x * x;
         }
     }
-    m0 = wsum(m0);
-    m1 = wsum(m1);
-    m2 = wsum(m2);
-    if ((threadIdx.x & 63) == 0) {
-        atomicAdd(sums + 0, m0);
-        atomicAdd(sums + 1, m1);
-        atomicAdd(sums + 2, m2);
-    }
+    double v[3] = {m0, m1, m2};
+    block_partials<3>(v, part);
+}
+
+__global__ void k_flag_word(const int* __restrict__ d_err, unsigned long long* __restrict__ out) {
+    *out = (unsigned long long)(unsigned)*d_err;
 }
 
 int grid_of(int64_t n) {
@@ -208,20 +257,26 @@ hipError_t launch_axis_line(const Geom& g, const float* F, int j0, int k0, doubl
     return hipGetLastError();
 }
 
+hipError_t launch_flag_word(const int* d_err, unsigned long long* out, hipStream_t st) {
+    hipLaunchKernelGGL(k_flag_word, dim3(1), dim3(1), 0, st, d_err, out);
+    return hipGetLastError();
+}
+
 hipError_t launch_spectrum(const Geom& g, const SpeciesDev& s, const int* d_count, int max_count, int quantity,
                            double lo, double hi, int nbins, double qdv, double* charge, unsigned long long* count,
                            hipStream_t st) {
     if (max_count <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_spectrum, dim3(grid_of(max_count)), dim3(256), 0, st, g, s, d_count, quantity, lo, hi, nbins,
-                       qdv, charge, count);
+    const int copies = std::max(1, std::min(kSumThreads / 64, kMaxBins / nbins));
+    hipLaunchKernelGGL(k_spectrum, dim3(sum_blocks(max_count)), dim3(kSumThreads), 0, st, g, s, d_count, quantity, lo,
+                       hi, nbins, copies, qdv, charge, count);
     return hipGetLastError();
 }
 
 hipError_t launch_beam_moments(const Geom& g, const SpeciesDev& s, const int* d_count, int max_count, double ux_min,
-                               double dy, double dz, double* sums, hipStream_t st) {
-    if (max_count <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_beam_moments, dim3(grid_of(max_count)), dim3(256), 0, st, g, s, d_count, ux_min, dy, dz,
-                       sums);
+                               double dy, double dz, double* sums, double* part, hipStream_t st) {
+    const int nb = sum_blocks(max_count);
+    hipLaunchKernelGGL(k_beam_moments, dim3(nb), dim3(kSumThreads), 0, st, g, s, d_count, ux_min, dy, dz, part);
+    hipLaunchKernelGGL(k_sums_out<13>, dim3(1), dim3(64 * 13), 0, st, part, nb, sums);
     return hipGetLastError();
 }
 
@@ -234,9 +289,11 @@ hipError_t launch_select(const Geom& g, const SpeciesDev& s, const int* d_count,
 }
 
 hipError_t launch_field_moments(const Geom& g, float* const E[3], float* const B[3], int mask, double dx, double dv,
-                                double* sums, hipStream_t st) {
-    hipLaunchKernelGGL(k_field_moments, dim3(grid_of(g.ncell)), dim3(256), 0, st, g, E[0], E[1], E[2], B[0], B[1],
-                       B[2], mask, dx, dv, sums);
+                                double* sums, double* part, hipStream_t st) {
+    const int nb = sum_blocks(g.ncell);
+    hipLaunchKernelGGL(k_field_moments, dim3(nb), dim3(kSumThreads), 0, st, g, E[0], E[1], E[2], B[0], B[1], B[2],
+                       mask, dx, dv, part);
+    hipLaunchKernelGGL(k_sums_out<3>, dim3(1), dim3(64 * 3), 0, st, part, nb, sums);
     return hipGetLastError();
 }
 

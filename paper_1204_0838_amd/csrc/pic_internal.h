@@ -239,18 +239,20 @@ hipError_t launch_clear_pml_plane(const Geom& g, const PmlDev& P, int ix, hipStr
 hipError_t launch_binomial(const Geom& g, float* const src[3], float* const dst[3], hipStream_t st);
 hipError_t launch_zero_u64(unsigned long long* p, int64_t n, hipStream_t st);
 
-// reductions (pic_reduce.hip)
+// reductions (pic_reduce.hip); part: scratch of 4096 words, free after the call
 // out[0] += sum q w dV, out[1] += sum m w (gamma-1) dV (FP64); cnt[0] += live count
 hipError_t launch_diag_particles(const Geom& g, const SpeciesDev& s, double q, double m, double dv,
                                  const int* d_count, int max_count, double* out, unsigned long long* cnt,
-                                 hipStream_t st);
+                                 double* part, hipStream_t st);
 // out[2] += 1/2 sum (E^2 + B^2) dV; maxbits[0] = max |J| as float bits
 hipError_t launch_diag_fields(const Geom& g, float* const E[3], float* const B[3], float* const J[3], double dv,
-                              double* out, unsigned int* maxbits, hipStream_t st);
+                              double* out, unsigned int* maxbits, double* part, hipStream_t st);
 // rho += sign * q w S S S (FP64 atomics) for positions (cell, off)
 hipError_t launch_rho(const Geom& g, const int* cell, float* const off[3], const float* w, double q, double sign,
                       const int* d_count, int max_count, double* rho, hipStream_t st);
 // run diagnostics (pic_diag.hip)
+// *out = the error flags, so that they come to the host with the results
+hipError_t launch_flag_word(const int* d_err, unsigned long long* out, hipStream_t st);
 int diag_max_bins();
 hipError_t launch_axis_line(const Geom& g, const float* F, int j0, int k0, double ty, double tz, double* out,
                             hipStream_t st);
@@ -258,11 +260,11 @@ hipError_t launch_spectrum(const Geom& g, const SpeciesDev& s, const int* d_coun
                            double lo, double hi, int nbins, double qdv, double* charge, unsigned long long* count,
                            hipStream_t st);
 hipError_t launch_beam_moments(const Geom& g, const SpeciesDev& s, const int* d_count, int max_count, double ux_min,
-                               double dy, double dz, double* sums, hipStream_t st);
+                               double dy, double dz, double* sums, double* part, hipStream_t st);
 hipError_t launch_select(const Geom& g, const SpeciesDev& s, const int* d_count, int max_count, double ux_min,
                          int* ocell, float* ooff, float* oux, int* oid, int* counter, hipStream_t st);
 hipError_t launch_field_moments(const Geom& g, float* const E[3], float* const B[3], int mask, double dx, double dv,
-                                double* sums, hipStream_t st);
+                                double* sums, double* part, hipStream_t st);
 
 // Scratch of the allocation-free continuity check (pic_reduce.hip): the
 // device address of this GPU's fixed scratch array (looked up once per

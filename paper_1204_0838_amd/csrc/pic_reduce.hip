@@ -3,22 +3,11 @@
 // stored FP32 positions).
 #include <mutex>
 
+#include "pic_block_sum.h"
 #include "pic_internal.h"
 #include "pic_particle_ops.h"
 
 namespace pic {
-
-__device__ __forceinline__ double wave_sum(double v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-    return v;
-}
-
-__device__ __forceinline__ float wave_maxf(float v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, 64));
-    return v;
-}
 
 __device__ __forceinline__ double wave_maxd(double v) {
 #pragma unroll
@@ -26,56 +15,91 @@ __device__ __forceinline__ double wave_maxd(double v) {
     return v;
 }
 
-__global__ void __launch_bounds__(256) k_diag_particles(Geom g, const int* __restrict__ cell, const float* __restrict__ ux,
-                                                        const float* __restrict__ uy, const float* __restrict__ uz,
-                                                        const float* __restrict__ w, const int* __restrict__ d_count,
-                                                        double qdv, double mdv, double* out,
-                                                        unsigned long long* cnt) {
+// Charge, kinetic energy and live count.  With neither a window nor a layer
+// every valid cell is live, and the cell's coordinates are not needed.
+__global__ void __launch_bounds__(kSumThreads) k_diag_particles(Geom g, const int* __restrict__ cell,
+                                                                const float* __restrict__ ux,
+                                                                const float* __restrict__ uy,
+                                                                const float* __restrict__ uz,
+                                                                const float* __restrict__ w,
+                                                                const int* __restrict__ d_count, double qdv,
+                                                                double mdv, double* __restrict__ part) {
     const int n = *d_count;
-    double q = 0.0, k = 0.0;
-    unsigned long long live = 0;
-    for (int p = blockIdx.x * blockDim.x + threadIdx.x; p < n; p += gridDim.x * blockDim.x) {
-        const int cl = cell[p];
-        if ((unsigned)cl >= (unsigned)g.ncell) continue;
-        int cc[3];
-        decompose(g, cl, cc);
-        if (particle_killed(g, cc)) continue;   // removed at the next step
-        const double a = ux[p], b = uy[p], c = uz[p];
-        const double u2 = a * a + b * b + c * c;
-        q += qdv * (double)w[p];
-        // gamma - 1 = u^2 / (gamma + 1) avoids cancellation for slow particles
-        k += mdv * (double)w[p] * (u2 / (sqrt(1.0 + u2) + 1.0));
-        ++live;
+    const bool cut = g.window || g.pml;
+    double v[3] = {0.0, 0.0, 0.0};
+    const int step = gridDim.x * kSumThreads;
+    constexpr int U = 4;   // particles per thread whose loads are in flight together
+    for (int64_t p0 = (int64_t)blockIdx.x * kSumThreads + threadIdx.x; p0 < n; p0 += (int64_t)U * step) {
+        int cl[U];
+        float a[U], b[U], c[U], wt[U];
+#pragma unroll
+        for (int k = 0; k < U; ++k) {
+            const int64_t p = p0 + (int64_t)k * step;
+            const bool in = p < n;
+            cl[k] = in ? cell[p] : -1;
+            a[k] = in ? ux[p] : 0.0f;
+            b[k] = in ? uy[p] : 0.0f;
+            c[k] = in ? uz[p] : 0.0f;
+            wt[k] = in ? w[p] : 0.0f;
+        }
+#pragma unroll
+        for (int k = 0; k < U; ++k) {
+            if ((unsigned)cl[k] >= (unsigned)g.ncell) continue;
+            if (cut) {
+                int cc[3];
+                decompose(g, cl[k], cc);
+                if (particle_killed(g, cc)) continue;   // removed at the next step
+            }
+            const double da = a[k], db = b[k], dc = c[k];
+            const double u2 = da * da + db * db + dc * dc;
+            v[0] += qdv * (double)wt[k];
+            // gamma - 1 = u^2 / (gamma + 1) avoids cancellation for slow particles
+            v[1] += mdv * (double)wt[k] * (u2 / (sqrt(1.0 + u2) + 1.0));
+            v[2] += 1.0;
+        }
     }
-    q = wave_sum(q);
-    k = wave_sum(k);
-    for (int o = 32; o > 0; o >>= 1) live += __shfl_xor(live, o, 64);
-    if ((threadIdx.x & 63) == 0) {
-        atomicAdd(out + 0, q);
-        atomicAdd(out + 1, k);
-        atomicAdd(cnt, live);
-    }
+    block_partials<3>(v, part);
 }
 
-__global__ void __launch_bounds__(256) k_diag_fields(int ncell, const float* __restrict__ E0,
-                                                     const float* __restrict__ E1, const float* __restrict__ E2,
-                                                     const float* __restrict__ B0, const float* __restrict__ B1,
-                                                     const float* __restrict__ B2, const float* __restrict__ J0,
-                                                     const float* __restrict__ J1, const float* __restrict__ J2,
-                                                     double hdv, double* out, unsigned int* maxbits) {
+// out[0] += charge, out[1] += kinetic energy, *cnt += live particles
+__global__ void __launch_bounds__(3 * 64) k_diag_particles_out(const double* __restrict__ part, int nb, double* out,
+                                                               unsigned long long* cnt) {
+    combine_partials<3, 3>(part, nb, [&](int k, double v) {
+        if (k < 2) out[k] += v;
+        else *cnt += (unsigned long long)v;
+    });
+}
+
+__global__ void __launch_bounds__(kSumThreads) k_diag_fields(int ncell, const float* __restrict__ E0,
+                                                             const float* __restrict__ E1,
+                                                             const float* __restrict__ E2,
+                                                             const float* __restrict__ B0,
+                                                             const float* __restrict__ B1,
+                                                             const float* __restrict__ B2,
+                                                             const float* __restrict__ J0,
+                                                             const float* __restrict__ J1,
+                                                             const float* __restrict__ J2, double hdv,
+                                                             double* __restrict__ part) {
     double e = 0.0;
     float mj = 0.0f;
-    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < ncell; i += gridDim.x * blockDim.x) {
+#pragma unroll 2
+    for (int64_t i = (int64_t)blockIdx.x * kSumThreads + threadIdx.x; i < ncell;
+         i += (int64_t)gridDim.x * kSumThreads) {
         const double a0 = E0[i], a1 = E1[i], a2 = E2[i], b0 = B0[i], b1 = B1[i], b2 = B2[i];
         e += a0 * a0 + a1 * a1 + a2 * a2 + b0 * b0 + b1 * b1 + b2 * b2;
         mj = fmaxf(mj, fmaxf(fabsf(J0[i]), fmaxf(fabsf(J1[i]), fabsf(J2[i]))));
     }
-    e = wave_sum(e);
-    mj = wave_maxf(mj);
-    if ((threadIdx.x & 63) == 0) {
-        atomicAdd(out + 2, e * hdv);
-        atomicMax(maxbits, __float_as_uint(mj));   // non-negative floats order like their bits
-    }
+    double v[2] = {e * hdv, (double)mj};
+    block_partials<1>(v, part);
+}
+
+// out[2] += field energy, *maxbits = max |J| (float bits)
+__global__ void __launch_bounds__(2 * 64) k_diag_fields_out(const double* __restrict__ part, int nb, double* out,
+                                                            unsigned int* maxbits) {
+    combine_partials<1, 2>(part, nb, [&](int k, double v) {
+        if (k == 0) out[2] += v;
+        else *maxbits = __float_as_uint((float)v);
+    });
 }
 
 __global__ void __launch_bounds__(256) k_rho(Geom g, const int* __restrict__ cell, const float* __restrict__ ox,
@@ -165,17 +189,21 @@ static int grid_for(int64_t n) {
 
 hipError_t launch_diag_particles(const Geom& g, const SpeciesDev& s, double q, double m, double dv,
                                  const int* d_count, int max_count, double* out, unsigned long long* cnt,
-                                 hipStream_t st) {
+                                 double* part, hipStream_t st) {
     if (max_count <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_diag_particles, dim3(grid_for(max_count)), dim3(256), 0, st, g, s.cell, s.u[0], s.u[1], s.u[2],
-                       s.w, d_count, q * dv, m * dv, out, cnt);
+    const int nb = sum_blocks(max_count);
+    hipLaunchKernelGGL(k_diag_particles, dim3(nb), dim3(kSumThreads), 0, st, g, s.cell, s.u[0], s.u[1], s.u[2], s.w,
+                       d_count, q * dv, m * dv, part);
+    hipLaunchKernelGGL(k_diag_particles_out, dim3(1), dim3(3 * 64), 0, st, part, nb, out, cnt);
     return hipGetLastError();
 }
 
 hipError_t launch_diag_fields(const Geom& g, float* const E[3], float* const B[3], float* const J[3], double dv,
-                              double* out, unsigned int* maxbits, hipStream_t st) {
-    hipLaunchKernelGGL(k_diag_fields, dim3(grid_for(g.ncell)), dim3(256), 0, st, g.ncell, E[0], E[1], E[2], B[0],
-                       B[1], B[2], J[0], J[1], J[2], 0.5 * dv, out, maxbits);
+                              double* out, unsigned int* maxbits, double* part, hipStream_t st) {
+    const int nb = sum_blocks(g.ncell);
+    hipLaunchKernelGGL(k_diag_fields, dim3(nb), dim3(kSumThreads), 0, st, g.ncell, E[0], E[1], E[2], B[0], B[1], B[2],
+                       J[0], J[1], J[2], 0.5 * dv, part);
+    hipLaunchKernelGGL(k_diag_fields_out, dim3(1), dim3(2 * 64), 0, st, part, nb, out, maxbits);
     return hipGetLastError();
 }
 
