@@ -272,6 +272,8 @@ struct pic_ctx {
     Prof prof;
     // a split-path step is in progress (pic_gather_push since the last pic_field_step)
     bool mid_step = false;
+    // the accumulator may hold contributions (it is zero between whole steps)
+    bool acc_used = false;
     // the J planes hold the post-processed current (binomial or denoiser
     // output) rather than the raw deposit: the continuity check filters rho
     bool j_filtered = false;
@@ -461,7 +463,8 @@ pic_status laser_plane(pic_ctx* c, bool e_plane, double h, double t) {
 
 // Field update of the step that starts at t = step dt: B half step, E step,
 // B half step (Section 2, eq. 2.1), with the laser source while it is active.
-pic_status field_update(pic_ctx* c, float* const Juse[3]) {
+// The current: J (with Jcopy, stored there too), or acc read out into J and cleared.
+pic_status field_update(pic_ctx* c, float* const J[3], float* const Jcopy[3], unsigned long long* acc) {
     FieldPtrs f = fields_of(c);
     const int pd = c->desc.solver == PIC_SOLVER_PD;
     const double dt = c->desc.dt, t = c->step * dt;
@@ -469,7 +472,9 @@ pic_status field_update(pic_ctx* c, float* const Juse[3]) {
     const PmlDev* pml = c->g.pml ? &c->pml : nullptr;
     HIPCHK(c, launch_bhalf(c->g, pd, c->pd, f.E, f.B, (float)(0.5 * dt), pml, 1, c->stream));
     if (laser) PICCHK(laser_plane(c, false, 0.5 * dt, t));
-    HIPCHK(c, launch_efull(c->g, f.E, f.B, Juse, pml, c->stream));
+    double sc[3];
+    jscale(c, sc);
+    HIPCHK(c, launch_efull(c->g, f.E, f.B, J, Jcopy, acc, sc, pml, c->stream));
     if (laser) PICCHK(laser_plane(c, true, dt, t + 0.5 * dt));
     HIPCHK(c, launch_bhalf(c->g, pd, c->pd, f.E, f.B, (float)(0.5 * dt), pml, 0, c->stream));
     if (laser) PICCHK(laser_plane(c, false, 0.5 * dt, t + dt));
@@ -563,15 +568,21 @@ pic_status denoise(pic_ctx* c, float* const Jin[3], float* const Jout[3]) {
     return PIC_OK;
 }
 
+// The post-processed J in the workspace current (tmp); jpost must not be none.
+pic_status filter_to(pic_ctx* c, float* const tmp[3]) {
+    if (c->desc.jpost == PIC_JPOST_BINOMIAL)
+        HIPCHK(c, launch_binomial(c->g, c->f.J, tmp, c->stream));
+    else
+        PICCHK(denoise(c, c->f.J, tmp));
+    return PIC_OK;
+}
+
 // J post-processing in place (through the workspace current).
 pic_status filter_in_place(pic_ctx* c) {
     if (c->desc.jpost == PIC_JPOST_NONE) return PIC_OK;
     float* tmp[3];
     jtmp_of(c, tmp);
-    if (c->desc.jpost == PIC_JPOST_BINOMIAL)
-        HIPCHK(c, launch_binomial(c->g, c->f.J, tmp, c->stream));
-    else
-        PICCHK(denoise(c, c->f.J, tmp));
+    PICCHK(filter_to(c, tmp));
     for (int a = 0; a < 3; ++a)
         HIPCHK(c, hipMemcpyAsync(c->f.J[a], tmp[a], (size_t)c->g.ncell * 4, hipMemcpyDeviceToDevice, c->stream));
     c->j_filtered = true;
@@ -582,26 +593,25 @@ pic_status filter_in_place(pic_ctx* c) {
 pic_status finish_step(pic_ctx* c) {
     double sc[3];
     jscale(c, sc);
-    float* Juse[3] = {c->f.J[0], c->f.J[1], c->f.J[2]};
     hipEvent_t t0, t1;
     PICCHK(prof_mark(c, &t0));
-    if (c->desc.jpost == PIC_JPOST_BINOMIAL) {
-        float* tmp[3];
-        jtmp_of(c, tmp);
-        HIPCHK(c, launch_jfinal(c->g, acc_of(c), tmp, sc, 1, c->stream));
-        HIPCHK(c, launch_binomial(c->g, tmp, c->f.J, c->stream));
-    } else if (c->desc.jpost == PIC_JPOST_NONE) {
-        HIPCHK(c, launch_jfinal(c->g, acc_of(c), c->f.J, sc, 1, c->stream));
+    unsigned long long* acc = nullptr;
+    if (c->desc.jpost == PIC_JPOST_NONE) {
+        acc = acc_of(c);   // the E update reads it out
     } else {
         float* tmp[3];
         jtmp_of(c, tmp);
         HIPCHK(c, launch_jfinal(c->g, acc_of(c), tmp, sc, 1, c->stream));
-        PICCHK(denoise(c, tmp, c->f.J));
+        if (c->desc.jpost == PIC_JPOST_BINOMIAL)
+            HIPCHK(c, launch_binomial(c->g, tmp, c->f.J, c->stream));
+        else
+            PICCHK(denoise(c, tmp, c->f.J));
     }
     c->j_filtered = c->desc.jpost != PIC_JPOST_NONE;
     PICCHK(prof_end(c, PH_JPOST, t0));
     PICCHK(prof_mark(c, &t1));
-    PICCHK(field_update(c, Juse));
+    PICCHK(field_update(c, c->f.J, nullptr, acc));
+    c->acc_used = false;   // (read out and cleared above, or by the read-out kernel)
     PICCHK(prof_end(c, PH_FIELD, t1));
     return end_step(c);
 }
@@ -876,6 +886,7 @@ pic_status batch_one_step(pic_batch* b) {
                 sp.sort_step = c->step;
             }
             sp.prev_valid = false;
+            c->acc_used = true;
             lds = std::max(lds, tile_lds_bytes(c->tl.t, c->tl.guard));
             all_888g1 = all_888g1 && c->tl.t.T[0] == 8 && c->tl.t.T[1] == 8 && c->tl.t.T[2] == 8 && c->tl.guard == 1;
         }
@@ -897,12 +908,13 @@ pic_status batch_one_step(pic_batch* b) {
         // for the field phase and re-stage the others then
     }
     // current read-out and field update (member-wide parts of the last table)
-    int max_cells = 0, max_plane = 0, max_btiles = 0;
+    int max_cells = 0, max_plane = 0, max_btiles = 0, max_bin = 0;
     bool any_bin = false, any_laser = false, any_move = false;
     for (int i = 0; i < n; ++i) {
         pic_ctx* c = b->m[i];
         max_cells = std::max(max_cells, c->g.ncell);
         max_btiles = std::max(max_btiles, bhalf_tiles(c->g.n));
+        max_bin = std::max(max_bin, binomial_tiles(c->g.n));
         max_plane = std::max(max_plane, c->g.n[1] * c->g.n[2]);
         any_bin = any_bin || c->desc.jpost == PIC_JPOST_BINOMIAL;
         const double t = c->step * c->desc.dt;
@@ -911,8 +923,10 @@ pic_status batch_one_step(pic_batch* b) {
     }
     hipEvent_t t3, t4, t5;
     PICCHK(bmark(b, &t3));
-    BHIPCHK(b, launch_batch_jfinal(dtab, n, max_cells, b->stream));
-    if (any_bin) BHIPCHK(b, launch_batch_binomial(dtab, n, max_cells, b->stream));
+    if (any_bin) {
+        BHIPCHK(b, launch_batch_jfinal(dtab, n, max_cells, b->stream));
+        BHIPCHK(b, launch_batch_binomial(dtab, n, max_bin, b->stream));
+    }
     PICCHK(bend(b, PH_JPOST, t3));
     PICCHK(bmark(b, &t4));
     BHIPCHK(b, launch_batch_bhalf(dtab, n, max_btiles, b->stream));
@@ -962,6 +976,7 @@ pic_status batch_one_step(pic_batch* b) {
     for (int i = 0; i < n; ++i) {
         pic_ctx* c = b->m[i];
         const bool move = c->g.window && c->step + 1 >= c->window_start;
+        c->acc_used = false;   // (cleared by the read-out or the E update)
         c->step += 1;
         if (move) {
             c->g.origin = c->g.origin + 1 == c->g.n[0] ? 0 : c->g.origin + 1;
@@ -1121,6 +1136,7 @@ pic_status pic_deposit(pic_ctx* c, int32_t s) {
     PICCHK(check_species(c, s));
     Species& sp = c->sp[s];
     if (!sp.prev_valid) return fail(c, PIC_ESTATE, "deposit needs a preceding gather_push");
+    c->acc_used = true;
     if (sp.bound > kDepositTilesMin + c->g.ncell / 128) {
         // tile by tile through an index list by the old cells (every particle
         // with a valid old cell, also one that the window has since left
@@ -1148,10 +1164,17 @@ pic_status pic_deposit(pic_ctx* c, int32_t s) {
 
 pic_status pic_field_step(pic_ctx* c) {
     if (!c) return PIC_EINVAL;
-    float* Juse[3] = {c->f.J[0], c->f.J[1], c->f.J[2]};
-    PICCHK(filter_in_place(c));
-    PICCHK(field_update(c, Juse));
-    HIPCHK(c, launch_zero_u64(acc_of(c), 3 * (int64_t)c->g.ncell, c->stream));
+    if (c->desc.jpost == PIC_JPOST_NONE) {
+        PICCHK(field_update(c, c->f.J, nullptr, nullptr));
+    } else {   // the E update also stores the post-processed current to J
+        float* tmp[3];
+        jtmp_of(c, tmp);
+        PICCHK(filter_to(c, tmp));
+        PICCHK(field_update(c, tmp, c->f.J, nullptr));
+        c->j_filtered = true;
+    }
+    if (c->acc_used) HIPCHK(c, launch_zero_u64(acc_of(c), 3 * (int64_t)c->g.ncell, c->stream));
+    c->acc_used = false;
     c->mid_step = false;
     return end_step(c);
 }
@@ -1174,6 +1197,7 @@ pic_status pic_step(pic_ctx* c, int32_t nsteps) {
                 if (c->prof.on) c->prof.sorts += 1;
                 gather = true;
             }
+            c->acc_used = true;
             Small* sm = small_of(c);
             PICCHK(prof_mark(c, &t1));
             int* rest_idx = reinterpret_cast<int*>(c->ws + c->L.sort_rank) + sp.base;
@@ -1555,6 +1579,7 @@ pic_status pic_copy_in(pic_ctx* c, const void* host_blob, size_t bytes) {
         sp.prev_valid = false;
     }
     HIPCHK(c, launch_zero_u64(acc_of(c), 3 * (int64_t)c->g.ncell, c->stream));
+    c->acc_used = false;
     c->step = h.step;
     c->shift = h.shift;
     c->g.origin = h.origin;

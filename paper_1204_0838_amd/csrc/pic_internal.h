@@ -140,7 +140,9 @@ hipError_t launch_batch_tile(const InstDesc* d, const int* tile_begin, int n, in
                              size_t lds_bytes, bool all_888g1, hipStream_t st);
 hipError_t launch_batch_rest(const InstDesc* d, int n, hipStream_t st);
 hipError_t launch_batch_jfinal(const InstDesc* d, int n, int max_cells, hipStream_t st);
-hipError_t launch_batch_binomial(const InstDesc* d, int n, int max_cells, hipStream_t st);
+// (max_tiles = the largest binomial_tiles of a member)
+hipError_t launch_batch_binomial(const InstDesc* d, int n, int max_tiles, hipStream_t st);
+int binomial_tiles(const int n[3]);
 // B half step over the members' tiles (max_tiles = the largest bhalf_tiles of a member)
 hipError_t launch_batch_bhalf(const InstDesc* d, int n, int max_tiles, hipStream_t st);
 int bhalf_tiles(const int n[3]);
@@ -233,8 +235,10 @@ hipError_t launch_tile_rest(const Geom& g, const FieldPtrs& f, const SpeciesDev&
 // B half steps advances the layer's B arrays, the second only reads them.
 hipError_t launch_bhalf(const Geom& g, int pd, const PDCoef& c, float* const E[3], float* const B[3], float h,
                         const PmlDev* pml, int store, hipStream_t st);
-hipError_t launch_efull(const Geom& g, float* const E[3], float* const B[3], float* const J[3], const PmlDev* pml,
-                        hipStream_t st);
+// acc null: the current is J; with Jcopy it is stored there too.  acc: the
+// current is acc (times scale), stored to J, and acc is cleared.
+hipError_t launch_efull(const Geom& g, float* const E[3], float* const B[3], float* const J[3], float* const Jcopy[3],
+                        unsigned long long* acc, const double scale[3], const PmlDev* pml, hipStream_t st);
 hipError_t launch_clear_pml_plane(const Geom& g, const PmlDev& P, int ix, hipStream_t st);
 hipError_t launch_binomial(const Geom& g, float* const src[3], float* const dst[3], hipStream_t st);
 hipError_t launch_zero_u64(unsigned long long* p, int64_t n, hipStream_t st);

@@ -111,15 +111,15 @@ __global__ void k_jfinal(unsigned long long* __restrict__ acc, float* J0, float*
     jfinal_one(acc, J0, J1, J2, ncell, s0, s1, s2, zero_acc, i);
 }
 
-// Batched read-out of the current (accumulator cleared); into the workspace
-// current when the binomial filter follows.
+// Batched read-out of the current (accumulator cleared) of the members whose
+// binomial filter follows, into the workspace current (the E update reads the
+// others' accumulators itself).
 __global__ void __launch_bounds__(256) k_batch_jfinal(const InstDesc* __restrict__ tab) {
     const InstDesc& d = tab[blockIdx.y];
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     const int ncell = d.g.ncell;
-    if (i >= ncell) return;
-    float* const* J = d.jpost ? d.Jt : d.J;
-    jfinal_one(d.acc, J[0], J[1], J[2], ncell, d.jscale[0], d.jscale[1], d.jscale[2], 1, i);
+    if (!d.jpost || i >= ncell) return;
+    jfinal_one(d.acc, d.Jt[0], d.Jt[1], d.Jt[2], ncell, d.jscale[0], d.jscale[1], d.jscale[2], 1, i);
 }
 
 hipError_t launch_batch_jfinal(const InstDesc* d, int n, int max_cells, hipStream_t st) {
