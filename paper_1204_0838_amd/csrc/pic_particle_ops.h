@@ -95,46 +95,15 @@ __device__ __forceinline__ bool moved(const int c0[3], const int c1[3], const fl
 // the two scaled arrays of the first transverse axis computed once per
 // component, and Q and P are multiplied exactly and rounded once.
 // Callers skip particles that did not move (every contribution is zero).
-//
-// CELLREL: the indices passed to Emit::add are slots relative to the old
-// cell instead of union nodes.  Along an axis transverse to the component,
-// slots 0..3 are the nodes at cell - 1 .. cell + 2 whatever the crossing and
-// slot 4 is the node a crossing adds (cell + 3 forward, cell - 2 backward);
-// along the component's own axis slots 0..2 are cell - 1 .. cell + 1 and
-// slot 3 is cell + 2 (forward) or cell - 2 (backward).  A backward crossing
-// (union base -2) just rotates its arrays by one place, so every value goes
-// to the same node as with union indices, bit for bit.
-__device__ __forceinline__ void rotate_back5(bool back, float v[5]) {
-    const float v0 = v[0];
-#pragma unroll
-    for (int j = 0; j < 4; ++j) v[j] = back ? v[j + 1] : v[j];
-    v[4] = back ? v0 : v[4];
-}
-
-__device__ __forceinline__ void rotate_back4(bool back, float v[4]) {
-    const float v0 = v[0];
-#pragma unroll
-    for (int j = 0; j < 3; ++j) v[j] = back ? v[j + 1] : v[j];
-    v[3] = back ? v0 : v[3];
-}
-
-template <bool CELLREL = false, class Emit>
+template <class Emit>
 __device__ __forceinline__ void esirkepov(const Axis5 A[3], float qw, Emit& em) {
     const float qw40 = qw * PIC_FIX_SCALE;   // exact: a power-of-two scale
     const float qw12 = qw40 * (1.0f / 12.0f);
-    float M[3][5], dS[3][5];
+    float M[3][5];
 #pragma unroll
-    for (int d = 0; d < 3; ++d) {
+    for (int d = 0; d < 3; ++d)
 #pragma unroll
-        for (int j = 0; j < 5; ++j) {
-            M[d][j] = fmaf(0.5f, A[d].dS[j], A[d].S0[j]);
-            dS[d][j] = A[d].dS[j];
-        }
-        if (CELLREL) {
-            rotate_back5(A[d].base < -1, M[d]);
-            rotate_back5(A[d].base < -1, dS[d]);
-        }
-    }
+        for (int j = 0; j < 5; ++j) M[d][j] = fmaf(0.5f, A[d].dS[j], A[d].S0[j]);
 #pragma unroll
     for (int comp = 0; comp < 3; ++comp) {
         const int t1 = comp == 0 ? 1 : (comp == 1 ? 2 : 0);
@@ -143,7 +112,6 @@ __device__ __forceinline__ void esirkepov(const Axis5 A[3], float qw, Emit& em) 
         P[0] = A[comp].dS[0];
 #pragma unroll
         for (int a = 1; a < 4; ++a) P[a] = P[a - 1] + A[comp].dS[a];
-        if (CELLREL) rotate_back4(A[comp].base < -1, P);
         double Pd[4];
 #pragma unroll
         for (int a = 0; a < 4; ++a) Pd[a] = (double)P[a];
@@ -152,7 +120,7 @@ __device__ __forceinline__ void esirkepov(const Axis5 A[3], float qw, Emit& em) 
 #pragma unroll
         for (int b = 0; b < 5; ++b) {
             Mq[b] = qw40 * M[t1][b];
-            dSq[b] = qw12 * dS[t1][b];
+            dSq[b] = qw12 * A[t1].dS[b];
         }
 #pragma unroll
         for (int cc = 0; cc < 5; ++cc) {
@@ -160,7 +128,7 @@ __device__ __forceinline__ void esirkepov(const Axis5 A[3], float qw, Emit& em) 
 #pragma unroll
             for (int b = 0; b < 5; ++b) {
                 if (b >= lb) continue;
-                const double qy = (double)fmaf(dSq[b], dS[t2][cc], Mq[b] * M[t2][cc]);
+                const double qy = (double)fmaf(dSq[b], A[t2].dS[cc], Mq[b] * M[t2][cc]);
 #pragma unroll
                 for (int a = 0; a < 4; ++a) {
                     if (a >= la) continue;
@@ -174,6 +142,89 @@ __device__ __forceinline__ void esirkepov(const Axis5 A[3], float qw, Emit& em) 
                 }
             }
         }
+    }
+}
+
+// The same contributions in slots relative to the old cell, for the LDS
+// deposits.  Along an axis transverse to the component, core slots 0..3 are
+// the nodes at cell - 1 .. cell + 2 whatever the crossing, and slot 4 is the
+// node that a crossing adds (cell + 3 forward, cell - 2 backward); along the
+// component's own axis core slots 0..2 are cell - 1 .. cell + 1 and slot 3 is
+// cell + 2 (forward) or cell - 2 (backward).  The old weights fill the core;
+// the new ones sit one slot further on (forward, slot 4 the last of them) or
+// back (backward, slot 4 the first).  Every sum is Axis5's and esirkepov's,
+// in their order, so each node gets the same value bit for bit.
+struct AxisSlots {
+    float M[5], dS[5];   // S0 + dS / 2, dS; slot 4: the crossing's node
+    float P[4];          // running sum of dS; slot 3: the crossing's
+};
+
+__device__ __forceinline__ void axis_slots(int di, float d0, float d1, AxisSlots& A) {
+    const bool fwd = di > 0, back = di < 0;
+    const float r1 = di == 0 ? d0 : (fwd ? 0.0f : 1.0f);
+    const float r0 = di == 0 ? d0 : (fwd ? 1.0f : 0.0f);
+    float W[4], Dn[4], Do[4];
+    spline4(d0, W);
+    dweight4(d1, r1, Dn);
+    dweight4(r0, d0, Do);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        const float dn = fwd ? (j > 0 ? Dn[j - 1] : 0.0f) : (back ? (j < 3 ? Dn[j + 1] : 0.0f) : Dn[j]);
+        A.dS[j] = dn + Do[j];
+        A.M[j] = fmaf(0.5f, A.dS[j], W[j]);
+    }
+    A.dS[4] = fwd ? Dn[3] : Dn[0];
+    A.M[4] = 0.5f * A.dS[4];
+    A.P[0] = back ? A.dS[4] + A.dS[0] : A.dS[0];
+    A.P[1] = A.P[0] + A.dS[1];
+    A.P[2] = A.P[1] + A.dS[2];
+    A.P[3] = back ? A.dS[4] : A.P[2] + A.dS[3];
+}
+
+// Emit::add(comp, sx, sy, sz, k) receives the contributions by slot.  A
+// component's contributions over the slots [a0, a1) of its own axis and
+// [b0, b1) x [c0, c1) of the next two.
+template <int COMP, class Emit>
+__device__ __forceinline__ void emit_slots(const AxisSlots A[3], float qw, int a0, int a1, int b0, int b1, int c0,
+                                           int c1, const Emit& em) {
+    constexpr int t1 = COMP == 0 ? 1 : (COMP == 1 ? 2 : 0);
+    constexpr int t2 = COMP == 0 ? 2 : (COMP == 1 ? 0 : 1);
+    const float qw40 = qw * PIC_FIX_SCALE;   // exact: a power-of-two scale
+    const float qw12 = qw40 * (1.0f / 12.0f);
+#pragma unroll
+    for (int cc = 0; cc < 5; ++cc)
+#pragma unroll
+        for (int b = 0; b < 5; ++b) {
+            if (cc < c0 || cc >= c1 || b < b0 || b >= b1) continue;   // (compile-time ranges)
+            const float Mq = qw40 * A[t1].M[b], dSq = qw12 * A[t1].dS[b];
+            const double qy = (double)fmaf(dSq, A[t2].dS[cc], Mq * A[t2].M[cc]);
+#pragma unroll
+            for (int a = 0; a < 4; ++a) {
+                if (a < a0 || a >= a1) continue;
+                const long long k = fix_mul(qy, (double)A[COMP].P[a]);
+                if (COMP == 0)
+                    em.add(0, a, b, cc, k);
+                else if (COMP == 1)
+                    em.add(1, cc, a, b, k);
+                else
+                    em.add(2, b, cc, a, k);
+            }
+        }
+}
+
+// The contributions of one component that involve a crossing's slot (x: which
+// axes were crossed), by how many of its three axes were.
+template <int COMP, class Emit>
+__device__ __forceinline__ void emit_crossing(const AxisSlots A[3], float qw, const bool x[3], const Emit& em) {
+    const bool xa = x[COMP], xb = x[COMP == 0 ? 1 : (COMP == 1 ? 2 : 0)], xc = x[COMP == 0 ? 2 : (COMP == 1 ? 0 : 1)];
+    if (xa) emit_slots<COMP>(A, qw, 3, 4, 0, 4, 0, 4, em);
+    if (xb) emit_slots<COMP>(A, qw, 0, 3, 4, 5, 0, 4, em);
+    if (xc) emit_slots<COMP>(A, qw, 0, 3, 0, 4, 4, 5, em);
+    if (xa && xb) emit_slots<COMP>(A, qw, 3, 4, 4, 5, 0, 4, em);
+    if (xa && xc) emit_slots<COMP>(A, qw, 3, 4, 0, 4, 4, 5, em);
+    if (xb && xc) {
+        emit_slots<COMP>(A, qw, 0, 3, 4, 5, 4, 5, em);
+        if (xa) emit_slots<COMP>(A, qw, 3, 4, 4, 5, 4, 5, em);
     }
 }
 
