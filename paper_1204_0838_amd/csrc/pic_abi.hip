@@ -52,7 +52,7 @@ Tiling tiling_of(const pic_grid_desc* d) {
     r.t.ntiles = r.t.nt[0] * r.t.nt[1] * r.t.nt[2];
     r.t.tcells = r.t.T[0] * r.t.T[1] * r.t.T[2];
     r.guard = d->guard < 0 ? 1 : d->guard;
-    r.threads = d->threads > 0 ? d->threads : 512;
+    r.threads = d->threads > 0 ? d->threads : 0;   // 0: chosen at the launch
     r.interleave = d->interleave > 0 ? d->interleave : 0;   // 0: level order
     r.sort_interval = d->sort_interval > 0 ? d->sort_interval : 2;
     return r;
@@ -167,6 +167,9 @@ struct Species {
     int64_t bound;           // host upper bound of the particle count
     int64_t sort_step;       // step of the last sort
     bool sorted;             // tile ranges valid
+    bool appended = false;   // particles may have been added since the last sort
+    bool loose = false;      // particles may have moved other than by pic_step's steps since then
+                             // (the staged path, or a caller that was handed the arrays)
     bool prev_valid;         // x^n of the last split gather_push kept
 };
 
@@ -463,8 +466,10 @@ pic_status laser_plane(pic_ctx* c, bool e_plane, double h, double t) {
 
 // Field update of the step that starts at t = step dt: B half step, E step,
 // B half step (Section 2, eq. 2.1), with the laser source while it is active.
-// The current: J (with Jcopy, stored there too), or acc read out into J and cleared.
-pic_status field_update(pic_ctx* c, float* const J[3], float* const Jcopy[3], unsigned long long* acc) {
+// The current: J (with Jcopy, stored there too), or with `scale` acc read out
+// into J.  acc (may be null) is cleared.
+pic_status field_update(pic_ctx* c, float* const J[3], float* const Jcopy[3], unsigned long long* acc,
+                        const double* scale) {
     FieldPtrs f = fields_of(c);
     const int pd = c->desc.solver == PIC_SOLVER_PD;
     const double dt = c->desc.dt, t = c->step * dt;
@@ -472,9 +477,7 @@ pic_status field_update(pic_ctx* c, float* const J[3], float* const Jcopy[3], un
     const PmlDev* pml = c->g.pml ? &c->pml : nullptr;
     HIPCHK(c, launch_bhalf(c->g, pd, c->pd, f.E, f.B, (float)(0.5 * dt), pml, 1, c->stream));
     if (laser) PICCHK(laser_plane(c, false, 0.5 * dt, t));
-    double sc[3];
-    jscale(c, sc);
-    HIPCHK(c, launch_efull(c->g, f.E, f.B, J, Jcopy, acc, sc, pml, c->stream));
+    HIPCHK(c, launch_efull(c->g, f.E, f.B, J, Jcopy, acc, scale, pml, c->stream));
     if (laser) PICCHK(laser_plane(c, true, dt, t + 0.5 * dt));
     HIPCHK(c, launch_bhalf(c->g, pd, c->pd, f.E, f.B, (float)(0.5 * dt), pml, 0, c->stream));
     if (laser) PICCHK(laser_plane(c, false, 0.5 * dt, t + dt));
@@ -504,6 +507,7 @@ pic_status inject_slab(pic_ctx* c, int32_t s, int32_t xb, int32_t xe) {
     HIPCHK(c, launch_inject(c->g, P, dev_of(c, sp), (long long)c->shift, xb, xe, &small_of(c)->count[s],
                             (int)sp.user.capacity, &small_of(c)->err, c->stream));
     sp.bound += most;
+    sp.appended = true;
     return PIC_OK;
 }
 
@@ -543,9 +547,10 @@ pic_status sort_species(pic_ctx* c, int32_t s, bool copy) {
     HIPCHK(c, launch_sort(c->g, c->tl.t, dev_from(c, sp, sp.cur), dev_from(c, sp, sp.alt), &sm->count[s],
                           &sm->sorted[s], (int)sp.bound, hist_of(c), rank, reinterpret_cast<int*>(c->ws + c->L.sums),
                           level_of(c, sp), reinterpret_cast<int*>(c->ws + c->L.sort_lc), c->tl.interleave,
-                          toff_of(c, s), copy, sp.sorted, c->stream));
+                          toff_of(c, s), copy, sp.sorted, sp.appended, c->stream));
     std::swap(sp.cur, sp.alt);
     sp.sorted = true;
+    sp.appended = sp.loose = false;
     sp.sort_step = c->step;
     sp.prev_valid = false;
     return PIC_OK;
@@ -571,7 +576,7 @@ pic_status denoise(pic_ctx* c, float* const Jin[3], float* const Jout[3]) {
 // The post-processed J in the workspace current (tmp); jpost must not be none.
 pic_status filter_to(pic_ctx* c, float* const tmp[3]) {
     if (c->desc.jpost == PIC_JPOST_BINOMIAL)
-        HIPCHK(c, launch_binomial(c->g, c->f.J, tmp, c->stream));
+        HIPCHK(c, launch_binomial(c->g, c->f.J, nullptr, nullptr, tmp, c->stream));
     else
         PICCHK(denoise(c, c->f.J, tmp));
     return PIC_OK;
@@ -595,22 +600,22 @@ pic_status finish_step(pic_ctx* c) {
     jscale(c, sc);
     hipEvent_t t0, t1;
     PICCHK(prof_mark(c, &t0));
-    unsigned long long* acc = nullptr;
-    if (c->desc.jpost == PIC_JPOST_NONE) {
-        acc = acc_of(c);   // the E update reads it out
-    } else {
+    // without post-processing the E update reads the accumulator out; the
+    // binomial filter reads it, and the E update clears it
+    unsigned long long* acc = acc_of(c);
+    if (c->desc.jpost == PIC_JPOST_BINOMIAL) {
+        HIPCHK(c, launch_binomial(c->g, nullptr, acc, sc, c->f.J, c->stream));
+    } else if (c->desc.jpost == PIC_JPOST_DENOISER) {
         float* tmp[3];
         jtmp_of(c, tmp);
-        HIPCHK(c, launch_jfinal(c->g, acc_of(c), tmp, sc, 1, c->stream));
-        if (c->desc.jpost == PIC_JPOST_BINOMIAL)
-            HIPCHK(c, launch_binomial(c->g, tmp, c->f.J, c->stream));
-        else
-            PICCHK(denoise(c, tmp, c->f.J));
+        HIPCHK(c, launch_jfinal(c->g, acc, tmp, sc, 1, c->stream));
+        PICCHK(denoise(c, tmp, c->f.J));
+        acc = nullptr;
     }
     c->j_filtered = c->desc.jpost != PIC_JPOST_NONE;
     PICCHK(prof_end(c, PH_JPOST, t0));
     PICCHK(prof_mark(c, &t1));
-    PICCHK(field_update(c, c->f.J, nullptr, acc));
+    PICCHK(field_update(c, c->f.J, nullptr, acc, c->desc.jpost == PIC_JPOST_NONE ? sc : nullptr));
     c->acc_used = false;   // (read out and cleared above, or by the read-out kernel)
     PICCHK(prof_end(c, PH_FIELD, t1));
     return end_step(c);
@@ -769,12 +774,7 @@ void fill_desc(pic_ctx* c, int32_t s, InstDesc& d) {
     d.sdiv = make_sortdiv(c->g, c->tl.t);
     d.c = c->pd;
     d.f = fields_of(c);
-    float* jt[3];
-    jtmp_of(c, jt);
-    for (int a = 0; a < 3; ++a) {
-        d.J[a] = c->f.J[a];
-        d.Jt[a] = jt[a];
-    }
+    for (int a = 0; a < 3; ++a) d.J[a] = c->f.J[a];
     d.jpost = c->desc.jpost == PIC_JPOST_BINOMIAL;
     d.sorting = !sp.sorted || c->step - sp.sort_step >= c->tl.sort_interval;
     d.s = dev_from(c, sp, sp.cur);
@@ -883,6 +883,7 @@ pic_status batch_one_step(pic_batch* b) {
                 max_tcells = std::max(max_tcells, c->tl.t.tcells);
                 std::swap(sp.cur, sp.alt);
                 sp.sorted = true;
+                sp.appended = sp.loose = false;
                 sp.sort_step = c->step;
             }
             sp.prev_valid = false;
@@ -923,10 +924,7 @@ pic_status batch_one_step(pic_batch* b) {
     }
     hipEvent_t t3, t4, t5;
     PICCHK(bmark(b, &t3));
-    if (any_bin) {
-        BHIPCHK(b, launch_batch_jfinal(dtab, n, max_cells, b->stream));
-        BHIPCHK(b, launch_batch_binomial(dtab, n, max_bin, b->stream));
-    }
+    if (any_bin) BHIPCHK(b, launch_batch_binomial(dtab, n, max_bin, b->stream));
     PICCHK(bend(b, PH_JPOST, t3));
     PICCHK(bmark(b, &t4));
     BHIPCHK(b, launch_batch_bhalf(dtab, n, max_btiles, b->stream));
@@ -956,6 +954,7 @@ pic_status batch_one_step(pic_batch* b) {
                                      i, s, (long long)sp.bound, (long long)most, (long long)sp.user.capacity);
                 }
                 sp.bound += most;
+                sp.appended = true;
                 max_cand = std::max<long long>(max_cand, most);
                 any = true;
             }
@@ -1128,6 +1127,7 @@ pic_status pic_gather_push(pic_ctx* c, int32_t s) {
     HIPCHK(c, launch_gather_push(c->g, fields_of(c), dev_of(c, sp), prev_of(c, sp), &small_of(c)->count[s],
                                  (int)sp.bound, &small_of(c)->err, c->stream));
     sp.prev_valid = true;
+    sp.loose = true;
     c->mid_step = true;
     return PIC_OK;
 }
@@ -1165,12 +1165,12 @@ pic_status pic_deposit(pic_ctx* c, int32_t s) {
 pic_status pic_field_step(pic_ctx* c) {
     if (!c) return PIC_EINVAL;
     if (c->desc.jpost == PIC_JPOST_NONE) {
-        PICCHK(field_update(c, c->f.J, nullptr, nullptr));
+        PICCHK(field_update(c, c->f.J, nullptr, nullptr, nullptr));
     } else {   // the E update also stores the post-processed current to J
         float* tmp[3];
         jtmp_of(c, tmp);
         PICCHK(filter_to(c, tmp));
-        PICCHK(field_update(c, tmp, c->f.J, nullptr));
+        PICCHK(field_update(c, tmp, c->f.J, nullptr, nullptr));
         c->j_filtered = true;
     }
     if (c->acc_used) HIPCHK(c, launch_zero_u64(acc_of(c), 3 * (int64_t)c->g.ncell, c->stream));
@@ -1202,15 +1202,21 @@ pic_status pic_step(pic_ctx* c, int32_t nsteps) {
             PICCHK(prof_mark(c, &t1));
             int* rest_idx = reinterpret_cast<int*>(c->ws + c->L.sort_rank) + sp.base;
             const SpeciesDev pre = dev_from(c, sp, sp.alt);   // the pre-sort set after a sort
-            HIPCHK(c, launch_pic_tile(c->g, c->tl.t, c->tl.guard, c->tl.threads, fields_of(c), dev_of(c, sp),
-                                      gather ? &pre : nullptr, toff_of(c, s), acc_of(c), &sm->err, &sm->rest_n[s],
-                                      rest_idx, c->stream));
+            // a particle moves less than a cell per step, so those in tile ranges
+            // stay within the guard for `guard` steps after a sort; with none
+            // appended either, there is nothing for a rest pass
+            const bool rest = sp.appended || sp.loose || c->step - sp.sort_step > c->tl.guard;
+            HIPCHK(c, launch_pic_tile(c->g, c->tl.t, c->tl.guard, c->tl.threads, (int)sp.bound, fields_of(c),
+                                      dev_of(c, sp), gather ? &pre : nullptr, toff_of(c, s), acc_of(c), &sm->err,
+                                      &sm->rest_n[s], rest_idx, rest, c->stream));
             PICCHK(prof_end(c, PH_TILE, t1));
             if (c->prof.on) c->prof.tiles += 1;
-            PICCHK(prof_mark(c, &t2));
-            HIPCHK(c, launch_tile_rest(c->g, fields_of(c), dev_of(c, sp), &sm->sorted[s], &sm->count[s],
-                                       &sm->rest_n[s], rest_idx, acc_of(c), &sm->err, c->stream));
-            PICCHK(prof_end(c, PH_LOOSE, t2));
+            if (rest) {
+                PICCHK(prof_mark(c, &t2));
+                HIPCHK(c, launch_tile_rest(c->g, fields_of(c), dev_of(c, sp), &sm->sorted[s], &sm->count[s],
+                                           &sm->rest_n[s], rest_idx, acc_of(c), &sm->err, c->stream));
+                PICCHK(prof_end(c, PH_LOOSE, t2));
+            }
             sp.prev_valid = false;
         }
         PICCHK(finish_step(c));
@@ -1228,6 +1234,7 @@ pic_status pic_species_view(pic_ctx* c, int32_t s, pic_species_bufs* out, int64_
     int cnt = 0;
     HIPCHK(c, hipMemcpyAsync(&cnt, &small_of(c)->count[s], sizeof(int), hipMemcpyDeviceToHost, c->stream));
     pic_status st = device_errors(c);
+    c->sp[s].loose = true;
     if (out) *out = c->sp[s].cur;
     if (n_live) *n_live = cnt;
     return st;

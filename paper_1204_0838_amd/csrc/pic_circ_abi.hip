@@ -508,8 +508,7 @@ pic_status pic_circ_step(pic_circ_ctx* c, int32_t nsteps) {
                 CHIP(c, launch_sort(sort_geom(c), c->t, cdev(c, sp, sp.cur), cdev(c, sp, sp.alt), &sm->count[s],
                                     &sm->sorted[s], (int)sp.bound, reinterpret_cast<int*>(c->ws + c->L.hist), rank,
                                     reinterpret_cast<int*>(c->ws + c->L.sums), nullptr, nullptr, c->desc.interleave, ctoff(c, s),
-                                    true, false,
-                                    c->stream));
+                                    true, false, true, c->stream));
                 std::swap(sp.cur, sp.alt);
                 sp.sorted = true;
                 sp.sort_step = c->step;

@@ -321,9 +321,10 @@ __global__ void __launch_bounds__(BT_THREADS) k_bhalf_march(Geom g, PDCoef c, co
     bhalf_columns<PD, PML>(g, c, Ex, Ey, Ez, Bx, By, Bz, h, bx, by, z0, min(z0 + planes, g.n[2]), El, P, store != 0);
 }
 
-// Where the E update takes its current from: the J planes; another buffer
-// (the post-processed current), which it also stores to the J planes; or the
-// fixed-point accumulator, which it rounds into the J planes and clears.
+// Where the E update takes its current from: the J planes (clearing the
+// accumulator when a filter has read it); another buffer (the post-processed
+// current), which it also stores to the J planes; or the fixed-point
+// accumulator, which it rounds into the J planes and clears.
 struct JSource {
     const float* in[3];
     unsigned long long* acc;
@@ -332,7 +333,7 @@ struct JSource {
 };
 // (Reading the accumulator here saves a read of J and a launch: 512x256x256
 // cells 634 -> 528 us together, 6.1 TB/s.)
-enum { J_PLANES = 0, J_COPY = 1, J_ACC = 2 };
+enum { J_PLANES = 0, J_COPY = 1, J_ACC = 2, J_CLEAR = 3 };
 
 template <int SRC>
 __device__ __forceinline__ float take_current(const JSource& s, int comp, int ncell, int idx) {
@@ -345,6 +346,7 @@ __device__ __forceinline__ float take_current(const JSource& s, int comp, int nc
     }
     const float j = s.in[comp][idx];
     if (SRC == J_COPY) s.J[comp][idx] = j;
+    if (SRC == J_CLEAR) s.acc[(size_t)comp * ncell + idx] = 0ull;
     return j;
 }
 
@@ -429,8 +431,19 @@ __global__ void __launch_bounds__(256) k_clear_pml_plane(Geom g, PmlDev P, int i
 // seam read as zero.
 constexpr int kBinRows = 4, kBinWaves = 4;   // a workgroup: 64 x by kBinWaves kBinRows rows
 
-__device__ __forceinline__ void binomial_march(const Geom& g, const float* __restrict__ src, float* __restrict__ dst,
-                                               int bx, int by, int z0, int z1) {
+struct PlaneSource {   // an FP32 component
+    const float* p;
+    __device__ __forceinline__ float operator()(size_t i) const { return p[i]; }
+};
+struct AccSource {     // a component of the accumulator, as the read-out rounds it
+    const unsigned long long* p;
+    double scale;
+    __device__ __forceinline__ float operator()(size_t i) const { return (float)((double)(long long)p[i] * scale); }
+};
+
+template <class Src>
+__device__ __forceinline__ void binomial_march(const Geom& g, const Src& src, float* __restrict__ dst, int bx, int by,
+                                               int z0, int z1) {
     const int i = bx * 64 + ((int)threadIdx.x & 63);
     const int j0 = (by * kBinWaves + ((int)threadIdx.x >> 6)) * kBinRows;
     if (i >= g.n[0] || j0 >= g.n[1]) return;
@@ -454,12 +467,12 @@ __device__ __forceinline__ void binomial_march(const Geom& g, const float* __res
     for (int b = 0; b < kBinRows; ++b) ym[b] = yc[b] = 0.0f;
     float v[kBinRows + 2][3];   // x - 1, x, x + 1 of each row: the next plane's, loaded a plane ahead
     auto load = [&](int z) {
-        const float* p = src + (size_t)g.nxy * (z < 0 ? z + g.n[2] : (z >= g.n[2] ? z - g.n[2] : z));
+        const size_t p = (size_t)g.nxy * (z < 0 ? z + g.n[2] : (z >= g.n[2] ? z - g.n[2] : z));
 #pragma unroll
         for (int b = 0; b < kBinRows + 2; ++b) {
-            v[b][0] = xm_ok ? p[row[b] + im] : 0.0f;
-            v[b][1] = p[row[b] + i];
-            v[b][2] = xp_ok ? p[row[b] + ip] : 0.0f;
+            v[b][0] = xm_ok ? src(p + row[b] + im) : 0.0f;
+            v[b][1] = src(p + row[b] + i);
+            v[b][2] = xp_ok ? src(p + row[b] + ip) : 0.0f;
         }
     };
     load(z0 - 1);
@@ -481,16 +494,23 @@ __device__ __forceinline__ void binomial_march(const Geom& g, const float* __res
     }
 }
 
-struct Ptr3 {
+struct BinArgs {
     const float* s[3];
+    const unsigned long long* acc;
+    double scale[3];
     float* d[3];
 };
 
-__global__ void __launch_bounds__(64 * kBinWaves) k_binomial(Geom g, Ptr3 p, int planes, int chunks) {
+template <bool ACC>
+__global__ void __launch_bounds__(64 * kBinWaves) k_binomial(Geom g, BinArgs p, int planes, int chunks) {
     const int tx = (g.n[0] + 63) / 64, ty = (g.n[1] + kBinWaves * kBinRows - 1) / (kBinWaves * kBinRows);
     const int t = xcd_run(blockIdx.x, gridDim.x);   // x fastest, then y, plane chunk, component
     const int u = t / (tx * ty), comp = u / chunks, z0 = (u - comp * chunks) * planes;
-    binomial_march(g, p.s[comp], p.d[comp], t % tx, (t / tx) % ty, z0, min(z0 + planes, g.n[2]));
+    const int bx = t % tx, by = (t / tx) % ty, z1 = min(z0 + planes, g.n[2]);
+    if (ACC)
+        binomial_march(g, AccSource{p.acc + (size_t)comp * g.ncell, p.scale[comp]}, p.d[comp], bx, by, z0, z1);
+    else
+        binomial_march(g, PlaneSource{p.s[comp]}, p.d[comp], bx, by, z0, z1);
 }
 
 // Batched field kernels: grid y = member.
@@ -530,7 +550,7 @@ __global__ void __launch_bounds__(256) k_batch_efull(const InstDesc* __restrict_
     }
     js.acc = d.acc;
     if (d.jpost)
-        efull_cell<false, J_PLANES>(g, d.f.E[0], d.f.E[1], d.f.E[2], d.f.B[0], d.f.B[1], d.f.B[2], js, idx);
+        efull_cell<false, J_CLEAR>(g, d.f.E[0], d.f.E[1], d.f.E[2], d.f.B[0], d.f.B[1], d.f.B[2], js, idx);
     else
         efull_cell<false, J_ACC>(g, d.f.E[0], d.f.E[1], d.f.E[2], d.f.B[0], d.f.B[1], d.f.B[2], js, idx);
 }
@@ -543,7 +563,8 @@ __global__ void __launch_bounds__(64 * kBinWaves) k_batch_binomial(const InstDes
     const int tx = (g.n[0] + 63) / 64, ty = (g.n[1] + kBinWaves * kBinRows - 1) / (kBinWaves * kBinRows);
     const int t = blockIdx.x, z0 = (t / (tx * ty)) * kBatchPlanes, comp = blockIdx.z;
     if (z0 >= g.n[2]) return;
-    binomial_march(g, d.Jt[comp], d.J[comp], t % tx, (t / tx) % ty, z0, min(z0 + kBatchPlanes, g.n[2]));
+    binomial_march(g, AccSource{d.acc + (size_t)comp * g.ncell, d.jscale[comp]}, d.J[comp], t % tx, (t / tx) % ty, z0,
+                   min(z0 + kBatchPlanes, g.n[2]));
 }
 
 __global__ void k_zero_u64(unsigned long long* p, int64_t n) {
@@ -564,7 +585,7 @@ hipError_t launch_bhalf(const Geom& g, int pd, const PDCoef& c, float* const E[3
 }
 
 hipError_t launch_efull(const Geom& g, float* const E[3], float* const B[3], float* const J[3], float* const Jcopy[3],
-                        unsigned long long* acc, const double scale[3], const PmlDev* pml, hipStream_t st) {
+                        unsigned long long* acc, const double* scale, const PmlDev* pml, hipStream_t st) {
     const int nb = (g.ncell + 255) / 256;
     const PmlDev P = pml ? *pml : PmlDev{};
     JSource js{};
@@ -574,7 +595,8 @@ hipError_t launch_efull(const Geom& g, float* const E[3], float* const B[3], flo
         if (scale) js.scale[a] = scale[a];
     }
     js.acc = acc;
-    auto k = acc ? (pml ? k_efull<true, J_ACC> : k_efull<false, J_ACC>)
+    auto k = acc && scale ? (pml ? k_efull<true, J_ACC> : k_efull<false, J_ACC>)
+             : acc        ? (pml ? k_efull<true, J_CLEAR> : k_efull<false, J_CLEAR>)
                  : Jcopy ? (pml ? k_efull<true, J_COPY> : k_efull<false, J_COPY>)
                          : (pml ? k_efull<true, J_PLANES> : k_efull<false, J_PLANES>);
     hipLaunchKernelGGL(k, dim3(nb), dim3(256), 0, st, g, E[0], E[1], E[2], B[0], B[1], B[2], js, P);
@@ -587,15 +609,19 @@ hipError_t launch_clear_pml_plane(const Geom& g, const PmlDev& P, int ix, hipStr
     return hipGetLastError();
 }
 
-hipError_t launch_binomial(const Geom& g, float* const src[3], float* const dst[3], hipStream_t st) {
+hipError_t launch_binomial(const Geom& g, float* const src[3], const unsigned long long* acc, const double scale[3],
+                           float* const dst[3], hipStream_t st) {
     const int bx = (g.n[0] + 63) / 64, by = (g.n[1] + kBinWaves * kBinRows - 1) / (kBinWaves * kBinRows);
     const int planes = march_planes(3ll * bx * by, g.n[2], 2 * kMarchResident), chunks = (g.n[2] + planes - 1) / planes;
-    Ptr3 p;
+    BinArgs p{};
     for (int a = 0; a < 3; ++a) {
-        p.s[a] = src[a];
+        if (src) p.s[a] = src[a];
+        if (scale) p.scale[a] = scale[a];
         p.d[a] = dst[a];
     }
-    hipLaunchKernelGGL(k_binomial, dim3(bx * by * 3 * chunks), dim3(64 * kBinWaves), 0, st, g, p, planes, chunks);
+    p.acc = acc;
+    hipLaunchKernelGGL(src ? k_binomial<false> : k_binomial<true>, dim3(bx * by * 3 * chunks), dim3(64 * kBinWaves), 0,
+                       st, g, p, planes, chunks);
     return hipGetLastError();
 }
 

@@ -94,7 +94,6 @@ struct InstDesc {
     PDCoef c;
     FieldPtrs f;
     float* J[3];             // current read by the E update
-    float* Jt[3];            // workspace current (binomial filter source)
     int jpost;               // 0: none, 1: binomial filter
     int sorting;             // 1: sort s -> alt first (no copy pass: the tile step gathers from s); the step runs on alt
     SpeciesDev s;            // particle arrays at the start of the step
@@ -139,7 +138,6 @@ hipError_t launch_batch_sort(const InstDesc* d, int n, int max_particles, int ma
 hipError_t launch_batch_tile(const InstDesc* d, const int* tile_begin, int n, int total_tiles, int threads,
                              size_t lds_bytes, bool all_888g1, hipStream_t st);
 hipError_t launch_batch_rest(const InstDesc* d, int n, hipStream_t st);
-hipError_t launch_batch_jfinal(const InstDesc* d, int n, int max_cells, hipStream_t st);
 // (max_tiles = the largest binomial_tiles of a member)
 hipError_t launch_batch_binomial(const InstDesc* d, int n, int max_tiles, hipStream_t st);
 int binomial_tiles(const int n[3]);
@@ -209,10 +207,11 @@ hipError_t launch_tile_list(const Geom& g, const TileGeom& t, const int* cell, c
 // dst.cell: the next tile step (launch_pic_tile with src) then gathers the
 // particles itself.  resort: particles [0, *d_sorted) still occupy the tile
 // ranges toff of the last sort with this tiling (counted tile by tile; lc:
-// scratch of t.ntiles * t.tcells ints).
+// scratch of t.ntiles * t.tcells ints); appended: particles may have been
+// added after them.
 hipError_t launch_sort(const Geom& g, const TileGeom& t, const SpeciesDev& src, const SpeciesDev& dst,
                        int* d_count, int* d_sorted, int max_count, int* hist, int* rank, int* sums, int* level,
-                       int* lc, int depth, int* toff, bool copy, bool resort, hipStream_t st);
+                       int* lc, int depth, int* toff, bool copy, bool resort, bool appended, hipStream_t st);
 
 // fused tile kernel (pic_tile.hip)
 size_t tile_lds_bytes(const TileGeom& t, int guard);
@@ -220,9 +219,12 @@ size_t tile_lds_bytes(const TileGeom& t, int guard);
 // rest_n / rest_idx: the species' rest list (counter zeroed here, indices appended by the kernel)
 // src: null, or the pre-sort arrays when the sort ran without its copy pass
 // (s.cell then holds source indices; the step writes every array of s)
-hipError_t launch_pic_tile(const Geom& g, const TileGeom& t, int guard, int threads, const FieldPtrs& f,
-                           const SpeciesDev& s, const SpeciesDev* src, const int* toff, unsigned long long* acc,
-                           int* d_err, int* rest_n, int* rest_idx, hipStream_t st);
+// threads: per workgroup, 0 = by the tiles' population; max_count: the host's bound of the particles
+// rest: a rest pass follows (false: no particle can be beyond the guard)
+hipError_t launch_pic_tile(const Geom& g, const TileGeom& t, int guard, int threads, int max_count,
+                           const FieldPtrs& f, const SpeciesDev& s, const SpeciesDev* src, const int* toff,
+                           unsigned long long* acc, int* d_err, int* rest_n, int* rest_idx, bool rest,
+                           hipStream_t st);
 // rest pass after the tile kernel: the particles on its rest list (beyond
 // their tile's guard, marked cell -2 - c) and those appended after the last
 // sort (index >= sorted)
@@ -235,12 +237,14 @@ hipError_t launch_tile_rest(const Geom& g, const FieldPtrs& f, const SpeciesDev&
 // B half steps advances the layer's B arrays, the second only reads them.
 hipError_t launch_bhalf(const Geom& g, int pd, const PDCoef& c, float* const E[3], float* const B[3], float h,
                         const PmlDev* pml, int store, hipStream_t st);
-// acc null: the current is J; with Jcopy it is stored there too.  acc: the
-// current is acc (times scale), stored to J, and acc is cleared.
+// Where its current is: J (scale null; with Jcopy it is stored there too), or
+// acc times scale, stored to J.  acc not null: cleared.
 hipError_t launch_efull(const Geom& g, float* const E[3], float* const B[3], float* const J[3], float* const Jcopy[3],
-                        unsigned long long* acc, const double scale[3], const PmlDev* pml, hipStream_t st);
+                        unsigned long long* acc, const double* scale, const PmlDev* pml, hipStream_t st);
 hipError_t launch_clear_pml_plane(const Geom& g, const PmlDev& P, int ix, hipStream_t st);
-hipError_t launch_binomial(const Geom& g, float* const src[3], float* const dst[3], hipStream_t st);
+// src null: the source is acc times scale (left as it is)
+hipError_t launch_binomial(const Geom& g, float* const src[3], const unsigned long long* acc, const double scale[3],
+                           float* const dst[3], hipStream_t st);
 hipError_t launch_zero_u64(unsigned long long* p, int64_t n, hipStream_t st);
 
 // reductions (pic_reduce.hip); part: scratch of 4096 words, free after the call

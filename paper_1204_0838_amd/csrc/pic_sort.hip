@@ -192,11 +192,6 @@ __global__ void __launch_bounds__(kTileCountThreads) k_sort_count_tiles(Geom g, 
     count_tile(g, t, sd, cell, toff, hist, lc, rank, blockIdx.x, lh);
 }
 
-__global__ void __launch_bounds__(256) k_add_counts(int* __restrict__ hist, const int* __restrict__ lc, int nkeys) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < nkeys) hist[i] += lc[i];
-}
-
 // Level order of one tile (depth 0).  The scatter has stored the tile's
 // source indices in plain cell order in `src` (off[key] is the first
 // cell-order place of a key, off[key + 1] - off[key] its count); this writes
@@ -338,11 +333,17 @@ __global__ void __launch_bounds__(kLevelThreads) k_sort_levels_local(const int* 
     sort_levels_tile(off, tcells, src, out, blockIdx.x, &lp);
 }
 
-// Exclusive scan, phase 1: per-block totals of 1024-element blocks.
-__device__ __forceinline__ void scan_reduce_block(const int* __restrict__ in, int n, int* __restrict__ sums, int bx) {
+// Exclusive scan of the histogram, phase 1: per-block totals of 1024-element
+// blocks, after adding a re-sort's local counts (lc, one per key; null: none).
+__device__ __forceinline__ void scan_reduce_block(int* __restrict__ in, const int* __restrict__ lc, int n,
+                                                  int* __restrict__ sums, int bx) {
     __shared__ int ws[16];
     const int i = bx * 1024 + threadIdx.x;
     int v = i < n ? in[i] : 0;
+    if (lc && i < n - 1) {   // (n = keys + 1)
+        v += lc[i];
+        in[i] = v;
+    }
     for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
     if ((threadIdx.x & 63) == 0) ws[threadIdx.x >> 6] = v;
     __syncthreads();
@@ -353,8 +354,9 @@ __device__ __forceinline__ void scan_reduce_block(const int* __restrict__ in, in
     }
 }
 
-__global__ void __launch_bounds__(1024) k_scan_reduce(const int* __restrict__ in, int n, int* __restrict__ sums) {
-    scan_reduce_block(in, n, sums, blockIdx.x);
+__global__ void __launch_bounds__(1024) k_scan_reduce(int* __restrict__ in, const int* __restrict__ lc, int n,
+                                                      int* __restrict__ sums) {
+    scan_reduce_block(in, lc, n, sums, blockIdx.x);
 }
 
 // Block-wide inclusive scan of one value per thread (1024 threads).
@@ -380,7 +382,7 @@ __device__ __forceinline__ int block_scan_incl(int v, int* ws) {
     return v + add;
 }
 
-// Phase 2: exclusive scan of the block totals by one workgroup; total -> sums[nb].
+// Phase 2: exclusive scan of the block totals by one workgroup.
 __device__ __forceinline__ void scan_sums_block(int* __restrict__ sums, int nb) {
     __shared__ int ws[32];
     __shared__ int carry;
@@ -396,22 +398,46 @@ __device__ __forceinline__ void scan_sums_block(int* __restrict__ sums, int nb) 
         if (threadIdx.x == 1023) carry = c0 + inc;
         __syncthreads();
     }
-    if (threadIdx.x == 0) sums[nb] = carry;
 }
 
 __global__ void __launch_bounds__(1024) k_scan_sums(int* __restrict__ sums, int nb) { scan_sums_block(sums, nb); }
 
-// Phase 3: exclusive scan inside each block plus the block offset; out may alias in.
-__device__ __forceinline__ void scan_apply_block(const int* in, int n, const int* __restrict__ sums, int* out, int bx) {
+// Phase 3: exclusive scan inside each block plus the block offset; out may
+// alias in.  totals: sums holds the block totals themselves (no phase 2): the
+// block adds up those before it, up to kSumsInline of them.
+constexpr int kSumsInline = 1024;
+
+__device__ __forceinline__ void scan_apply_block(const int* in, int n, const int* __restrict__ sums, bool totals,
+                                                 int* out, int bx) {
     __shared__ int ws[32];
+    int before = totals ? ((int)threadIdx.x < bx ? sums[threadIdx.x] : 0) : 0;
+    if (totals) {
+        before = block_scan_incl(before, ws);
+        __shared__ int all;
+        if (threadIdx.x == 1023) all = before;
+        __syncthreads();
+        before = all;
+    } else {
+        before = sums[bx];
+    }
     const int i = bx * 1024 + threadIdx.x;
     const int v = i < n ? in[i] : 0;
     const int inc = block_scan_incl(v, ws);
-    if (i < n) out[i] = sums[bx] + inc - v;
+    if (i < n) out[i] = before + inc - v;
 }
 
-__global__ void __launch_bounds__(1024) k_scan_apply(const int* in, int n, const int* __restrict__ sums, int* out) {
-    scan_apply_block(in, n, sums, out, blockIdx.x);
+__global__ void __launch_bounds__(1024) k_scan_apply(const int* in, int n, const int* __restrict__ sums, int totals,
+                                                     int* out) {
+    scan_apply_block(in, n, sums, totals != 0, out, blockIdx.x);
+}
+
+// hist (n entries, lc added first when not null) becomes its exclusive scan.
+static void scan_hist(int* hist, const int* lc, int n, int* sums, hipStream_t st) {
+    const int nb = (n + 1023) / 1024;
+    hipLaunchKernelGGL(k_scan_reduce, dim3(nb), dim3(1024), 0, st, hist, lc, n, sums);
+    const bool inline_sums = nb <= kSumsInline;
+    if (!inline_sums) hipLaunchKernelGGL(k_scan_sums, dim3(1), dim3(1024), 0, st, sums, nb);
+    hipLaunchKernelGGL(k_scan_apply, dim3(nb), dim3(1024), 0, st, hist, n, sums, inline_sums ? 1 : 0, hist);
 }
 
 // Source index of particle p to its place: out[off[key] + rank] in cell
@@ -500,18 +526,19 @@ __global__ void __launch_bounds__(256) k_sort_gather(SpeciesDev src, SpeciesDev 
     gather_one(src, dst, i);
 }
 
-// New live count = total of the histogram.
-__global__ void k_sort_finish(const int* __restrict__ off, int nkeys, int* __restrict__ d_count,
-                              int* __restrict__ d_sorted) {
-    d_count[0] = off[nkeys];
-    d_sorted[0] = off[nkeys];
-}
-
-// Tile ranges of the species: toff[t] = first particle of tile t (t = 0..ntiles).
-__global__ void __launch_bounds__(256) k_tile_offsets(const int* __restrict__ off, int tcells, int ntiles,
-                                                      int* __restrict__ toff) {
+// Tile ranges of the species: toff[t] = first particle of tile t (t = 0..ntiles);
+// new live count = total of the histogram.
+__global__ void __launch_bounds__(256) k_sort_finish(const int* __restrict__ off, int tcells, int ntiles,
+                                                     int* __restrict__ toff, int* __restrict__ d_count,
+                                                     int* __restrict__ d_sorted) {
     const int t = blockIdx.x * blockDim.x + threadIdx.x;
-    if (t <= ntiles) toff[t] = off[t * tcells];
+    if (t > ntiles) return;
+    const int o = off[t * tcells];
+    toff[t] = o;
+    if (t == ntiles) {
+        d_count[0] = o;
+        d_sorted[0] = o;
+    }
 }
 
 // Batched sort: grid y = member; members that do not sort this step return at once.
@@ -546,13 +573,6 @@ __global__ void __launch_bounds__(kTileCountThreads) k_batch_sort_count_tiles(co
     count_tile(g, t, d.sdiv, d.s.cell, d.toff, d.hist, d.lc, d.rank, blockIdx.x, lh);
 }
 
-__global__ void __launch_bounds__(256) k_batch_add_counts(const InstDesc* __restrict__ tab) {
-    const InstDesc& d = tab[blockIdx.y];
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (!d.sorting || !d.resort || i >= d.nkeys) return;
-    d.hist[i] += d.lc[i];
-}
-
 // Level order of the sorting members with depth 0 (after their scatter):
 // grid x = tile, y = member.  A member that re-sorts places the particles
 // that stayed in their tile here, from its last tile ranges (its scatter
@@ -573,7 +593,7 @@ __global__ void __launch_bounds__(1024) k_batch_scan_reduce(const InstDesc* __re
     const InstDesc& d = tab[blockIdx.y];
     const int n = d.nkeys + 1;
     if (!d.sorting || (int)blockIdx.x * 1024 >= n) return;
-    scan_reduce_block(d.hist, n, d.sums, blockIdx.x);
+    scan_reduce_block(d.hist, d.resort ? d.lc : nullptr, n, d.sums, blockIdx.x);
 }
 
 __global__ void __launch_bounds__(1024) k_batch_scan_sums(const InstDesc* __restrict__ tab) {
@@ -586,7 +606,7 @@ __global__ void __launch_bounds__(1024) k_batch_scan_apply(const InstDesc* __res
     const InstDesc& d = tab[blockIdx.y];
     const int n = d.nkeys + 1;
     if (!d.sorting || (int)blockIdx.x * 1024 >= n) return;
-    scan_apply_block(d.hist, n, d.sums, d.hist, blockIdx.x);
+    scan_apply_block(d.hist, n, d.sums, false, d.hist, blockIdx.x);
 }
 
 __global__ void __launch_bounds__(256) k_batch_sort_scatter(const InstDesc* __restrict__ tab) {
@@ -625,7 +645,6 @@ hipError_t launch_batch_sort(const InstDesc* d, int n, int max_particles, int ma
     hipLaunchKernelGGL(k_batch_sort_count_tiles, dim3(max_tiles1 - 1, n), dim3(kTileCountThreads),
                        max_tcells * sizeof(int), st, d);
     hipLaunchKernelGGL(k_batch_sort_count, dim3((ncol + 255) / 256, n), dim3(256), 0, st, d);
-    hipLaunchKernelGGL(k_batch_add_counts, dim3((max_keys1 + 255) / 256, n), dim3(256), 0, st, d);
     hipLaunchKernelGGL(k_batch_scan_reduce, dim3(nb, n), dim3(1024), 0, st, d);
     hipLaunchKernelGGL(k_batch_scan_sums, dim3(1, n), dim3(1024), 0, st, d);
     hipLaunchKernelGGL(k_batch_scan_apply, dim3(nb, n), dim3(1024), 0, st, d);
@@ -638,31 +657,26 @@ hipError_t launch_batch_sort(const InstDesc* d, int n, int max_particles, int ma
 
 hipError_t launch_sort(const Geom& g, const TileGeom& t, const SpeciesDev& src, const SpeciesDev& dst,
                        int* d_count, int* d_sorted, int max_count, int* hist, int* rank, int* sums, int* level,
-                       int* lc, int depth, int* toff, bool copy, bool resort, hipStream_t st) {
+                       int* lc, int depth, int* toff, bool copy, bool resort, bool appended, hipStream_t st) {
     const int nkeys = t.ntiles * t.tcells;
     if (depth == 0 && (level == nullptr || t.tcells > kLevelThreads * kLevelMaxPer)) return hipErrorInvalidValue;
     if (resort && lc == nullptr) return hipErrorInvalidValue;
-    hipError_t e = hipMemsetAsync(hist, 0, ((size_t)nkeys + 1) * sizeof(int), st);
-    if (e != hipSuccess) return e;
     const int np = max_count > 0 ? max_count : 1;
     const int stride = count_stride(t, depth);
     const int ncol = count_threads(np, stride);
     const SortDiv sd = make_sortdiv(g, t);
+    hipLaunchKernelGGL(k_zero_hist, dim3((nkeys + 1 + 255) / 256), dim3(256), 0, st, hist, nkeys + 1);
     if (resort) {   // [0, *d_sorted) sit in the tile ranges toff of the last sort; appended ones after them
         hipLaunchKernelGGL(k_sort_count_tiles, dim3(t.ntiles), dim3(kTileCountThreads), t.tcells * sizeof(int), st,
                            g, t, sd, src.cell, toff, hist, lc, rank);
-        hipLaunchKernelGGL(k_sort_count, dim3((ncol + 255) / 256), dim3(256), 0, st, g, t, sd, src.cell, d_sorted,
-                           d_count, stride, 1, hist, rank);
-        hipLaunchKernelGGL(k_add_counts, dim3((nkeys + 255) / 256), dim3(256), 0, st, hist, lc, nkeys);
+        if (appended)
+            hipLaunchKernelGGL(k_sort_count, dim3((ncol + 255) / 256), dim3(256), 0, st, g, t, sd, src.cell, d_sorted,
+                               d_count, stride, 1, hist, rank);
     } else {
         hipLaunchKernelGGL(k_sort_count, dim3((ncol + 255) / 256), dim3(256), 0, st, g, t, sd, src.cell, nullptr,
                            d_count, stride, 0, hist, rank);
     }
-    const int n = nkeys + 1;
-    const int nb = (n + 1023) / 1024;
-    hipLaunchKernelGGL(k_scan_reduce, dim3(nb), dim3(1024), 0, st, hist, n, sums);
-    hipLaunchKernelGGL(k_scan_sums, dim3(1), dim3(1024), 0, st, sums, nb);
-    hipLaunchKernelGGL(k_scan_apply, dim3(nb), dim3(1024), 0, st, hist, n, sums, hist);
+    scan_hist(hist, resort ? lc : nullptr, nkeys + 1, sums, st);
     if (depth == 0 && resort) {
         // toff still holds the last sort's tile ranges (rewritten at the end)
         hipLaunchKernelGGL(k_sort_scatter_moved, dim3((np + 255) / 256), dim3(256), 0, st, g, t, sd, src.cell, level,
@@ -678,9 +692,8 @@ hipError_t launch_sort(const Geom& g, const TileGeom& t, const SpeciesDev& src, 
                                dst.cell);
     }
     if (copy) hipLaunchKernelGGL(k_sort_gather, dim3((np + 255) / 256), dim3(256), 0, st, src, dst, hist, nkeys);
-    hipLaunchKernelGGL(k_sort_finish, dim3(1), dim3(1), 0, st, hist, nkeys, d_count, d_sorted);
-    hipLaunchKernelGGL(k_tile_offsets, dim3((t.ntiles + 1 + 255) / 256), dim3(256), 0, st, hist, t.tcells, t.ntiles,
-                       toff);
+    hipLaunchKernelGGL(k_sort_finish, dim3((t.ntiles + 1 + 255) / 256), dim3(256), 0, st, hist, t.tcells, t.ntiles,
+                       toff, d_count, d_sorted);
     return hipGetLastError();
 }
 
@@ -689,15 +702,13 @@ hipError_t launch_sort(const Geom& g, const TileGeom& t, const SpeciesDev& src, 
 // in level order (hist is left holding off).  Nothing else is moved.
 hipError_t launch_tile_list(const Geom& g, const TileGeom& t, const int* cell, const int* d_count, int max_count,
                             int* hist, int* list, int* tmp, int* sums, hipStream_t st) {
-    const int nkeys = t.ntiles * t.tcells, n = nkeys + 1, nb = (n + 1023) / 1024;
+    const int n = t.ntiles * t.tcells + 1;
     const int stride = count_stride(t, 0), ncol = count_threads(max_count, stride);
     const SortDiv sd = make_sortdiv(g, t);
     hipLaunchKernelGGL(k_zero_hist, dim3((n + 255) / 256), dim3(256), 0, st, hist, n);
     hipLaunchKernelGGL(k_sort_count, dim3((ncol + 255) / 256), dim3(256), 0, st, g, t, sd, cell, nullptr, d_count,
                        stride, 0, hist, list);
-    hipLaunchKernelGGL(k_scan_reduce, dim3(nb), dim3(1024), 0, st, hist, n, sums);
-    hipLaunchKernelGGL(k_scan_sums, dim3(1), dim3(1024), 0, st, sums, nb);
-    hipLaunchKernelGGL(k_scan_apply, dim3(nb), dim3(1024), 0, st, hist, n, sums, hist);
+    scan_hist(hist, nullptr, n, sums, st);
     hipLaunchKernelGGL(k_sort_scatter, dim3((max_count + 255) / 256), dim3(256), 0, st, g, t, sd, cell, tmp, d_count,
                        list, hist, nullptr, 0);
     hipLaunchKernelGGL(k_sort_levels, dim3(t.ntiles), dim3(kLevelThreads), 0, st, hist, t.tcells, tmp, list);

@@ -343,7 +343,14 @@ __device__ __forceinline__ void tile_body(const Geom& g, const TileGeom& t, int 
                                           const SpeciesDev& s, const SpeciesDev& src, const int* __restrict__ toff,
                                           unsigned long long* __restrict__ acc, int* __restrict__ d_err,
                                           int* __restrict__ rest_n, int* __restrict__ rest_idx,
-                                          unsigned long long* lds_u64, int tile) {
+                                          unsigned long long* lds_u64, int tile, int part = 0, int parts = 1) {
+    int pb = toff[tile], n = toff[tile + 1] - pb;
+    if (parts > 1) {   // this workgroup's share of the tile's particles, in whole wavefronts
+        const int share = ((n + parts - 1) / parts + 63) & ~63;
+        pb += part * share;
+        n = min(n - part * share, share);
+    }
+    if (n <= 0) return;
     const int T[3] = {TX > 0 ? TX : t.T[0], TY > 0 ? TY : t.T[1], TZ > 0 ? TZ : t.T[2]};
     const int guard = GD >= 0 ? GD : guard_rt;
     const int tz = tile / (t.nt[0] * t.nt[1]);
@@ -397,8 +404,6 @@ __device__ __forceinline__ void tile_body(const Geom& g, const TileGeom& t, int 
     float* const El[3] = {Fl, Fl + fr, Fl + 2 * fr};
     float* const Bl[3] = {Fl + 3 * fr, Fl + 4 * fr, Fl + 5 * fr};
     const int fstride[3] = {1, fx, fpl};
-    const int pb = toff[tile];
-    const int n = toff[tile + 1] - pb;
     int errs = 0;
     TileDeposit dep;
     dep.init(Jl, guard, jx, jpl, jr);
@@ -445,7 +450,12 @@ __device__ __forceinline__ void tile_body(const Geom& g, const TileGeom& t, int 
                 lc[d] = l;
                 inside = inside && l >= -guard && l < te[d] + guard;
             }
-            if (!inside) {   // beyond the guard: the rest pass takes it
+            if (!inside && rest_idx == nullptr) {   // (only if cells were changed behind the library's back)
+                errs |= ERR_OVERFLOW;
+                if (GATHER) s.cell[p] = cell;
+                keep_particle<GATHER>(s, p, o, u);
+                go = false;
+            } else if (!inside) {   // beyond the guard: the rest pass takes it
                 s.cell[p] = -2 - cell;
                 keep_particle<GATHER>(s, p, o, u);
                 const unsigned long long m = __ballot(1);   // the lanes in this branch
@@ -508,8 +518,8 @@ __global__ void __launch_bounds__(NT) k_pic_tile(Geom g, TileGeom t, int guard, 
     extern __shared__ unsigned long long lds_u64[];
     const int tile = xcd_tile(blockIdx.x, t.ntiles, t.nt[0]);
     if (tile >= t.ntiles) return;
-    tile_body<NT, TX, TY, TZ, GD, GATHER>(g, t, guard, f, s, src, toff, acc, d_err, rest_n, rest_idx, lds_u64,
-                                          tile);
+    tile_body<NT, TX, TY, TZ, GD, GATHER>(g, t, guard, f, s, src, toff, acc, d_err, rest_n, rest_idx, lds_u64, tile,
+                                          blockIdx.y, gridDim.y);
 }
 
 // Batched form: the work list is the concatenation of every member's tiles
@@ -689,54 +699,82 @@ size_t tile_lds_bytes(const TileGeom& t, int guard) {
     return 3 * jr * 8 + 6 * fr * 4;
 }
 
+// One tile launch: parts workgroups of NT threads per tile.
+struct TileLaunch {
+    const Geom& g;
+    const TileGeom& t;
+    int guard, parts;
+    const FieldPtrs& f;
+    const SpeciesDev& s;
+    const SpeciesDev* src;
+    const int* toff;
+    unsigned long long* acc;
+    int *d_err, *rest_n, *rest_idx;
+    bool rest;   // particles beyond the guard are possible (the rest list starts empty)
+    hipStream_t st;
+};
+
 template <int NT, int TX, int TY, int TZ, int GD, bool GATHER>
-static hipError_t launch_tile_k(const Geom& g, const TileGeom& t, int guard, const FieldPtrs& f,
-                                const SpeciesDev& s, const SpeciesDev& src, const int* toff, unsigned long long* acc,
-                                int* d_err, int* rest_n, int* rest_idx, hipStream_t st) {
-    const size_t lds = tile_lds_bytes(t, guard);
-    const int nb = xcd_blocks(t.ntiles, t.nt[0]);
+static hipError_t launch_tile_k(const TileLaunch& L) {
+    const size_t lds = tile_lds_bytes(L.t, L.guard);
+    const int nb = xcd_blocks(L.t.ntiles, L.t.nt[0]);
     hipError_t e = hipFuncSetAttribute((const void*)k_pic_tile<NT, TX, TY, TZ, GD, GATHER>,
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_zero_rest, dim3(1), dim3(1), 0, st, rest_n);
-    hipLaunchKernelGGL((k_pic_tile<NT, TX, TY, TZ, GD, GATHER>), dim3(nb), dim3(NT), lds, st, g, t, guard, f, s, src,
-                       toff, acc, d_err, rest_n, rest_idx);
+    if (L.rest) hipLaunchKernelGGL(k_zero_rest, dim3(1), dim3(1), 0, L.st, L.rest_n);
+    hipLaunchKernelGGL((k_pic_tile<NT, TX, TY, TZ, GD, GATHER>), dim3(nb, L.parts), dim3(NT), lds, L.st, L.g, L.t,
+                       L.guard, L.f, L.s, GATHER ? *L.src : L.s, L.toff, L.acc, L.d_err, L.rest_n,
+                       L.rest ? L.rest_idx : nullptr);
     return hipGetLastError();
 }
 
 template <int NT, int TX = 0, int TY = 0, int TZ = 0, int GD = -1>
-static hipError_t launch_tile_nt(const Geom& g, const TileGeom& t, int guard, const FieldPtrs& f,
-                                 const SpeciesDev& s, const SpeciesDev* src, const int* toff, unsigned long long* acc,
-                                 int* d_err, int* rest_n, int* rest_idx, hipStream_t st) {
-    if (src)
-        return launch_tile_k<NT, TX, TY, TZ, GD, true>(g, t, guard, f, s, *src, toff, acc, d_err, rest_n, rest_idx, st);
-    return launch_tile_k<NT, TX, TY, TZ, GD, false>(g, t, guard, f, s, s, toff, acc, d_err, rest_n, rest_idx, st);
+static hipError_t launch_tile_nt(const TileLaunch& L) {
+    if (L.src) return launch_tile_k<NT, TX, TY, TZ, GD, true>(L);
+    return launch_tile_k<NT, TX, TY, TZ, GD, false>(L);
 }
 
 // Tile shapes with a compile-time specialisation (the library default and
 // the autotuner's usual picks); every other shape runs the general body.
 template <int NT>
-static hipError_t launch_tile_shape(const Geom& g, const TileGeom& t, int guard, const FieldPtrs& f,
-                                    const SpeciesDev& s, const SpeciesDev* src, const int* toff,
-                                    unsigned long long* acc, int* d_err, int* rest_n, int* rest_idx, hipStream_t st) {
-    if (t.T[0] == 8 && t.T[1] == 8 && t.T[2] == 8) {
-        if (guard == 1)
-            return launch_tile_nt<NT, 8, 8, 8, 1>(g, t, guard, f, s, src, toff, acc, d_err, rest_n, rest_idx, st);
-        if (guard == 0)
-            return launch_tile_nt<NT, 8, 8, 8, 0>(g, t, guard, f, s, src, toff, acc, d_err, rest_n, rest_idx, st);
+static hipError_t launch_tile_shape(const TileLaunch& L) {
+    const int* T = L.t.T;
+    if (T[0] == 8 && T[1] == 8 && T[2] == 8) {
+        if (L.guard == 1) return launch_tile_nt<NT, 8, 8, 8, 1>(L);
+        if (L.guard == 0) return launch_tile_nt<NT, 8, 8, 8, 0>(L);
     }
-    if (t.T[0] == 8 && t.T[1] == 8 && t.T[2] == 4 && guard == 1)
-        return launch_tile_nt<NT, 8, 8, 4, 1>(g, t, guard, f, s, src, toff, acc, d_err, rest_n, rest_idx, st);
-    return launch_tile_nt<NT>(g, t, guard, f, s, src, toff, acc, d_err, rest_n, rest_idx, st);
+    if (T[0] == 8 && T[1] == 8 && T[2] == 4 && L.guard == 1) return launch_tile_nt<NT, 8, 8, 4, 1>(L);
+    return launch_tile_nt<NT>(L);
 }
 
-hipError_t launch_pic_tile(const Geom& g, const TileGeom& t, int guard, int threads, const FieldPtrs& f,
-                           const SpeciesDev& s, const SpeciesDev* src, const int* toff, unsigned long long* acc,
-                           int* d_err, int* rest_n, int* rest_idx, hipStream_t st) {
-    switch (threads) {
-        case 256: return launch_tile_shape<256>(g, t, guard, f, s, src, toff, acc, d_err, rest_n, rest_idx, st);
-        case 1024: return launch_tile_shape<1024>(g, t, guard, f, s, src, toff, acc, d_err, rest_n, rest_idx, st);
-        default: return launch_tile_shape<512>(g, t, guard, f, s, src, toff, acc, d_err, rest_n, rest_idx, st);
+// Launch shape for tiles of `population` particles on average.
+// Parts: a tile's LDS leaves room for one workgroup per CU, so a grid of
+// fewer tiles than CUs shares each tile's particles between workgroups (each
+// stages the fields and adds its own current: sums are integers, so J is the
+// same), as long as each gets kPartMin particles.
+// Measured, 128 tiles of 4096 particles: 113 us per launch with one part, 67
+// with two; 12 tiles of 1050: 48 us, 21 with four.
+// Threads (0: chosen here) 1024: also where a share holds fewer particles, the
+// staging, clearing and flush of the tile's LDS gain from them (12 tiles of
+// 1050 particles in four parts: 72 us a step, 73 with 512, 84 with 256; 7200
+// tiles of 4096: 4.60 ms per two steps, 5.05 with 512, 7.5 with 256).
+constexpr int kCUs = 256, kPartMin = 256, kTileThreads = 1024;
+
+static int tile_parts(int ntiles, int64_t count) {
+    const int64_t fill = kCUs / ntiles, most = count / ((int64_t)ntiles * kPartMin);
+    return (int)std::max<int64_t>(1, std::min(fill, most));
+}
+
+hipError_t launch_pic_tile(const Geom& g, const TileGeom& t, int guard, int threads, int max_count,
+                           const FieldPtrs& f, const SpeciesDev& s, const SpeciesDev* src, const int* toff,
+                           unsigned long long* acc, int* d_err, int* rest_n, int* rest_idx, bool rest,
+                           hipStream_t st) {
+    const int parts = tile_parts(t.ntiles, max_count);
+    const TileLaunch L{g, t, guard, parts, f, s, src, toff, acc, d_err, rest_n, rest_idx, rest, st};
+    switch (threads > 0 ? threads : kTileThreads) {
+        case 256: return launch_tile_shape<256>(L);
+        case 1024: return launch_tile_shape<1024>(L);
+        default: return launch_tile_shape<512>(L);
     }
 }
 
@@ -762,7 +800,7 @@ static hipError_t launch_batch_tile_nt(const InstDesc* d, const int* tile_begin,
 hipError_t launch_batch_tile(const InstDesc* d, const int* tile_begin, int n, int total_tiles, int threads,
                              size_t lds_bytes, bool all_888g1, hipStream_t st) {
     if (n <= 0 || total_tiles <= 0) return hipSuccess;
-    switch (threads) {
+    switch (threads > 0 ? threads : kTileThreads) {
         case 256: return launch_batch_tile_nt<256>(d, tile_begin, n, total_tiles, lds_bytes, all_888g1, st);
         case 1024: return launch_batch_tile_nt<1024>(d, tile_begin, n, total_tiles, lds_bytes, all_888g1, st);
         default: return launch_batch_tile_nt<512>(d, tile_begin, n, total_tiles, lds_bytes, all_888g1, st);
