@@ -172,7 +172,7 @@ __global__ void __launch_bounds__(DN_THREADS) k_dn_conv32(DnArgs a) {
     uint4 v[DN_ACT_PER];
     if (tile < end) {
         dn_tile_of(tile, ntx, nty, t0);
-        dn_load_act(a, box, t0, hc, v);
+        dn_load_act(a.act_in, box, t0, hc, v);
     }
     while (tile < end) {
         __syncthreads();   // the previous tile's LDS reads are done (first pass: nothing)
@@ -182,7 +182,7 @@ __global__ void __launch_bounds__(DN_THREADS) k_dn_conv32(DnArgs a) {
         const int next = tile + stride;
         if (next < end) {
             dn_tile_of(next, ntx, nty, t0);
-            dn_load_act(a, box, t0, hc, v);
+            dn_load_act(a.act_in, box, t0, hc, v);
         }
         if constexpr (KIND == 2) {
             f32x4 acc = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
@@ -215,119 +215,14 @@ __global__ void __launch_bounds__(DN_THREADS) k_dn_conv32(DnArgs a) {
     }
 }
 
-// Window/box coordinates of cell index i (x fastest), its storage index,
-// and the storage indices of neighbours (-1 = zero).
-struct DnCell {
-    int w[3];
-    int s;
-};
-
-__device__ __forceinline__ int dn_nb(const DnCombine& c, const DnCell& k, int dx, int dy, int dz) {
-    const int x = dn_axis(k.w[0] + dx, c.n[0], c.bc[0], c.origin);
-    const int y = dn_axis(k.w[1] + dy, c.n[1], c.bc[1], 0);
-    const int z = dn_axis(k.w[2] + dz, c.n[2], c.bc[2], 0);
-    if (x < 0 || y < 0 || z < 0) return -1;
-    return x + c.n[0] * (y + c.n[1] * z);
-}
-
-__device__ __forceinline__ bool dn_cell(const DnCombine& c, int i, DnCell& k) {
-    if (i >= c.n[0] * c.n[1] * c.n[2]) return false;
-    k.w[0] = i % c.n[0];
-    const int r = i / c.n[0];
-    k.w[1] = r % c.n[1];
-    k.w[2] = r / c.n[1];
-    k.s = dn_nb(c, k, 0, 0, 0);
-    return true;
-}
-
 __device__ __forceinline__ float dn_at(const float* __restrict__ F, int s) { return s >= 0 ? F[s] : 0.0f; }
 
-// dst = src + sigma curl(y), curl(y)_a = (y_{a+2} - y_{a+2}[-e_{a+1}]) / d_{a+1} - (y_{a+1} - y_{a+1}[-e_{a+2}]) / d_{a+2}.
-__global__ void __launch_bounds__(256) k_dn_curl_add(DnCombine c) {
-    DnCell k;
-    if (!dn_cell(c, blockIdx.x * blockDim.x + threadIdx.x, k)) return;
-    const int off[3][3] = {{1, 0, 0}, {0, 1, 0}, {0, 0, 1}};
-#pragma unroll
-    for (int comp = 0; comp < 3; ++comp) {
-        const int t1 = (comp + 1) % 3, t2 = (comp + 2) % 3;
-        const int m1 = dn_nb(c, k, -off[t1][0], -off[t1][1], -off[t1][2]);
-        const int m2 = dn_nb(c, k, -off[t2][0], -off[t2][1], -off[t2][2]);
-        const float cu = (c.y[t2][k.s] - dn_at(c.y[t2], m1)) * c.inv_d[t1] -
-                         (c.y[t1][k.s] - dn_at(c.y[t1], m2)) * c.inv_d[t2];
-        c.dst[comp][k.s] = fmaf(c.sigma, cu, c.src[comp][k.s]);
-    }
-}
-
-// Binomial filter of src (27-point product stencil, x innermost).
-template <bool LOSS>
-__device__ __forceinline__ void dn_binomial_cell(const DnCombine& c, const DnCell& k, double& part) {
-    const float w[3] = {0.25f, 0.5f, 0.25f};
-    int nb[27];
-#pragma unroll
-    for (int q = 0; q < 27; ++q) nb[q] = dn_nb(c, k, q % 3 - 1, (q / 3) % 3 - 1, q / 9 - 1);
-#pragma unroll
-    for (int comp = 0; comp < 3; ++comp) {
-        float acc = 0.0f;
-#pragma unroll
-        for (int zc = 0; zc < 3; ++zc) {
-            float ay = 0.0f;
-#pragma unroll
-            for (int yb = 0; yb < 3; ++yb) {
-                float ax = 0.0f;
-#pragma unroll
-                for (int xa = 0; xa < 3; ++xa) ax = fmaf(w[xa], dn_at(c.src[comp], nb[(zc * 3 + yb) * 3 + xa]), ax);
-                ay = fmaf(w[yb], ax, ay);
-            }
-            acc = fmaf(w[zc], ay, acc);
-        }
-        if (LOSS) {
-            const float e = (acc - c.T[comp][k.s]) * c.inv_scale[comp];
-            part += (double)e * (double)e;
-            c.dst[comp][k.s] = c.grad_scale * e * c.inv_scale[comp];
-        } else {
-            c.dst[comp][k.s] = acc;
-        }
-    }
-}
-
-template <bool LOSS>
-__global__ void __launch_bounds__(256) k_dn_binomial(DnCombine c) {
-    DnCell k;
-    const bool ok = dn_cell(c, blockIdx.x * blockDim.x + threadIdx.x, k);
-    double part = 0.0;
-    if (ok) dn_binomial_cell<LOSS>(c, k, part);
-    if (LOSS) {   // every lane takes part in the wavefront reduction
-        for (int o = 32; o > 0; o >>= 1) part += __shfl_xor(part, o, 64);
-        if ((threadIdx.x & 63) == 0) atomicAdd(c.loss, part * (0.5 * (double)c.grad_scale));
-    }
-}
-
-// dy = sigma curl^T(src): dy_a = sigma [(src_{a+2}(p + e_{a+1}) - src_{a+2}(p)) / d_{a+1}
-//                                       - (src_{a+1}(p + e_{a+2}) - src_{a+1}(p)) / d_{a+2}]
-// (the forward-difference curl), as bf16 [cell][4] with channel 3 zero.
-__global__ void __launch_bounds__(256) k_dn_curl_adjoint(DnCombine c) {
-    DnCell k;
-    if (!dn_cell(c, blockIdx.x * blockDim.x + threadIdx.x, k)) return;
-    const int off[3][3] = {{1, 0, 0}, {0, 1, 0}, {0, 0, 1}};
-    bf16x4 out;
-#pragma unroll
-    for (int a = 0; a < 3; ++a) {
-        const int a1 = (a + 1) % 3, a2 = (a + 2) % 3;
-        const int p1 = dn_nb(c, k, off[a1][0], off[a1][1], off[a1][2]);
-        const int p2 = dn_nb(c, k, off[a2][0], off[a2][1], off[a2][2]);
-        const float v = (dn_at(c.src[a2], p1) - c.src[a2][k.s]) * c.inv_d[a1] -
-                        (dn_at(c.src[a1], p2) - c.src[a1][k.s]) * c.inv_d[a2];
-        out[a] = (__bf16)(c.sigma * v);
-    }
-    out[3] = (__bf16)0.0f;
-    reinterpret_cast<bf16x4*>(c.dy)[k.s] = out;
-}
-
-// Inference output stage fused in one pass over tiles of 32 x 8 x 4 cells:
-// J' = B(t), t = J + sigma curl(y), with t computed in LDS on the tile plus a
-// 1-cell halo (zero outside the box) from y staged with a further cell below
-// (the backward differences).  Same arithmetic, in the same order, as
-// k_dn_curl_add followed by k_dn_binomial<false>.
+// Output stage in one pass over tiles of 32 x 8 x 4 cells: J' = B(t),
+// t = J + sigma curl(y), curl(y)_a = (y_{a+2} - y_{a+2}[-e_{a+1}]) / d_{a+1} -
+// (y_{a+1} - y_{a+1}[-e_{a+2}]) / d_{a+2}, with t computed in LDS on the tile
+// plus a 1-cell halo (zero outside the box) from y staged with a further cell
+// below (the backward differences).  LOSS: J' is compared with the target
+// (one FP64 atomic per workgroup) and dst takes the loss gradient.
 constexpr int DO_TX = 32, DO_TY = 8, DO_TZ = 4, DO_THREADS = DO_TX * DO_TY * DO_TZ;
 constexpr int DO_YX = DO_TX + 3, DO_YY = DO_TY + 3, DO_YZ = DO_TZ + 3;   // y: cells -2 .. T
 constexpr int DO_SX = DO_TX + 2, DO_SY = DO_TY + 2, DO_SZ = DO_TZ + 2;   // t: cells -1 .. T
@@ -340,6 +235,29 @@ __device__ __forceinline__ int do_src(const DnCombine& c, int x, int y, int z) {
     return sx + c.n[0] * (sy + c.n[1] * sz);
 }
 
+// Binomial filter (27-point product stencil, x innermost) of an LDS region of
+// rows SX and planes SX x SY, at the cells (lx .. lx + 2, ly .. , lz ..).
+template <int SX, int SY>
+__device__ __forceinline__ float do_binomial(const float* F, int lx, int ly, int lz) {
+    const float w[3] = {0.25f, 0.5f, 0.25f};
+    float acc = 0.0f;
+#pragma unroll
+    for (int zc = 0; zc < 3; ++zc) {
+        float ay = 0.0f;
+#pragma unroll
+        for (int yb = 0; yb < 3; ++yb) {
+            float ax = 0.0f;
+            const int row = ((lz + zc) * SY + (ly + yb)) * SX + lx;
+#pragma unroll
+            for (int xa = 0; xa < 3; ++xa) ax = fmaf(w[xa], F[row + xa], ax);
+            ay = fmaf(w[yb], ax, ay);
+        }
+        acc = fmaf(w[zc], ay, acc);
+    }
+    return acc;
+}
+
+template <bool LOSS>
 __global__ void __launch_bounds__(DO_THREADS) k_dn_output(DnCombine c) {
     __shared__ float ys[3][DO_YZ * DO_YY * DO_YX];
     __shared__ float ts[3][DO_SZ * DO_SY * DO_SX];
@@ -399,52 +317,100 @@ __global__ void __launch_bounds__(DO_THREADS) k_dn_output(DnCombine c) {
     __syncthreads();
     const int lx = threadIdx.x % DO_TX, ly = (threadIdx.x / DO_TX) % DO_TY, lz = threadIdx.x / (DO_TX * DO_TY);
     const int x = t0[0] + lx, y = t0[1] + ly, z = t0[2] + lz;
-    if (x >= c.n[0] || y >= c.n[1] || z >= c.n[2]) return;
-    const int s = do_src(c, x, y, z);
-    const float w[3] = {0.25f, 0.5f, 0.25f};
+    const bool inside = x < c.n[0] && y < c.n[1] && z < c.n[2];
+    double part = 0.0;
+    if (inside) {
+        const int s = do_src(c, x, y, z);
 #pragma unroll
-    for (int comp = 0; comp < 3; ++comp) {
-        float acc = 0.0f;
-#pragma unroll
-        for (int zc = 0; zc < 3; ++zc) {
-            float ay = 0.0f;
-#pragma unroll
-            for (int yb = 0; yb < 3; ++yb) {
-                float ax = 0.0f;
-                const int row = ((lz + zc) * DO_SY + (ly + yb)) * DO_SX + lx;
-#pragma unroll
-                for (int xa = 0; xa < 3; ++xa) ax = fmaf(w[xa], ts[comp][row + xa], ax);
-                ay = fmaf(w[yb], ax, ay);
+        for (int comp = 0; comp < 3; ++comp) {
+            const float acc = do_binomial<DO_SX, DO_SY>(ts[comp], lx, ly, lz);
+            if (LOSS) {
+                const float e = (acc - c.T[comp][s]) * c.inv_scale[comp];
+                part += (double)e * (double)e;
+                c.dst[comp][s] = c.grad_scale * e * c.inv_scale[comp];
+            } else {
+                c.dst[comp][s] = acc;
             }
-            acc = fmaf(w[zc], ay, acc);
         }
-        c.dst[comp][s] = acc;
+    }
+    if (LOSS) {
+        __shared__ double ws[DO_THREADS / 64];
+        for (int o = 32; o > 0; o >>= 1) part += __shfl_xor(part, o, 64);
+        if ((threadIdx.x & 63) == 0) ws[threadIdx.x >> 6] = part;
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            double sum = 0.0;
+            for (int k = 0; k < DO_THREADS / 64; ++k) sum += ws[k];
+            unsafeAtomicAdd(c.loss, sum * (0.5 * (double)c.grad_scale));
+        }
     }
 }
 
-hipError_t launch_dn_output(const DnCombine& c, hipStream_t st) {
-    const dim3 g((c.n[0] + DO_TX - 1) / DO_TX, (c.n[1] + DO_TY - 1) / DO_TY, (c.n[2] + DO_TZ - 1) / DO_TZ);
-    hipLaunchKernelGGL(k_dn_output, g, dim3(DO_THREADS), 0, st, c);
+// Adjoint of the output stage for training (B is symmetric): dy = sigma
+// curl^T(B src), the forward-difference curl
+// dy_a = sigma [(b_{a+2}(p + e_{a+1}) - b_{a+2}(p)) / d_{a+1} - (b_{a+1}(p + e_{a+2}) - b_{a+1}(p)) / d_{a+2}],
+// b = B src, as bf16 [cell][4] with channel 3 zero: src staged on cells
+// -1 .. T + 1, b on 0 .. T (zero outside the box).
+constexpr int DA_GX = DO_TX + 3, DA_GY = DO_TY + 3, DA_GZ = DO_TZ + 3;   // src: cells -1 .. T + 1
+constexpr int DA_BX = DO_TX + 1, DA_BY = DO_TY + 1, DA_BZ = DO_TZ + 1;   // b: cells 0 .. T
+
+__global__ void __launch_bounds__(DO_THREADS) k_dn_output_adjoint(DnCombine c) {
+    __shared__ float gs[3][DA_GZ * DA_GY * DA_GX];
+    __shared__ float bs[3][DA_BZ * DA_BY * DA_BX];
+    const int t0[3] = {(int)blockIdx.x * DO_TX, (int)blockIdx.y * DO_TY, (int)blockIdx.z * DO_TZ};
+    constexpr int NG = DA_GZ * DA_GY * DA_GX, PG = (NG + DO_THREADS - 1) / DO_THREADS;
+    constexpr int NB = DA_BZ * DA_BY * DA_BX;
+    float v[PG][3];
+#pragma unroll
+    for (int q = 0; q < PG; ++q) {
+        const int i = (int)threadIdx.x + q * DO_THREADS;
+        const int hx = i % DA_GX, r = i / DA_GX, hy = r % DA_GY, hz = r / DA_GY;
+        const int s = i < NG ? do_src(c, t0[0] - 1 + hx, t0[1] - 1 + hy, t0[2] - 1 + hz) : -1;
+#pragma unroll
+        for (int d = 0; d < 3; ++d) v[q][d] = dn_at(c.src[d], s);
+    }
+#pragma unroll
+    for (int q = 0; q < PG; ++q) {
+        const int i = (int)threadIdx.x + q * DO_THREADS;
+        if (i < NG)
+#pragma unroll
+            for (int d = 0; d < 3; ++d) gs[d][i] = v[q][d];
+    }
+    __syncthreads();
+    for (int i = threadIdx.x; i < NB; i += DO_THREADS) {
+        const int hx = i % DA_BX, r = i / DA_BX, hy = r % DA_BY, hz = r / DA_BY;
+        const bool in = do_src(c, t0[0] + hx, t0[1] + hy, t0[2] + hz) >= 0;
+#pragma unroll
+        for (int comp = 0; comp < 3; ++comp) bs[comp][i] = in ? do_binomial<DA_GX, DA_GY>(gs[comp], hx, hy, hz) : 0.0f;
+    }
+    __syncthreads();
+    const int lx = threadIdx.x % DO_TX, ly = (threadIdx.x / DO_TX) % DO_TY, lz = threadIdx.x / (DO_TX * DO_TY);
+    const int x = t0[0] + lx, y = t0[1] + ly, z = t0[2] + lz;
+    if (x >= c.n[0] || y >= c.n[1] || z >= c.n[2]) return;
+    const int b = (lz * DA_BY + ly) * DA_BX + lx;
+    const int up[3] = {b + 1, b + DA_BX, b + DA_BX * DA_BY};
+    bf16x4 out;
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        const int a1 = (a + 1) % 3, a2 = (a + 2) % 3;
+        const float w = (bs[a2][up[a1]] - bs[a2][b]) * c.inv_d[a1] - (bs[a1][up[a2]] - bs[a1][b]) * c.inv_d[a2];
+        out[a] = (__bf16)(c.sigma * w);
+    }
+    out[3] = (__bf16)0.0f;
+    reinterpret_cast<bf16x4*>(c.dy)[do_src(c, x, y, z)] = out;
+}
+
+static dim3 do_grid(const DnCombine& c) {
+    return dim3((c.n[0] + DO_TX - 1) / DO_TX, (c.n[1] + DO_TY - 1) / DO_TY, (c.n[2] + DO_TZ - 1) / DO_TZ);
+}
+
+hipError_t launch_dn_output(const DnCombine& c, bool loss, hipStream_t st) {
+    hipLaunchKernelGGL(loss ? k_dn_output<true> : k_dn_output<false>, do_grid(c), dim3(DO_THREADS), 0, st, c);
     return hipGetLastError();
 }
 
-static dim3 dn_cells_grid(const DnCombine& c) { return dim3((c.n[0] * c.n[1] * c.n[2] + 255) / 256); }
-
-hipError_t launch_dn_curl_add(const DnCombine& c, hipStream_t st) {
-    hipLaunchKernelGGL(k_dn_curl_add, dn_cells_grid(c), dim3(256), 0, st, c);
-    return hipGetLastError();
-}
-
-hipError_t launch_dn_binomial(const DnCombine& c, bool loss, hipStream_t st) {
-    if (loss)
-        hipLaunchKernelGGL(k_dn_binomial<true>, dn_cells_grid(c), dim3(256), 0, st, c);
-    else
-        hipLaunchKernelGGL(k_dn_binomial<false>, dn_cells_grid(c), dim3(256), 0, st, c);
-    return hipGetLastError();
-}
-
-hipError_t launch_dn_curl_adjoint(const DnCombine& c, hipStream_t st) {
-    hipLaunchKernelGGL(k_dn_curl_adjoint, dn_cells_grid(c), dim3(256), 0, st, c);
+hipError_t launch_dn_output_adjoint(const DnCombine& c, hipStream_t st) {
+    hipLaunchKernelGGL(k_dn_output_adjoint, do_grid(c), dim3(DO_THREADS), 0, st, c);
     return hipGetLastError();
 }
 
@@ -535,7 +501,7 @@ hipError_t launch_denoise(const Geom& g, const int bc[3], const DenoiseWeights& 
     }
     c.origin = a.origin;
     c.sigma = w.sigma;
-    return launch_dn_output(c, st);
+    return launch_dn_output(c, false, st);
 }
 
 }  // namespace pic

@@ -97,9 +97,9 @@ struct DnCombine {
     int n[3];
     int bc[3];
     int origin;
-    const float* src[3];    // curl_add: J;   binomial: its input
+    const float* src[3];    // J (adjoint: dL/dJ')
     const float* y[3];
-    float* dst[3];          // curl_add: J + sigma curl(y);  binomial: B(src) (or the loss gradient)
+    float* dst[3];          // J' (or the loss gradient)
     float sigma;
     float inv_d[3];
     // training
@@ -110,12 +110,10 @@ struct DnCombine {
     __bf16* dy;             // sigma curl^T(src) as bf16 [cell][4]
 };
 
-// dst = src + sigma curl(y)
-hipError_t launch_dn_curl_add(const DnCombine& c, hipStream_t st);
-// dst = B(src); with loss: J' = B(src) against T, dst = dL/dJ' = grad_scale (J' - T) / s^2
-hipError_t launch_dn_binomial(const DnCombine& c, bool loss, hipStream_t st);
-// dy = sigma curl^T(src)
-hipError_t launch_dn_curl_adjoint(const DnCombine& c, hipStream_t st);
+// dst = B(src + sigma curl(y)); with loss: J' = that against T, dst = dL/dJ' = grad_scale (J' - T) / s^2
+hipError_t launch_dn_output(const DnCombine& c, bool loss, hipStream_t st);
+// dy = sigma curl^T(B src)
+hipError_t launch_dn_output_adjoint(const DnCombine& c, hipStream_t st);
 
 // Output tiles of a box of n cells.
 inline dim3 dn_grid(const int n[3]) {
@@ -204,9 +202,9 @@ __device__ __forceinline__ int dn_axis_sel(int v, int n, int bc, int origin) {
     return bc != 0 && out ? -1 : r;
 }
 
-__device__ __forceinline__ void dn_load_act(const DnArgs& a, const DnBox& b, const int t0[3],
+__device__ __forceinline__ void dn_load_act(const __bf16* __restrict__ act, const DnBox& b, const int t0[3],
                                             const int hc[DN_ACT_PER], uint4 v[DN_ACT_PER]) {
-    const uint4* src = reinterpret_cast<const uint4*>(a.act_in);
+    const uint4* src = reinterpret_cast<const uint4*>(act);
     long long off[DN_ACT_PER];
 #pragma unroll
     for (int k = 0; k < DN_ACT_PER; ++k) {

@@ -29,134 +29,244 @@ namespace pic {
 
 struct WgArgs {
     int n[3];
-    int bc[3];
-    const __bf16* in;     // [cell][CIN] bf16 (unless the input is the scaled current)
+    const __bf16* in;     // [cell][32] bf16 (unless the input is the scaled current)
     const float* J[3];    // scaled-current input (layer 1)
     float inv_scale[3];
     const __bf16* dout;   // [cell][DC] bf16
     float* dW;            // [16 MB][NPAD] FP32
     float* db;            // [DC] FP32
-    int ntiles;
 };
 
-// Flat tile index -> tile origin.
-__device__ __forceinline__ void wg_tile(const WgArgs& a, int t, int t0[3]) {
-    const int gx = (a.n[0] + DN_TX - 1) / DN_TX, gy = (a.n[1] + DN_TY - 1) / DN_TY;
-    t0[0] = (t % gx) * DN_TX;
-    t0[1] = ((t / gx) % gy) * DN_TY;
-    t0[2] = (t / (gx * gy)) * DN_TZ;
+// Both operands have the cells as their K index, but lie in LDS with a cell's
+// channels together: ds_read_b64_tr_b16 transposes while it reads.  In each
+// group of 16 lanes, lane t gives the address of 4 channels ((t & 3) 4 ..) of
+// row t >> 2 and receives channel t of the 4 rows: two such reads, rows four
+// apart, make one 16x16x32 operand (8 consecutive x cells per lane, as the
+// MFMA wants its K elements).
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+
+__device__ __forceinline__ bf16x8 tr_operand(const char* p, int rows4) {
+    typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
+    const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)p);
+    const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(p + rows4));
+    typedef short s16x8 __attribute__((ext_vector_type(8)));
+    const s16x8 v = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+    return __builtin_bit_cast(bf16x8, v);
 }
 
-__device__ __forceinline__ int wg_src(const WgArgs& a, const int t0[3], int hx, int hy, int hz) {
-    const int x = dn_axis(t0[0] - 1 + hx, a.n[0], a.bc[0], 0);
-    const int y = dn_axis(t0[1] - 1 + hy, a.n[1], a.bc[1], 0);
-    const int z = dn_axis(t0[2] - 1 + hz, a.n[2], a.bc[2], 0);
-    if (x < 0 || y < 0 || z < 0) return -1;
-    return x + a.n[0] * (y + a.n[1] * z);
-}
+// Byte offset of the 16-channel half `half` of 64-byte cell row c: the halves
+// of every second pair of rows are exchanged, so that the four rows of one
+// transposing read lie in 32 different banks.
+__device__ __forceinline__ int wg_half(int c, int half) { return c * 64 + ((half ^ ((c >> 1) & 1)) << 5); }
 
-template <int CIN, int DC, int MB, bool INJ>
+constexpr int WG_CELLS = DN_TX * DN_TY * DN_TZ;   // cells of a tile
+constexpr int WG_CHUNKS = WG_CELLS / 32;          // K steps of a tile
+
+// dW[co][n] of the cells of this workgroup's tiles, n = tap * CIN + channel in
+// NB blocks of 16 columns, co in MB blocks of 16 rows.  Persistent: one
+// workgroup per compute unit walks an XCD's contiguous range
+// of tiles, loading the next tile's halo and output gradient into registers
+// while the matrix work of the current one runs.  32 input channels: each
+// wavefront takes every eighth column block and all K steps, a B operand
+// serves both row blocks.  4 input channels (7 column blocks): each wavefront
+// takes all blocks and an eighth of the K steps; their sums meet in LDS.
+// The bias gradient is one more column, whose input is 1 (32 channels: block
+// NB; 4 channels: the columns past tap 26 of the last block).
+// Element by element reads of the operands (eight 2-byte LDS reads each)
+// bounded the earlier form; 128x64x64 cells: 342 -> 82 us (32 x 32
+// channels), 73 -> 47 (32 x 3), 123 -> 54 (3 x 32); the latency of a tile's
+// loads bounds it now.
+template <int CIN, int DC>
 __global__ void __launch_bounds__(DN_THREADS) k_dn_wgrad(WgArgs a) {
-    constexpr int NB = (27 * CIN + 15) / 16;          // 16-column blocks of n
-    constexpr int NPAIR = MB * NB;
-    constexpr int PW = (NPAIR + 7) / 8;               // (mb, nb) pairs per wavefront
-    extern __shared__ __attribute__((aligned(16))) char wlds[];
-    __bf16* in_l = reinterpret_cast<__bf16*>(wlds);                         // [halo cell][CIN]
-    __bf16* do_l = reinterpret_cast<__bf16*>(wlds + DN_HCELLS * CIN * 2);  // [tile cell][DC]
-    const int l = threadIdx.x & 63, w = threadIdx.x >> 6;
+    constexpr int DCP = DC < 16 ? 16 : DC;            // padded channels of a staged output gradient
+    constexpr int MB = DCP / 16, NB = (27 * CIN + 15) / 16, NPAD = NB * 16;
+    constexpr bool KSPLIT = CIN == 4;
+    constexpr int PW = KSPLIT ? NB : (NB + 1 + 7) / 8;   // column blocks per wavefront
+    constexpr int IN_B = DN_HCELLS * CIN * 2, DO_B = WG_CELLS * DCP * 2;
+    constexpr int RED = 32 * NPAD;                    // (K split) sums of the wavefronts
+    __shared__ __attribute__((aligned(16))) char lds[IN_B + DO_B + 64 + (KSPLIT ? RED * 4 : 0)];
+    __shared__ float bias[DC];
+    char* in_l = lds;                 // halo cells (wg_half rows, or [cell][4])
+    char* do_l = lds + IN_B;          // tile cells (wg_half rows, or [cell][16])
+    char* ones_l = do_l + DO_B;       // 32 ones
+    const int l = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int m = l & 15, q = l >> 4;
-    // per pair: halo offset of the tap, channel, validity
-    int pdel[PW], pci[PW], pmb[PW];
-    bool pok[PW];
+    const __bf16 one = (__bf16)1.0f;
+    const bf16x8 ones = {one, one, one, one, one, one, one, one};
+    if (threadIdx.x < 32) reinterpret_cast<__bf16*>(ones_l)[threadIdx.x] = one;
+    if (DC < 16)
+        for (int i = threadIdx.x; i < DO_B / 4; i += DN_THREADS) reinterpret_cast<int*>(do_l)[i] = 0;
+    // lane offsets of the operands: cells 4 h + (m >> 2) of the lane's x row
+    int boff[PW];
+    bool past = false;   // this lane's piece of the last column block is past tap 26
 #pragma unroll
     for (int i = 0; i < PW; ++i) {
-        const int p = w + 8 * i;
-        const int mb = p / NB, nb = p % NB;
-        const int nn = nb * 16 + m;
-        const int tap = nn / CIN;
-        pok[i] = p < NPAIR && tap < 27;
+        const int nb = KSPLIT ? i : w + 8 * i;
+        const int tap = KSPLIT ? 4 * nb + (m & 3) : nb >> 1;
         const int dz = tap / 9, dy = (tap / 3) % 3, dx = tap % 3;
-        pdel[i] = (dz * DN_HY + dy) * DN_HX + dx;
-        pci[i] = nn % CIN;
-        pmb[i] = mb;
+        const int c = (dz * DN_HY + dy) * DN_HX + dx + (m >> 2);
+        if (KSPLIT) {
+            boff[i] = c * 8;
+            if (tap > 26) past = true;
+        } else {
+            boff[i] = wg_half(c, nb & 1) + (m & 3) * 8;   // (row starts are multiples of 4 cells: the parity stays)
+        }
     }
-    f32x4 acc[PW];
+    const int aoff = DC < 16 ? (m >> 2) * 32 + (m & 3) * 8 : wg_half(m >> 2, 0) + (m & 3) * 8;
+    f32x4 acc[PW][MB];
 #pragma unroll
-    for (int i = 0; i < PW; ++i) acc[i] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-    float bsum = 0.0f;
-    for (int t = blockIdx.x; t < a.ntiles; t += gridDim.x) {
+    for (int i = 0; i < PW; ++i)
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb) acc[i][mb] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+    // the tiles of this workgroup (as the persistent layers walk them)
+    int ntx, nty;
+    const int ntiles = dn_ntiles(a.n, &ntx, &nty);
+    int tile, stride, end;
+    if (gridDim.x % 8 == 0) {
+        const int per = (ntiles + 7) / 8, k = blockIdx.x % 8;
+        tile = k * per + blockIdx.x / 8;
+        stride = gridDim.x / 8;
+        end = min(ntiles, (k + 1) * per);
+    } else {
+        tile = blockIdx.x;
+        stride = gridDim.x;
+        end = ntiles;
+    }
+    DnBox box;
+#pragma unroll
+    for (int d = 0; d < 3; ++d) {
+        box.n[d] = a.n[d];
+        box.bc[d] = 1;   // zero beyond the crop's faces
+    }
+    box.origin = 0;
+    int hc[DN_ACT_PER];
+    if (!KSPLIT) dn_halo_coords(hc);
+    constexpr int JPER = (DN_HCELLS + DN_THREADS - 1) / DN_THREADS;
+    constexpr int OPER = DC < 16 ? 1 : WG_CELLS * 4 / DN_THREADS;   // pieces of the output gradient per thread
+    uint4 hv[KSPLIT ? 1 : DN_ACT_PER], ov[OPER];
+    float jv[KSPLIT ? JPER : 1][3];
+    auto load = [&](int t) {
         int t0[3];
-        wg_tile(a, t, t0);
-        __syncthreads();   // the previous tile's reads are done
-        for (int c = threadIdx.x; c < DN_HCELLS; c += DN_THREADS) {
-            const int hx = c % DN_HX, r = c / DN_HX, hy = r % DN_HY, hz = r / DN_HY;
-            const int s = hx < DN_TX + 2 ? wg_src(a, t0, hx, hy, hz) : -1;
-            if (INJ) {
+        dn_tile_of(t, ntx, nty, t0);
+        if constexpr (KSPLIT) {
 #pragma unroll
-                for (int d = 0; d < 4; ++d)
-                    in_l[c * CIN + d] = (__bf16)(s >= 0 && d < 3 ? a.J[d][s] * a.inv_scale[d] : 0.0f);
+            for (int k = 0; k < JPER; ++k) {
+                const int c = threadIdx.x + k * DN_THREADS;
+                const int hx = c % DN_HX, r = c / DN_HX;
+                const int x = t0[0] - 1 + hx, y = t0[1] - 1 + r % DN_HY, z = t0[2] - 1 + r / DN_HY;
+                const bool ok = c < DN_HCELLS && hx < DN_TX + 2 && x >= 0 && x < a.n[0] && y >= 0 && y < a.n[1] &&
+                                z >= 0 && z < a.n[2];
+                const size_t s = ok ? (size_t)x + a.n[0] * ((size_t)y + (size_t)a.n[1] * z) : 0;
+#pragma unroll
+                for (int d = 0; d < 3; ++d) jv[k][d] = ok ? a.J[d][s] : 0.0f;
+            }
+        } else {
+            dn_load_act(a.in, box, t0, hc, hv);
+        }
+#pragma unroll
+        for (int k = 0; k < OPER; ++k) {
+            const int g = threadIdx.x + k * DN_THREADS, c = DC < 16 ? g : g >> 2;
+            const int lx = c % DN_TX, r = c / DN_TX;
+            const int x = t0[0] + lx, y = t0[1] + r % DN_TY, z = t0[2] + r / DN_TY;
+            const bool ok = x < a.n[0] && y < a.n[1] && z < a.n[2];
+            const size_t s = ok ? (size_t)x + a.n[0] * ((size_t)y + (size_t)a.n[1] * z) : 0;
+            if (DC < 16) {
+                const uint2 v = ok ? reinterpret_cast<const uint2*>(a.dout)[s] : make_uint2(0u, 0u);
+                ov[k] = make_uint4(v.x, v.y, 0u, 0u);
             } else {
-                const uint4* src = reinterpret_cast<const uint4*>(a.in + (size_t)(s >= 0 ? s : 0) * CIN);
-                uint4* dst = reinterpret_cast<uint4*>(in_l + c * CIN);
-#pragma unroll
-                for (int k = 0; k < CIN / 8; ++k) dst[k] = s >= 0 ? src[k] : make_uint4(0u, 0u, 0u, 0u);
+                ov[k] = ok ? reinterpret_cast<const uint4*>(a.dout)[s * 4 + (g & 3)] : make_uint4(0u, 0u, 0u, 0u);
             }
         }
-        for (int c = threadIdx.x; c < DN_TX * DN_TY * DN_TZ; c += DN_THREADS) {
-            const int lx = c % DN_TX, r = c / DN_TX, ly = r % DN_TY, lz = r / DN_TY;
-            const int x = t0[0] + lx, y = t0[1] + ly, z = t0[2] + lz;
-            const bool inside = x < a.n[0] && y < a.n[1] && z < a.n[2];
-            const size_t s = inside ? (size_t)x + a.n[0] * ((size_t)y + (size_t)a.n[1] * z) : 0;
-            if (DC == 4) {
-                const uint2 v = inside ? reinterpret_cast<const uint2*>(a.dout)[s] : make_uint2(0u, 0u);
-                reinterpret_cast<uint2*>(do_l)[c] = v;
-            } else {
-                const uint4* src = reinterpret_cast<const uint4*>(a.dout + s * DC);
-                uint4* dst = reinterpret_cast<uint4*>(do_l + c * DC);
+    };
+    if (tile < end) load(tile);
+    for (; tile < end; tile += stride) {
+        __syncthreads();   // the previous tile's LDS reads are done
+        if constexpr (KSPLIT) {
 #pragma unroll
-                for (int k = 0; k < DC / 8; ++k) dst[k] = inside ? src[k] : make_uint4(0u, 0u, 0u, 0u);
+            for (int k = 0; k < JPER; ++k) {
+                const int c = threadIdx.x + k * DN_THREADS;
+                bf16x4 v;
+#pragma unroll
+                for (int d = 0; d < 3; ++d) v[d] = (__bf16)(jv[k][d] * a.inv_scale[d]);
+                v[3] = (__bf16)0.0f;
+                if (c < DN_HCELLS) *reinterpret_cast<bf16x4*>(in_l + c * 8) = v;
             }
+        } else {
+#pragma unroll
+            for (int k = 0; k < DN_ACT_PER; ++k) {
+                const int g = threadIdx.x + k * DN_THREADS, c = g >> 2;
+                if (g < DN_HCELLS * 4)
+                    *reinterpret_cast<uint4*>(in_l + wg_half(c, (g >> 1) & 1) + (g & 1) * 16) = hv[k];
+            }
+        }
+#pragma unroll
+        for (int k = 0; k < OPER; ++k) {
+            const int g = threadIdx.x + k * DN_THREADS;
+            if (DC < 16)
+                *reinterpret_cast<uint2*>(do_l + g * 32) = make_uint2(ov[k].x, ov[k].y);
+            else
+                *reinterpret_cast<uint4*>(do_l + wg_half(g >> 2, (g >> 1) & 1) + (g & 1) * 16) = ov[k];
         }
         __syncthreads();
-        if ((int)threadIdx.x < DC)
-            for (int c = 0; c < DN_TX * DN_TY * DN_TZ; ++c) bsum += (float)do_l[c * DC + threadIdx.x];
-        for (int ch = 0; ch < DN_TX * DN_TY * DN_TZ / 32; ++ch) {
+        if (tile + stride < end) load(tile + stride);
+#pragma unroll 1
+        for (int ch = KSPLIT ? w : 0; ch < WG_CHUNKS; ch += KSPLIT ? 8 : 1) {
             // K elements of this lane: tile cells 32 ch + 8 q + j, j = 0..7 (one x-row half)
             const int row = 2 * ch + (q >> 1);
             const int lz = row / DN_TY, ly = row % DN_TY, lx0 = 8 * (q & 1);
             const int hbase = (lz * DN_HY + ly) * DN_HX + lx0;
-            const int cbase = row * DN_TX + lx0;
+            const char* ap = do_l + aoff + (row * DN_TX + lx0) * (DCP * 2);
             bf16x8 A[MB];
-#pragma unroll
-            for (int mb = 0; mb < MB; ++mb) {
-                const int co = mb * 16 + m;
-#pragma unroll
-                for (int j = 0; j < 8; ++j) A[mb][j] = co < DC ? do_l[(cbase + j) * DC + co] : (__bf16)0.0f;
-            }
+            A[0] = tr_operand(ap, 4 * DCP * 2);
+            // (the other half of a swizzled row is 32 bytes up or down)
+            if constexpr (MB == 2) A[1] = tr_operand(ap + (((m >> 3) & 1) ? -32 : 32), 4 * DCP * 2);
+            const char* bp = in_l + hbase * (CIN * 2);
 #pragma unroll
             for (int i = 0; i < PW; ++i) {
-                if (w + 8 * i >= NPAIR) break;
+                if (!KSPLIT && w + 8 * i > NB) break;
+                const char* p = bp + boff[i];
+                if (KSPLIT && i == PW - 1 && past) p = ones_l;
                 bf16x8 B;
+                if (!KSPLIT && w + 8 * i == NB) B = ones;
+                else B = tr_operand(p, 4 * CIN * 2);
 #pragma unroll
-                for (int j = 0; j < 8; ++j) B[j] = pok[i] ? in_l[(hbase + j + pdel[i]) * CIN + pci[i]] : (__bf16)0.0f;
-                acc[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A[pmb[i]], B, acc[i], 0, 0, 0);
+                for (int mb = 0; mb < MB; ++mb)
+                    acc[i][mb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A[mb], B, acc[i][mb], 0, 0, 0);
             }
         }
     }
-    constexpr int NPAD = NB * 16;
+    float* red = reinterpret_cast<float*>(ones_l + 64);
+    if (KSPLIT)
+        for (int i = threadIdx.x; i < RED; i += DN_THREADS) red[i] = 0.0f;
+    __syncthreads();
 #pragma unroll
     for (int i = 0; i < PW; ++i) {
-        const int p = w + 8 * i;
-        if (p >= NPAIR) break;
-        const int nn = (p % NB) * 16 + m;
-        if (nn >= 27 * CIN) continue;
+        const int nb = KSPLIT ? i : w + 8 * i;
+        if (nb > NB) break;
+        const int nn = nb * 16 + m;
+        if (nn > 27 * CIN) continue;
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int co = pmb[i] * 16 + 4 * q + j;
-            if (co < DC) atomicAdd(a.dW + (size_t)co * NPAD + nn, acc[i][j]);
-        }
+        for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const int co = mb * 16 + 4 * q + j;
+                if (co >= DC) continue;
+                if (KSPLIT)
+                    atomicAdd(red + co * NPAD + nn, acc[i][mb][j]);
+                else if (nn == 27 * CIN)
+                    bias[co] = acc[i][mb][j];   // (one wavefront and lane group per channel)
+                else
+                    unsafeAtomicAdd(a.dW + (size_t)co * NPAD + nn, acc[i][mb][j]);
+            }
     }
-    if ((int)threadIdx.x < DC) atomicAdd(a.db + threadIdx.x, bsum);
+    __syncthreads();
+    if (KSPLIT)
+        for (int i = threadIdx.x; i < RED; i += DN_THREADS)
+            if (i % NPAD < 27 * CIN) unsafeAtomicAdd(a.dW + i, red[i]);
+    // (one instruction for all channels: every workgroup adds to this one line,
+    // and a request per channel cost 60 us)
+    if ((int)threadIdx.x < DC)
+        unsafeAtomicAdd(a.db + threadIdx.x, KSPLIT ? red[threadIdx.x * NPAD + 27 * CIN] : bias[threadIdx.x]);
 }
 
 // ---- parameters -------------------------------------------------------------
@@ -234,6 +344,14 @@ __global__ void k_dn_adam_pack(float* __restrict__ P, float* __restrict__ M, flo
     }
 }
 
+// The loss (8 bytes) and the gradient in the order of the parameter vector,
+// together for one copy to the host.
+__global__ void k_dn_grad_out(const float* __restrict__ G, const double* __restrict__ loss, char* __restrict__ out) {
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < kP_N) reinterpret_cast<float*>(out + 8)[i] = G[grad_index(i)];
+    if (i == 0) *reinterpret_cast<double*>(out) = *loss;
+}
+
 __global__ void k_dn_zero(float* __restrict__ p, int n, double* __restrict__ loss) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i < n) p[i] = 0.0f;
@@ -255,7 +373,7 @@ constexpr size_t kAl = 256;
 size_t al(size_t v) { return (v + kAl - 1) / kAl * kAl; }
 
 struct TrLayout {
-    size_t P, M, V, G, K, Bk, loss, a1, a2, dy, dz2, dz1, y, g, t, total;
+    size_t P, M, V, G, K, Bk, loss, out, a1, a2, dy, dz2, dz1, y, g, total;
 };
 
 TrLayout tr_layout(const int32_t c[3]) {
@@ -274,6 +392,7 @@ TrLayout tr_layout(const int32_t c[3]) {
     L.K = take(kK_N * 2);
     L.Bk = take(kB_N * 4);
     L.loss = take(8);
+    L.out = take(8 + kP_N * 4);
     L.a1 = take(N * 64);
     L.a2 = take(N * 64);
     L.dy = take(N * 8);
@@ -281,7 +400,6 @@ TrLayout tr_layout(const int32_t c[3]) {
     L.dz1 = take(N * 64);
     L.y = take(N * 12);
     L.g = take(N * 12);
-    L.t = take(N * 12);
     L.total = o;
     return L;
 }
@@ -339,14 +457,13 @@ DnArgs base_args(pic_dn_trainer* t, float* const in[3], float* const target[3]) 
     return a;
 }
 
-template <int CIN, int DC, int MB, bool INJ>
+template <int CIN, int DC>
 hipError_t wgrad(pic_dn_trainer* t, const WgArgs& w) {
-    const size_t lds = (size_t)DN_HCELLS * CIN * 2 + (size_t)DN_TX * DN_TY * DN_TZ * DC * 2;
-    hipError_t e = hipFuncSetAttribute((const void*)k_dn_wgrad<CIN, DC, MB, INJ>,
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    if (e != hipSuccess) return e;
-    const int grid = w.ntiles < 512 ? w.ntiles : 512;
-    hipLaunchKernelGGL((k_dn_wgrad<CIN, DC, MB, INJ>), dim3(grid), dim3(DN_THREADS), lds, t->st, w);
+    const dim3 g = dn_grid(t->n);
+    const long long ntiles = (long long)g.x * g.y * g.z;
+    long long nb = ntiles < 256 ? ntiles : 256;   // one workgroup per compute unit
+    if (nb >= 8) nb -= nb % 8;
+    hipLaunchKernelGGL((k_dn_wgrad<CIN, DC>), dim3((unsigned)nb), dim3(DN_THREADS), 0, t->st, w);
     return hipGetLastError();
 }
 
@@ -378,15 +495,14 @@ pic_status tr_grad(pic_dn_trainer* t, float* const in[3], float* const target[3]
     a.w = K + kK_W3, a.bias = Bk + 64, a.act_in = a2, a.act_out = nullptr;
     for (int d = 0; d < 3; ++d) a.Jout[d] = y + d * N;
     THIPCHK(t, launch_dn_layer(DN_L3_Y, a, t->st));
-    // t = J + sigma curl(y);  J' = B(t);  loss;  g = dL/dJ';  dy = sigma curl^T(B g)
-    float* tb = at<float>(t, t->L.t);
+    // J' = B(J + sigma curl(y));  loss;  g = dL/dJ';  dy = sigma curl^T(B g)
     DnCombine c{};
     for (int d = 0; d < 3; ++d) {
         c.n[d] = t->n[d];
         c.bc[d] = 1;
         c.src[d] = in[d];
         c.y[d] = y + d * N;
-        c.dst[d] = tb + d * N;
+        c.dst[d] = gJ + d * N;
         c.T[d] = target[d];
         c.inv_scale[d] = 1.0f / t->scale[d];
         c.inv_d[d] = (float)(1.0 / t->cell[d]);
@@ -395,40 +511,27 @@ pic_status tr_grad(pic_dn_trainer* t, float* const in[3], float* const target[3]
     c.grad_scale = a.grad_scale;
     c.loss = a.loss;
     c.dy = dy;
-    THIPCHK(t, launch_dn_curl_add(c, t->st));
-    for (int d = 0; d < 3; ++d) {
-        c.src[d] = tb + d * N;
-        c.dst[d] = gJ + d * N;
-    }
-    THIPCHK(t, launch_dn_binomial(c, true, t->st));
+    THIPCHK(t, launch_dn_output(c, true, t->st));
     if (forward_only) return PIC_OK;
-    for (int d = 0; d < 3; ++d) {
-        c.src[d] = gJ + d * N;
-        c.dst[d] = tb + d * N;
-    }
-    THIPCHK(t, launch_dn_binomial(c, false, t->st));     // B is symmetric: B^T g = B g
-    for (int d = 0; d < 3; ++d) c.src[d] = tb + d * N;
-    THIPCHK(t, launch_dn_curl_adjoint(c, t->st));
+    for (int d = 0; d < 3; ++d) c.src[d] = gJ + d * N;
+    THIPCHK(t, launch_dn_output_adjoint(c, t->st));
     // backward
     WgArgs w{};
     for (int d = 0; d < 3; ++d) {
         w.n[d] = t->n[d];
-        w.bc[d] = 1;
         w.J[d] = in[d];
         w.inv_scale[d] = 1.0f / t->scale[d];
     }
-    const dim3 gr = dn_grid(t->n);
-    w.ntiles = (int)(gr.x * gr.y * gr.z);
     w.in = a2, w.dout = dy, w.dW = G + kG_W3, w.db = G + kG_B3;
-    THIPCHK(t, (wgrad<32, 4, 1, false>(t, w)));
+    THIPCHK(t, (wgrad<32, 4>(t, w)));
     a.c4_in = dy, a.w = K + kK_W3T, a.mask = a2, a.act_out = dz2;
     THIPCHK(t, launch_dn_layer(DN_L1_C4_MASK, a, t->st));
     w.in = a1, w.dout = dz2, w.dW = G + kG_W2, w.db = G + kG_B2;
-    THIPCHK(t, (wgrad<32, 32, 2, false>(t, w)));
+    THIPCHK(t, (wgrad<32, 32>(t, w)));
     a.act_in = dz2, a.w = K + kK_W2T, a.mask = a1, a.act_out = dz1;
     THIPCHK(t, launch_dn_layer(DN_L2_MASK, a, t->st));
     w.in = nullptr, w.dout = dz1, w.dW = G + kG_W1, w.db = G + kG_B1;
-    THIPCHK(t, (wgrad<4, 32, 2, true>(t, w)));
+    THIPCHK(t, (wgrad<4, 32>(t, w)));
     return PIC_OK;
 }
 
@@ -585,24 +688,15 @@ pic_status pic_dn_trainer_grad(pic_dn_trainer* t, float* const input[3], float* 
     if (!t->has_params) return tfail(t, PIC_ESTATE, "parameters not set");
     pic_status s = tr_grad(t, input, target);
     if (s != PIC_OK) return s;
-    std::vector<float> g(kG_N);
-    THIPCHK(t, hipMemcpyAsync(g.data(), t->ws + t->L.G, kG_N * 4, hipMemcpyDeviceToHost, t->st));
-    THIPCHK(t, hipMemcpyAsync(loss, t->ws + t->L.loss, 8, hipMemcpyDeviceToHost, t->st));
+    hipLaunchKernelGGL(k_dn_grad_out, dim3((kP_N + 255) / 256), dim3(256), 0, t->st, at<float>(t, t->L.G),
+                       at<double>(t, t->L.loss), t->ws + t->L.out);
+    THIPCHK(t, hipGetLastError());
+    std::vector<char> h(8 + kP_N * 4);
+    THIPCHK(t, hipMemcpyAsync(h.data(), t->ws + t->L.out, h.size(), hipMemcpyDeviceToHost, t->st));
     THIPCHK(t, hipStreamSynchronize(t->st));
-    for (int co = 0; co < 32; ++co)
-        for (int ci = 0; ci < 3; ++ci)
-            for (int tp = 0; tp < 27; ++tp) grad_weights[kP_W1 + (co * 3 + ci) * 27 + tp] = g[kG_W1 + co * 112 + tp * 4 + ci];
-    for (int co = 0; co < 32; ++co)
-        for (int ci = 0; ci < 32; ++ci)
-            for (int tp = 0; tp < 27; ++tp)
-                grad_weights[kP_W2 + (co * 32 + ci) * 27 + tp] = g[kG_W2 + co * 864 + tp * 32 + ci];
-    for (int co = 0; co < 3; ++co)
-        for (int ci = 0; ci < 32; ++ci)
-            for (int tp = 0; tp < 27; ++tp)
-                grad_weights[kP_W3 + (co * 32 + ci) * 27 + tp] = g[kG_W3 + co * 864 + tp * 32 + ci];
-    for (int i = 0; i < 32; ++i) grad_biases[i] = g[kG_B1 + i];
-    for (int i = 0; i < 32; ++i) grad_biases[32 + i] = g[kG_B2 + i];
-    for (int i = 0; i < 3; ++i) grad_biases[64 + i] = g[kG_B3 + i];
+    memcpy(loss, h.data(), 8);
+    memcpy(grad_weights, h.data() + 8, sizeof(float) * kP_B1);
+    memcpy(grad_biases, h.data() + 8 + sizeof(float) * kP_B1, sizeof(float) * (kP_N - kP_B1));
     return PIC_OK;
 }
 
