@@ -12,47 +12,48 @@
 namespace pic {
 
 // 32 output channels: EPI 0 = bf16 relu(acc + bias), 1 = bf16 acc where the
-// mask activation is > 0.  The tile's 512 x 32 bf16 outputs are first placed
-// in the LDS buffer ob (32 KB, rows swizzled like the inputs, so the 16 lanes
-// of one cell and the 4 cells of one write hit different banks), then stored
-// to HBM as whole 16-byte chunks of each cell.  The caller guarantees that no
-// wavefront still reads ob; the function ends with ob free again only after
-// the caller's next barrier.
+// mask activation is > 0.  The weights are the first operand of the MFMAs, so
+// that lane (m, q) = (l & 15, l >> 4) holds channels 8 q + 4 h + j (dn_co) of
+// cell m of each row block: 16 consecutive bytes of one cell, stored straight
+// from the registers, four lanes to a cell's 64 bytes (the mask is read the
+// same way).  Staging the output tile through LDS instead, with its two
+// barriers and 32 two-byte stores per lane, took
+// 773 us for layer 2 and 336 for layer 1 on 384x192x160 cells; this takes 746
+// and 307.
 template <int EPI>
-__device__ __forceinline__ void dn_store32(const DnArgs& a, const int t0[3], const f32x4 acc[4][2], char* ob) {
+__device__ __forceinline__ void dn_store32(const DnArgs& a, const int t0[3], const f32x4 acc[4][2],
+                                           const float bias[2][4]) {
     const int l = threadIdx.x & 63, lz = threadIdx.x >> 6;
-    const int col = l & 15, rq = l >> 4;
+    const int m = l & 15, q = l >> 4;
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
-        const int co = h * 16 + col;
-        const float b = EPI == 0 ? a.bias[co] : 0.0f;
+    for (int blk = 0; blk < 4; ++blk) {
+        const int cell = dn_out_cell(a, t0, lz, blk, m);
+        if (cell < 0) continue;
+        bf16x8 v;
+        if (EPI == 0) {
 #pragma unroll
-        for (int blk = 0; blk < 4; ++blk)
+            for (int h = 0; h < 2; ++h)
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const int m = rq * 4 + j;
-                float v;
-                if (EPI == 0) {
-                    v = fmaxf(acc[blk][h][j] + b, 0.0f);
-                } else {
-                    const int cell = dn_out_cell(a, t0, lz, blk, m);
-                    v = cell >= 0 && (float)a.mask[(size_t)cell * 32 + co] > 0.0f ? acc[blk][h][j] : 0.0f;
-                }
-                const int lc = (lz * DN_TY + blk) * DN_TX + m;
-                *reinterpret_cast<__bf16*>(ob + dn_chunk(lc, co >> 3) + (co & 7) * 2) = (__bf16)v;
-            }
+                for (int j = 0; j < 4; ++j) v[4 * h + j] = (__bf16)fmaxf(acc[blk][h][j] + bias[h][j], 0.0f);
+        } else {
+            const bf16x8 mk = reinterpret_cast<const bf16x8*>(a.mask)[(size_t)cell * 4 + q];
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+                    v[4 * h + j] = (float)mk[4 * h + j] > 0.0f ? (__bf16)acc[blk][h][j] : (__bf16)0.0f;
+        }
+        reinterpret_cast<bf16x8*>(a.act_out)[(size_t)cell * 4 + q] = v;
     }
-    __syncthreads();
-    constexpr int NCH = DN_TX * DN_TY * DN_TZ * 4;
+}
+
+// The biases of this lane's channels (see dn_store32).
+__device__ __forceinline__ void dn_bias32(const float* __restrict__ bias, float b[2][4]) {
+    const int q = (threadIdx.x & 63) >> 4;
 #pragma unroll
-    for (int k = 0; k < NCH / DN_THREADS; ++k) {
-        const int g = threadIdx.x + k * DN_THREADS;
-        const int lc = g >> 2, q = g & 3;
-        const int m = lc % DN_TX, r = lc / DN_TX, blk = r % DN_TY, pz = r / DN_TY;
-        const int cell = dn_out_cell(a, t0, pz, blk, m);
-        if (cell >= 0)
-            reinterpret_cast<uint4*>(a.act_out)[(size_t)cell * 4 + q] = *reinterpret_cast<const uint4*>(ob + dn_chunk(lc, q));
-    }
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) b[h][j] = bias[8 * q + 4 * h + j];
 }
 
 // 4-channel input (3 used), 32 output channels.  K = tap * 4 + channel
@@ -61,15 +62,16 @@ __device__ __forceinline__ void dn_store32(const DnArgs& a, const int t0[3], con
 // rounded to bf16 here); IN 1: a bf16 [cell][4] array.
 template <int IN, int EPI>
 __global__ void __launch_bounds__(DN_THREADS) k_dn_c4(DnArgs a) {
-    __shared__ __attribute__((aligned(16))) char lds[DN_HCELLS * 8 + 32 * 256 + DN_TX * DN_TY * DN_TZ * 64];
+    constexpr int WROW = 272;              // bytes of a weight row (256, padded: 16 rows in different banks)
+    __shared__ __attribute__((aligned(16))) char lds[DN_HCELLS * 8 + 32 * WROW];
     char* xin = lds;                       // [halo cell][4] bf16
-    char* wl = lds + DN_HCELLS * 8;        // [co][128] bf16, 256 B rows
-    char* ob = wl + 32 * 256;              // output tile (dn_store32)
+    char* wl = lds + DN_HCELLS * 8;        // [co][128] bf16
     int t0[3];
     dn_tile(t0);
     {
         const uint4* src = reinterpret_cast<const uint4*>(a.w);
-        for (int g = threadIdx.x; g < 32 * 16; g += DN_THREADS) reinterpret_cast<uint4*>(wl)[g] = src[g];
+        for (int g = threadIdx.x; g < 32 * 16; g += DN_THREADS)
+            *reinterpret_cast<uint4*>(wl + (g >> 4) * WROW + (g & 15) * 16) = src[g];
     }
     {
         // every global load of the thread first, then the LDS stores
@@ -101,6 +103,8 @@ __global__ void __launch_bounds__(DN_THREADS) k_dn_c4(DnArgs a) {
     __syncthreads();
     const int l = threadIdx.x & 63, lz = threadIdx.x >> 6;
     const int m = l & 15, q = l >> 4;
+    float bias[2][4] = {};
+    if (EPI == 0) dn_bias32(a.bias, bias);
     f32x4 acc[4][2];
 #pragma unroll
     for (int blk = 0; blk < 4; ++blk)
@@ -111,7 +115,7 @@ __global__ void __launch_bounds__(DN_THREADS) k_dn_c4(DnArgs a) {
         bf16x8 B[2];
 #pragma unroll
         for (int h = 0; h < 2; ++h)
-            B[h] = *reinterpret_cast<const bf16x8*>(wl + (h * 16 + m) * 256 + s * 64 + q * 16);
+            B[h] = *reinterpret_cast<const bf16x8*>(wl + dn_co(m, h) * WROW + s * 64 + q * 16);
         const int ta = 8 * s + 2 * q;
 #pragma unroll
         for (int blk = 0; blk < 4; ++blk) {
@@ -130,10 +134,10 @@ __global__ void __launch_bounds__(DN_THREADS) k_dn_c4(DnArgs a) {
             }
 #pragma unroll
             for (int h = 0; h < 2; ++h)
-                acc[blk][h] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A, B[h], acc[blk][h], 0, 0, 0);
+                acc[blk][h] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(B[h], A, acc[blk][h], 0, 0, 0);
         }
     }
-    dn_store32<EPI>(a, t0, acc, ob);
+    dn_store32<EPI>(a, t0, acc, bias);
 }
 
 // Layers with a 32-channel input: 32 -> 32 channels (KIND 0: relu(acc + b),
@@ -169,6 +173,11 @@ __global__ void __launch_bounds__(DN_THREADS) k_dn_conv32(DnArgs a) {
     int hc[DN_ACT_PER];
     dn_halo_coords(hc);
     const DnBox box = dn_box(a);
+    float bias[2][4] = {}, bias3[3] = {};
+    if (KIND == 0) dn_bias32(a.bias, bias);
+    if (KIND == 2)
+#pragma unroll
+        for (int j = 0; j < 3; ++j) bias3[j] = a.bias[j];
     uint4 v[DN_ACT_PER];
     if (tile < end) {
         dn_tile_of(tile, ntx, nty, t0);
@@ -187,20 +196,12 @@ __global__ void __launch_bounds__(DN_THREADS) k_dn_conv32(DnArgs a) {
         if constexpr (KIND == 2) {
             f32x4 acc = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
             dn_mma3(act, wl, acc);
+            // lane (m, q): channels j = 0..2 of cell m of row block q
             const int l = threadIdx.x & 63, lz = threadIdx.x >> 6;
-            const int col = l & 15, rq = l >> 4;
-            const int blk = col >> 2, co = col & 3;
-            if (co < 3) {
-                // pick the component's pointer among the three (indexing the
-                // argument array with a lane value would re-read it from memory)
-                float* out = co == 0 ? a.Jout[0] : (co == 1 ? a.Jout[1] : a.Jout[2]);
-                const float b = a.bias[co];
+            const int cell = dn_out_cell(a, cur, lz, l >> 4, l & 15);
+            if (cell >= 0)
 #pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    const int cell = dn_out_cell(a, cur, lz, blk, rq * 4 + j);
-                    if (cell >= 0) out[cell] = acc[j] + b;
-                }
-            }
+                for (int j = 0; j < 3; ++j) a.Jout[j][cell] = acc[j] + bias3[j];
         } else {
             f32x4 acc[4][NH];
 #pragma unroll
@@ -208,8 +209,7 @@ __global__ void __launch_bounds__(DN_THREADS) k_dn_conv32(DnArgs a) {
 #pragma unroll
                 for (int h = 0; h < NH; ++h) acc[blk][h] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
             dn_mma32<NH>(act, wl, acc);
-            __syncthreads();   // every wavefront is done reading the halo: reuse it for the output tile
-            dn_store32<KIND>(a, cur, acc, act);
+            dn_store32<KIND>(a, cur, acc, bias);
         }
         tile = next;
     }

@@ -20,10 +20,12 @@
 // blocks of 16 output channels, accumulated over the 27 taps x 32 input
 // channels (one MFMA K-step of 32 per tap).
 //
-// MFMA operand layout (16x16x32): lane l holds A row l%16, K elements
-// 8(l/16)..8(l/16)+7; B column l%16 with the same K elements; the result
-// holds column l%16, rows 4(l/16)..4(l/16)+3.  A row = a cell, K = input
-// channels, B column = an output channel.
+// MFMA operand layout (16x16x32): lane l holds row l%16 of the first operand,
+// K elements 8(l/16)..8(l/16)+7, and column l%16 of the second with the same K
+// elements; the result holds column l%16, rows 4(l/16)..4(l/16)+3.  Rows =
+// output channels (the weights), K = input channels, columns = cells, so that
+// a lane's results are neighbouring channels of one cell.  (A and B below
+// name the cells' and the weights' fragments.)
 //
 // Weight rows of 64 B are stored in LDS as four 16-byte chunks rotated by
 // rot(r) = ((r >> 1) ^ (r >> 2)) & 3, so that the consecutive rows one B read
@@ -249,6 +251,10 @@ __device__ __forceinline__ int dn_out_cell(const DnArgs& a, const int t0[3], int
     return xs + a.n[0] * (y + a.n[1] * z);
 }
 
+// Output channel of weight operand row r (0..15) of half h: the four rows of
+// lane group q (4 q ..) of both halves together are channels 8 q .. 8 q + 7.
+__device__ __forceinline__ int dn_co(int r, int h) { return 8 * (r >> 2) + 4 * h + (r & 3); }
+
 // Accumulate the 27 taps x 32 input channels of a 32-channel layer.  Per tap
 // column (dz, dx) the wavefront reads the 6 halo rows its 4 output rows need
 // once and reuses each for the three dy taps (row blk + dy): 6 A reads per 12
@@ -259,7 +265,10 @@ __device__ __forceinline__ void dn_mma32(const char* act, const char* wl, f32x4 
     const int l = threadIdx.x & 63, lz = threadIdx.x >> 6;
     const int m = l & 15, q = l >> 4;
     const char* abase = act + (lz * DN_HY * DN_HX + m) * DN_ROWB + q * 16;
-    const char* bbase = wl + dn_chunk(m, q);
+    // (the 16 rows dn_co(m, h) of a tap also spread over all banks)
+    const char* bbase[NH];
+#pragma unroll
+    for (int h = 0; h < NH; ++h) bbase[h] = wl + dn_chunk(dn_co(m, h), q);
 #pragma unroll
     for (int zx = 0; zx < 9; ++zx) {
         const int dz = zx / 3, dx = zx % 3;   // 0..2 = offset + 1
@@ -273,23 +282,23 @@ __device__ __forceinline__ void dn_mma32(const char* act, const char* wl, f32x4 
             bf16x8 B[NH];
 #pragma unroll
             for (int h = 0; h < NH; ++h)
-                B[h] = *reinterpret_cast<const bf16x8*>(bbase + (tap * NH + h) * 1024);
+                B[h] = *reinterpret_cast<const bf16x8*>(bbase[h] + tap * NH * 1024);
 #pragma unroll
             for (int blk = 0; blk < 4; ++blk)
 #pragma unroll
                 for (int h = 0; h < NH; ++h)
-                    acc[blk][h] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A[blk + dy], B[h], acc[blk][h], 0, 0, 0);
+                    acc[blk][h] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(B[h], A[blk + dy], acc[blk][h], 0, 0, 0);
         }
     }
 }
 
-// The 32 -> 3 layer with the output rows folded into the matrix columns:
-// column 4 blk + c (c < 3; c = 3 is zero) of one MFMA holds output channel c
+// The 32 -> 3 layer with the output rows folded into the weight rows:
+// row 4 blk + c (c < 3; c = 3 is zero) of one MFMA holds output channel c
 // of row block blk, so the halo row r (0..5) of a tap column (dz, dx) is one
-// A fragment multiplied by one B fragment whose column (blk, c) carries the
+// A fragment multiplied by one B fragment whose row (blk, c) carries the
 // weight of tap (dz, r - blk, dx) when 0 <= r - blk <= 2 (else zero):
 // 6 MFMAs per tap column instead of 12 (4 row blocks x 3 dy taps), 12 of the
-// 16 columns useful instead of 3.  B fragment (zx, r) is rows
+// 16 rows useful instead of 3.  B fragment (zx, r) is rows
 // 16 (6 zx + r) .. + 15 of the packed weights.
 __device__ __forceinline__ void dn_mma3(const char* act, const char* wl, f32x4& acc) {
     const int l = threadIdx.x & 63, lz = threadIdx.x >> 6;
@@ -303,7 +312,7 @@ __device__ __forceinline__ void dn_mma3(const char* act, const char* wl, f32x4& 
         for (int r = 0; r < DN_HY; ++r) {
             const bf16x8 A = *reinterpret_cast<const bf16x8*>(abase + ((dz * DN_HY + r) * DN_HX + dx) * DN_ROWB);
             const bf16x8 B = *reinterpret_cast<const bf16x8*>(bbase + (zx * DN_HY + r) * 1024);
-            acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A, B, acc, 0, 0, 0);
+            acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(B, A, acc, 0, 0, 0);
         }
     }
 }
