@@ -140,21 +140,18 @@ __global__ void __launch_bounds__(DN_THREADS) k_dn_c4(DnArgs a) {
     dn_store32<EPI>(a, t0, acc, bias);
 }
 
-// Layers with a 32-channel input: 32 -> 32 channels (KIND 0: relu(acc + b),
-// 1: mask epilogue) or 32 -> 3 (KIND 2, the row blocks folded into the
-// matrix columns, dn_mma3: y = acc + b as FP32 components into a.Jout).  Persistent: one workgroup per compute unit stages
-// the weights once and walks the tiles t = blockIdx.x, + gridDim.x, ...; the
-// next tile's input halo is loaded into registers while the current tile's
-// matrix work runs.
+// Layers with a 32-channel input and output (KIND 0: relu(acc + b), 1: mask
+// epilogue).  Persistent: one workgroup per compute unit stages the weights
+// once and walks its tiles; the next tile's input halo is loaded into
+// registers while the current tile's matrix work runs.
 template <int KIND>
 __global__ void __launch_bounds__(DN_THREADS) k_dn_conv32(DnArgs a) {
-    constexpr int NH = KIND == 2 ? 1 : 2;
     extern __shared__ __attribute__((aligned(16))) char dlds[];
     char* act = dlds;
     char* wl = dlds + DN_ACT_LDS;
     int ntx, nty;
     const int ntiles = dn_ntiles(a.n, &ntx, &nty);
-    dn_stage_weights<KIND == 2 ? 9 * DN_HY * 16 : 27 * 16 * NH>(a.w, wl);
+    dn_stage_weights<27 * 32>(a.w, wl);
     // XCD-aware walk (workgroups go round-robin over the 8 XCDs): the
     // workgroups of one XCD share a contiguous range of tiles and walk it
     // together, so the halos they share stay in that XCD's L2
@@ -173,11 +170,8 @@ __global__ void __launch_bounds__(DN_THREADS) k_dn_conv32(DnArgs a) {
     int hc[DN_ACT_PER];
     dn_halo_coords(hc);
     const DnBox box = dn_box(a);
-    float bias[2][4] = {}, bias3[3] = {};
+    float bias[2][4] = {};
     if (KIND == 0) dn_bias32(a.bias, bias);
-    if (KIND == 2)
-#pragma unroll
-        for (int j = 0; j < 3; ++j) bias3[j] = a.bias[j];
     uint4 v[DN_ACT_PER];
     if (tile < end) {
         dn_tile_of(tile, ntx, nty, t0);
@@ -193,25 +187,122 @@ __global__ void __launch_bounds__(DN_THREADS) k_dn_conv32(DnArgs a) {
             dn_tile_of(next, ntx, nty, t0);
             dn_load_act(a.act_in, box, t0, hc, v);
         }
-        if constexpr (KIND == 2) {
-            f32x4 acc = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-            dn_mma3(act, wl, acc);
-            // lane (m, q): channels j = 0..2 of cell m of row block q
-            const int l = threadIdx.x & 63, lz = threadIdx.x >> 6;
-            const int cell = dn_out_cell(a, cur, lz, l >> 4, l & 15);
-            if (cell >= 0)
+        f32x4 acc[4][2];
 #pragma unroll
-                for (int j = 0; j < 3; ++j) a.Jout[j][cell] = acc[j] + bias3[j];
-        } else {
-            f32x4 acc[4][NH];
+        for (int blk = 0; blk < 4; ++blk)
 #pragma unroll
-            for (int blk = 0; blk < 4; ++blk)
-#pragma unroll
-                for (int h = 0; h < NH; ++h) acc[blk][h] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-            dn_mma32<NH>(act, wl, acc);
-            dn_store32<KIND>(a, cur, acc, bias);
-        }
+            for (int h = 0; h < 2; ++h) acc[blk][h] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+        dn_mma32<2>(act, wl, acc);
+        dn_store32<KIND>(a, cur, acc, bias);
         tile = next;
+    }
+}
+
+// The 32 -> 3 layer, y = conv(a2, W3) + b3 as FP32 components into a.Jout.
+// A row of 16 cells x 32 channels is 1 KB of HBM in exactly the order of an
+// MFMA's second operand, so no LDS is needed: a wavefront takes 16 columns
+// and 4 rows and marches along z, each input plane's 6 rows loaded once into
+// registers, two planes ahead.  The first operand holds the weights of one
+// (dz, dy): row 4 dx + c for x-tap dx and channel c, 9 operands in registers
+// for the whole march.  The x-taps' partial sums lie in three lane groups,
+// one column apart, and are added with two lane exchanges per value at the
+// end: 14 of the 16 columns are outputs.  Bound by the loads (64 B read, 12
+// written per cell, halos included 1.9 times that from L2).  On 384x192x160
+// cells this takes 266 us; 16x4x8 tiles in LDS, every row read once per x-tap
+// and the weights by every wavefront, took 588, and a single plane ahead,
+// moved between buffers, 371 (the moves wait for the loads).
+constexpr int L3_X = 14, L3_Y = 4, L3_WAVES = 4;
+
+__global__ void __launch_bounds__(64 * L3_WAVES, 2) k_dn_l3(DnArgs a, int tx, int ty, int zrun) {
+    const int l = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int m = l & 15, q = l >> 4;
+    // workgroups of an XCD in contiguous runs (x fastest), so that halos meet in its L2
+    const int nb = gridDim.x, k8 = blockIdx.x % 8, per = nb / 8, rem = nb % 8;
+    const int t = k8 * per + min(k8, rem) + blockIdx.x / 8;
+    const int x0 = (t % tx) * L3_X, y0 = ((t / tx) % ty * L3_WAVES + w) * L3_Y, z0 = (t / (tx * ty)) * zrun;
+    if (y0 >= a.n[1]) return;
+    const int z1 = min(z0 + zrun, a.n[2]);
+    bf16x8 W[9];
+#pragma unroll
+    for (int k = 0; k < 9; ++k) W[k] = reinterpret_cast<const bf16x8*>(a.w)[(k * 16 + m) * 4 + q];
+    const float b[3] = {a.bias[0], a.bias[1], a.bias[2]};
+    // column m is window cell x0 - 1 + m (past the right edge of the box: not needed)
+    const int xw = x0 - 1 + m;
+    const int xs = xw <= a.n[0] ? dn_axis_sel(xw, a.n[0], a.bc[0], a.origin) : -1;
+    // a column outside the box loads some cell of its row; its partial sums are dropped below
+    const unsigned lane = (unsigned)(xs >= 0 ? xs : min(m, a.n[0] - 1)) * 64u + (unsigned)q * 16u;
+    const bool ok0 = __shfl(xs, (m + 15) & 15, 64) >= 0, ok2 = __shfl(xs, (m + 1) & 15, 64) >= 0;
+    int row[L3_Y + 2];   // storage row of y0 - 1 + r, or -1
+#pragma unroll
+    for (int r = 0; r < L3_Y + 2; ++r) {
+        const int y = y0 - 1 + r;
+        row[r] = y <= a.n[1] ? dn_axis_sel(y, a.n[1], a.bc[1], 0) : -1;
+    }
+    auto load = [&](int z, bf16x8 (&P)[L3_Y + 2]) {
+        const int zs = dn_axis_sel(z, a.n[2], a.bc[2], 0);
+#pragma unroll
+        for (int r = 0; r < L3_Y + 2; ++r) {
+            const char* p = reinterpret_cast<const char*>(a.act_in) +
+                            (size_t)a.n[0] * 64 * ((size_t)max(row[r], 0) + (size_t)a.n[1] * max(zs, 0));
+            P[r] = *reinterpret_cast<const bf16x8*>(p + lane);
+        }
+        if (zs < 0 || row[0] < 0 || row[L3_Y + 1] < 0) {   // a row outside an open box
+#pragma unroll
+            for (int r = 0; r < L3_Y + 2; ++r)
+                if (zs < 0 || row[r] < 0) P[r] = __builtin_bit_cast(bf16x8, make_uint4(0u, 0u, 0u, 0u));
+        }
+    };
+    const int from0 = ((m + 15) & 15) << 2, from2 = (32 + ((m + 1) & 15)) << 2;   // lanes of dx = 0, 2
+    const bool mine = q == 1 && m >= 1 && m <= L3_X && xw < a.n[0];
+    using Plane = bf16x8[L3_Y + 2];
+    // plane z of the output from the input planes z - 1 .. z + 1, with the load of z + 3 started first
+    auto plane = [&](int z, const Plane& A, const Plane& B, const Plane& C, Plane& N) {
+        if (z + 2 < z1) load(z + 3, N);
+        f32x4 acc[L3_Y];
+#pragma unroll
+        for (int r = 0; r < L3_Y; ++r) acc[r] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+        for (int dz = 0; dz < 3; ++dz)
+#pragma unroll
+            for (int dy = 0; dy < 3; ++dy)
+#pragma unroll
+                for (int r = 0; r < L3_Y; ++r)
+                    acc[r] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                        W[dz * 3 + dy], dz == 0 ? A[r + dy] : (dz == 1 ? B[r + dy] : C[r + dy]), acc[r], 0, 0, 0);
+#pragma unroll
+        for (int r = 0; r < L3_Y; ++r) {
+            float o[3];
+#pragma unroll
+            for (int j = 0; j < 3; ++j) {
+                const float v0 = __int_as_float(__builtin_amdgcn_ds_bpermute(from0, __float_as_int(acc[r][j])));
+                const float v2 = __int_as_float(__builtin_amdgcn_ds_bpermute(from2, __float_as_int(acc[r][j])));
+                o[j] = (((ok0 ? v0 : 0.0f) + acc[r][j]) + (ok2 ? v2 : 0.0f)) + b[j];
+            }
+            if (y0 + r < a.n[1]) {
+                const size_t c0 = (size_t)a.n[0] * (row[r + 1] + (size_t)a.n[1] * z);
+                if (mine)
+#pragma unroll
+                    for (int j = 0; j < 3; ++j) (a.Jout[j] + c0)[(unsigned)xs] = o[j];
+            }
+        }
+    };
+    Plane P0, P1, P2, P3, P4;
+    load(z0 - 1, P0);
+    load(z0, P1);
+    load(z0 + 1, P2);
+    if (z0 + 1 < z1) load(z0 + 2, P3);
+    // five buffers take turns (no register moves): two planes' loads stay in flight
+    for (int z = z0;; ++z) {
+        plane(z, P0, P1, P2, P4);
+        if (++z >= z1) return;
+        plane(z, P1, P2, P3, P0);
+        if (++z >= z1) return;
+        plane(z, P2, P3, P4, P1);
+        if (++z >= z1) return;
+        plane(z, P3, P4, P0, P2);
+        if (++z >= z1) return;
+        plane(z, P4, P0, P1, P3);
+        if (z + 1 >= z1) return;
     }
 }
 
@@ -451,7 +542,17 @@ hipError_t launch_dn_layer(int kind, const DnArgs& a, hipStream_t st) {
         case DN_L1_C4_MASK: return dn_launch(k_dn_c4<1, 1>, 0, a, st);
         case DN_L2_ACT: return dn_launch_persistent(k_dn_conv32<0>, dn_lds(27 * 32), a, st);
         case DN_L2_MASK: return dn_launch_persistent(k_dn_conv32<1>, dn_lds(27 * 32), a, st);
-        case DN_L3_Y: return dn_launch_persistent(k_dn_conv32<2>, dn_lds(9 * DN_HY * 16), a, st);
+        case DN_L3_Y: {
+            const int tx = (a.n[0] + L3_X - 1) / L3_X, ty = (a.n[1] + L3_Y * L3_WAVES - 1) / (L3_Y * L3_WAVES);
+            // planes per wavefront: 16 (2 halo planes loaded), fewer where that leaves the chip with less
+            // than two workgroups per compute unit.  384x192x160 cells: 266 us with 16, 301 with 8;
+            // 128x64x64 cells: 27 with 16 (160 workgroups), 20 with 8 or 4.
+            int zrun = 16;
+            while (zrun > 4 && (long long)tx * ty * ((a.n[2] + zrun - 1) / zrun) < 512) zrun /= 2;
+            const int tz = (a.n[2] + zrun - 1) / zrun;
+            hipLaunchKernelGGL(k_dn_l3, dim3((unsigned)(tx * ty * tz)), dim3(64 * L3_WAVES), 0, st, a, tx, ty, zrun);
+            return hipGetLastError();
+        }
         default: return hipErrorInvalidValue;
     }
 }

@@ -6,19 +6,20 @@
 //   x  = bf16(J_d / s_d)                    layer 1: 3 (padded to 4) -> 32 channels
 //   a1 = bf16(relu(conv(x, W1) + b1))
 //   a2 = bf16(relu(conv(a1, W2) + b2))      layer 2: 32 -> 32 (84 % of the work)
-//   J'_d = J_d + s_d (conv(a2, W3) + b3)_d  layer 3: 32 -> 3 (4 row blocks x 4 columns)
+//   J'_d = J_d + s_d (conv(a2, W3) + b3)_d  layer 3: 32 -> 3 (3 x-taps x 4 weight rows)
 //
 // conv is the "same"-size 3x3x3 cross-correlation; y and z are periodic, x is
 // periodic or (moving window) zero beyond the window's two ends, or zero
 // outside the box on any axis (training crops).  Activations live in HBM
 // channels-last as bf16 [cell][32] (64 B per cell).
 //
-// One workgroup of 8 wavefronts computes a tile of 16 x 4 x 8 cells (x, y, z)
-// in window coordinates: it stages the tile's input halo (18 x 6 x 10 cells,
+// Layers 1 and 2: one workgroup of 8 wavefronts computes a tile of 16 x 4 x 8
+// cells (x, y, z) in window coordinates: it stages the tile's input halo (18 x 6 x 10 cells,
 // rows padded to 20) and the layer's weights in LDS, then each wavefront
 // takes one z-plane: 4 rows of 16 cells = 4 MFMA row blocks, times 2 (or 1)
 // blocks of 16 output channels, accumulated over the 27 taps x 32 input
-// channels (one MFMA K-step of 32 per tap).
+// channels (one MFMA K-step of 32 per tap).  Layer 3 streams its input from
+// HBM straight into the MFMA operands (k_dn_l3).
 //
 // MFMA operand layout (16x16x32): lane l holds row l%16 of the first operand,
 // K elements 8(l/16)..8(l/16)+7, and column l%16 of the second with the same K
@@ -288,31 +289,6 @@ __device__ __forceinline__ void dn_mma32(const char* act, const char* wl, f32x4 
 #pragma unroll
                 for (int h = 0; h < NH; ++h)
                     acc[blk][h] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(B[h], A[blk + dy], acc[blk][h], 0, 0, 0);
-        }
-    }
-}
-
-// The 32 -> 3 layer with the output rows folded into the weight rows:
-// row 4 blk + c (c < 3; c = 3 is zero) of one MFMA holds output channel c
-// of row block blk, so the halo row r (0..5) of a tap column (dz, dx) is one
-// A fragment multiplied by one B fragment whose row (blk, c) carries the
-// weight of tap (dz, r - blk, dx) when 0 <= r - blk <= 2 (else zero):
-// 6 MFMAs per tap column instead of 12 (4 row blocks x 3 dy taps), 12 of the
-// 16 rows useful instead of 3.  B fragment (zx, r) is rows
-// 16 (6 zx + r) .. + 15 of the packed weights.
-__device__ __forceinline__ void dn_mma3(const char* act, const char* wl, f32x4& acc) {
-    const int l = threadIdx.x & 63, lz = threadIdx.x >> 6;
-    const int m = l & 15, q = l >> 4;
-    const char* abase = act + (lz * DN_HY * DN_HX + m) * DN_ROWB + q * 16;
-    const char* bbase = wl + dn_chunk(m, q);
-#pragma unroll
-    for (int zx = 0; zx < 9; ++zx) {
-        const int dz = zx / 3, dx = zx % 3;
-#pragma unroll
-        for (int r = 0; r < DN_HY; ++r) {
-            const bf16x8 A = *reinterpret_cast<const bf16x8*>(abase + ((dz * DN_HY + r) * DN_HX + dx) * DN_ROWB);
-            const bf16x8 B = *reinterpret_cast<const bf16x8*>(bbase + (zx * DN_HY + r) * 1024);
-            acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(B, A, acc, 0, 0, 0);
         }
     }
 }

@@ -153,7 +153,7 @@ hipError_t launch_batch_inject(const InstDesc* d, int n, long long max_cand, hip
 // Learned current denoiser (pic_denoise.hip): J' = B(J + sigma curl(net(J / s))).
 // Packed bf16 weights:
 // w1 [32 out][128] with k = tap * 4 + in (in < 3, tap < 27, else zero);
-// w2 [27 tap][32 out][32 in]; w3 [27 tap][16 out][32 in] (out < 3, else zero);
+// w2 [27 tap][32 out][32 in]; w3 [9 (dz, dy)][16: 4 dx + out][32 in] (out < 3, dx < 3, else zero);
 // tap = 9 (dz + 1) + 3 (dy + 1) + (dx + 1).  Biases FP32: b1[32], b2[32], b3[16].
 struct DenoiseWeights {
     const __bf16* w1;
@@ -166,8 +166,8 @@ struct DenoiseWeights {
     float sigma;      // output stage J' = B(J + sigma curl(y)), sigma = dx (s_x + s_y + s_z) / 3
     float inv_d[3];
 };
-// bf16 elements; W3: 9 tap columns x 6 halo rows x 16 columns (4 row blocks x 4) x 32
-constexpr size_t kDnW1 = 32 * 128, kDnW2 = 27 * 32 * 32, kDnW3 = 9 * 6 * 16 * 32;
+// bf16 elements
+constexpr size_t kDnW1 = 32 * 128, kDnW2 = 27 * 32 * 32, kDnW3 = 9 * 16 * 32;
 constexpr size_t kDnBias = 32 + 32 + 16;                                            // floats
 
 // bc per axis: 0 periodic, 1 zero outside the box, 2 moving window (zero
