@@ -17,9 +17,8 @@ namespace pic {
 // cell m of each row block: 16 consecutive bytes of one cell, stored straight
 // from the registers, four lanes to a cell's 64 bytes (the mask is read the
 // same way).  Staging the output tile through LDS instead, with its two
-// barriers and 32 two-byte stores per lane, took
-// 773 us for layer 2 and 336 for layer 1 on 384x192x160 cells; this takes 746
-// and 307.
+// barriers and 32 two-byte stores per lane, took 336 us for layer 1 on
+// 384x192x160 cells; this takes 307.
 template <int EPI>
 __device__ __forceinline__ void dn_store32(const DnArgs& a, const int t0[3], const f32x4 acc[4][2],
                                            const float bias[2][4]) {
@@ -141,17 +140,26 @@ __global__ void __launch_bounds__(DN_THREADS) k_dn_c4(DnArgs a) {
 }
 
 // Layers with a 32-channel input and output (KIND 0: relu(acc + b), 1: mask
-// epilogue).  Persistent: one workgroup per compute unit stages the weights
-// once and walks its tiles; the next tile's input halo is loaded into
-// registers while the current tile's matrix work runs.
+// epilogue).  Persistent: one workgroup per compute unit walks its tiles; the
+// next tile's input halo is loaded into registers while the current tile's
+// matrix work runs.  A wavefront takes 16 of the output channels and two
+// planes, with its weights (27 operands) in registers for the whole walk: 72
+// LDS reads for 216 matrix instructions, where one plane, 32 channels and the
+// weights in LDS took 108.  384x192x160 cells: 746 -> 663 us (980 TFLOP/s,
+// the clock falling to 1.7 GHz under the matrix load; a large matrix product
+// reaches 1184), of which half is the halo's addresses (DnLane, and planes
+// inside the box by addition) and the order of stores and waits.
 template <int KIND>
 __global__ void __launch_bounds__(DN_THREADS) k_dn_conv32(DnArgs a) {
-    extern __shared__ __attribute__((aligned(16))) char dlds[];
-    char* act = dlds;
-    char* wl = dlds + DN_ACT_LDS;
+    extern __shared__ __attribute__((aligned(16))) char act[];
+    const int m = threadIdx.x & 15, q = (threadIdx.x & 63) >> 4;
+    const int h = (__builtin_amdgcn_readfirstlane(threadIdx.x) >> 6) & 1;
+    const int lz = (__builtin_amdgcn_readfirstlane(threadIdx.x) >> 7) * 2;
     int ntx, nty;
     const int ntiles = dn_ntiles(a.n, &ntx, &nty);
-    dn_stage_weights<27 * 32>(a.w, wl);
+    bf16x8 W[27];
+#pragma unroll
+    for (int t = 0; t < 27; ++t) W[t] = reinterpret_cast<const bf16x8*>(a.w)[(t * 32 + 16 * h + m) * 4 + q];
     // XCD-aware walk (workgroups go round-robin over the 8 XCDs): the
     // workgroups of one XCD share a contiguous range of tiles and walk it
     // together, so the halos they share stay in that XCD's L2
@@ -167,34 +175,71 @@ __global__ void __launch_bounds__(DN_THREADS) k_dn_conv32(DnArgs a) {
         end = ntiles;
     }
     int t0[3];
-    int hc[DN_ACT_PER];
-    dn_halo_coords(hc);
+    const DnLane lane = dn_lane();
     const DnBox box = dn_box(a);
-    float bias[2][4] = {};
-    if (KIND == 0) dn_bias32(a.bias, bias);
+    float bias[4] = {};
+    if (KIND == 0)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) bias[j] = a.bias[16 * h + 4 * q + j];
     uint4 v[DN_ACT_PER];
-    if (tile < end) {
-        dn_tile_of(tile, ntx, nty, t0);
-        dn_load_act(a.act_in, box, t0, hc, v);
-    }
-    while (tile < end) {
+    bf16x4 mk[2][4] = {};
+    f32x4 acc[2][4];
+    int cur[3] = {0, 0, 0};
+    // f(p, r, byte offset of the row, of the lane's 4 channels in it) for the tile's output rows (p, r) inside the box
+    const size_t rstep = (size_t)a.n[0] * 64, pstep = rstep * a.n[1];
+    auto rows = [&](auto&& f) {
+        const int x = cur[0] + m;
+        if (x >= a.n[0]) return;
+        const unsigned at = (unsigned)dn_axis_sel(x, a.n[0], a.bc[0], a.origin) * 64u + (unsigned)(4 * h + q) * 8u;
+        const size_t base = rstep * cur[1] + pstep * (cur[2] + lz);
+#pragma unroll
+        for (int p = 0; p < 2; ++p)
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+                if (cur[1] + r < a.n[1] && cur[2] + lz + p < a.n[2]) f(p, r, base + r * rstep + p * pstep, at);
+    };
+    bool have = false;
+    unsigned out = 0;
+    if (tile >= end) return;
+    dn_tile_of(tile, ntx, nty, t0);
+    out = dn_load_act(a.act_in, box, t0, lane, v);
+    // The last tile's outputs are stored after the next halo has been taken
+    // from the registers: the wait for the loads would wait for stores issued
+    // in between as well (one counter).  After the last tile v holds nothing
+    // new, and the halo stored is not read.
+    for (;;) {
         __syncthreads();   // the previous tile's LDS reads are done (first pass: nothing)
-        dn_store_act(v, act);
-        __syncthreads();   // halo (and, first pass, weights) staged
-        const int cur[3] = {t0[0], t0[1], t0[2]};
-        const int next = tile + stride;
-        if (next < end) {
-            dn_tile_of(next, ntx, nty, t0);
-            dn_load_act(a.act_in, box, t0, hc, v);
+        dn_zero_planes(v, out);
+        dn_store_act(v, lane, act);
+        if (have) {
+            rows([&](int p, int r, size_t row, unsigned at) {
+                bf16x4 o;
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+                    o[j] = KIND == 0 ? (__bf16)fmaxf(acc[p][r][j] + bias[j], 0.0f)
+                                     : ((float)mk[p][r][j] > 0.0f ? (__bf16)acc[p][r][j] : (__bf16)0.0f);
+                *reinterpret_cast<bf16x4*>(reinterpret_cast<char*>(a.act_out) + row + at) = o;
+            });
         }
-        f32x4 acc[4][2];
+        if (tile >= end) return;
+        __syncthreads();   // halo staged
 #pragma unroll
-        for (int blk = 0; blk < 4; ++blk)
+        for (int d = 0; d < 3; ++d) cur[d] = t0[d];
+        if (KIND == 1)
+            rows([&](int p, int r, size_t row, unsigned at) {
+                mk[p][r] = *reinterpret_cast<const bf16x4*>(reinterpret_cast<const char*>(a.mask) + row + at);
+            });
+        tile += stride;
+        if (tile < end) {
+            dn_tile_of(tile, ntx, nty, t0);
+            out = dn_load_act(a.act_in, box, t0, lane, v);
+        }
 #pragma unroll
-            for (int h = 0; h < 2; ++h) acc[blk][h] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-        dn_mma32<2>(act, wl, acc);
-        dn_store32<KIND>(a, cur, acc, bias);
-        tile = next;
+        for (int p = 0; p < 2; ++p)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) acc[p][r] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+        dn_mma32(act, W, acc);
+        have = true;
     }
 }
 
@@ -213,13 +258,11 @@ __global__ void __launch_bounds__(DN_THREADS) k_dn_conv32(DnArgs a) {
 // moved between buffers, 371 (the moves wait for the loads).
 constexpr int L3_X = 14, L3_Y = 4, L3_WAVES = 4;
 
-__global__ void __launch_bounds__(64 * L3_WAVES, 2) k_dn_l3(DnArgs a, int tx, int ty, int zrun) {
+__global__ void __launch_bounds__(64 * L3_WAVES, 2) k_dn_l3(DnArgs a, int zrun) {
     const int l = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int m = l & 15, q = l >> 4;
-    // workgroups of an XCD in contiguous runs (x fastest), so that halos meet in its L2
-    const int nb = gridDim.x, k8 = blockIdx.x % 8, per = nb / 8, rem = nb % 8;
-    const int t = k8 * per + min(k8, rem) + blockIdx.x / 8;
-    const int x0 = (t % tx) * L3_X, y0 = ((t / tx) % ty * L3_WAVES + w) * L3_Y, z0 = (t / (tx * ty)) * zrun;
+    const int3 t = dn_walk();
+    const int x0 = t.x * L3_X, y0 = (t.y * L3_WAVES + w) * L3_Y, z0 = t.z * zrun;
     if (y0 >= a.n[1]) return;
     const int z1 = min(z0 + zrun, a.n[2]);
     bf16x8 W[9];
@@ -352,7 +395,8 @@ template <bool LOSS>
 __global__ void __launch_bounds__(DO_THREADS) k_dn_output(DnCombine c) {
     __shared__ float ys[3][DO_YZ * DO_YY * DO_YX];
     __shared__ float ts[3][DO_SZ * DO_SY * DO_SX];
-    const int t0[3] = {(int)blockIdx.x * DO_TX, (int)blockIdx.y * DO_TY, (int)blockIdx.z * DO_TZ};
+    const int3 tile = dn_walk();
+    const int t0[3] = {tile.x * DO_TX, tile.y * DO_TY, tile.z * DO_TZ};
     // Every global load of a thread is issued before the first of them is
     // used (the y halo, then the current at the t cells, the latter in flight
     // while the y halo is stored), so each staging pass waits for one memory
@@ -448,7 +492,8 @@ constexpr int DA_BX = DO_TX + 1, DA_BY = DO_TY + 1, DA_BZ = DO_TZ + 1;   // b: c
 __global__ void __launch_bounds__(DO_THREADS) k_dn_output_adjoint(DnCombine c) {
     __shared__ float gs[3][DA_GZ * DA_GY * DA_GX];
     __shared__ float bs[3][DA_BZ * DA_BY * DA_BX];
-    const int t0[3] = {(int)blockIdx.x * DO_TX, (int)blockIdx.y * DO_TY, (int)blockIdx.z * DO_TZ};
+    const int3 tile = dn_walk();
+    const int t0[3] = {tile.x * DO_TX, tile.y * DO_TY, tile.z * DO_TZ};
     constexpr int NG = DA_GZ * DA_GY * DA_GX, PG = (NG + DO_THREADS - 1) / DO_THREADS;
     constexpr int NB = DA_BZ * DA_BY * DA_BX;
     float v[PG][3];
@@ -505,15 +550,9 @@ hipError_t launch_dn_output_adjoint(const DnCombine& c, hipStream_t st) {
     return hipGetLastError();
 }
 
-static size_t dn_lds(int weight_rows) { return (size_t)DN_ACT_LDS + (size_t)weight_rows * 64; }
-
 template <class K>
-static hipError_t dn_launch(K kern, size_t lds, const DnArgs& a, hipStream_t st) {
-    if (lds > 0) {
-        hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-        if (e != hipSuccess) return e;
-    }
-    hipLaunchKernelGGL(kern, dn_grid(a.n), dim3(DN_THREADS), lds, st, a);
+static hipError_t dn_launch(K kern, const DnArgs& a, hipStream_t st) {
+    hipLaunchKernelGGL(kern, dn_grid(a.n), dim3(DN_THREADS), 0, st, a);
     return hipGetLastError();
 }
 
@@ -538,10 +577,10 @@ static hipError_t dn_launch_persistent(K kern, size_t lds, const DnArgs& a, hipS
 
 hipError_t launch_dn_layer(int kind, const DnArgs& a, hipStream_t st) {
     switch (kind) {
-        case DN_L1_J_ACT: return dn_launch(k_dn_c4<0, 0>, 0, a, st);
-        case DN_L1_C4_MASK: return dn_launch(k_dn_c4<1, 1>, 0, a, st);
-        case DN_L2_ACT: return dn_launch_persistent(k_dn_conv32<0>, dn_lds(27 * 32), a, st);
-        case DN_L2_MASK: return dn_launch_persistent(k_dn_conv32<1>, dn_lds(27 * 32), a, st);
+        case DN_L1_J_ACT: return dn_launch(k_dn_c4<0, 0>, a, st);
+        case DN_L1_C4_MASK: return dn_launch(k_dn_c4<1, 1>, a, st);
+        case DN_L2_ACT: return dn_launch_persistent(k_dn_conv32<0>, DN_ACT_LDS, a, st);
+        case DN_L2_MASK: return dn_launch_persistent(k_dn_conv32<1>, DN_ACT_LDS, a, st);
         case DN_L3_Y: {
             const int tx = (a.n[0] + L3_X - 1) / L3_X, ty = (a.n[1] + L3_Y * L3_WAVES - 1) / (L3_Y * L3_WAVES);
             // planes per wavefront: 16 (2 halo planes loaded), fewer where that leaves the chip with less
@@ -550,7 +589,7 @@ hipError_t launch_dn_layer(int kind, const DnArgs& a, hipStream_t st) {
             int zrun = 16;
             while (zrun > 4 && (long long)tx * ty * ((a.n[2] + zrun - 1) / zrun) < 512) zrun /= 2;
             const int tz = (a.n[2] + zrun - 1) / zrun;
-            hipLaunchKernelGGL(k_dn_l3, dim3((unsigned)(tx * ty * tz)), dim3(64 * L3_WAVES), 0, st, a, tx, ty, zrun);
+            hipLaunchKernelGGL(k_dn_l3, dim3(tx, ty, tz), dim3(64 * L3_WAVES), 0, st, a, zrun);
             return hipGetLastError();
         }
         default: return hipErrorInvalidValue;

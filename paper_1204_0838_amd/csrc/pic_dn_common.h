@@ -14,12 +14,12 @@
 // channels-last as bf16 [cell][32] (64 B per cell).
 //
 // Layers 1 and 2: one workgroup of 8 wavefronts computes a tile of 16 x 4 x 8
-// cells (x, y, z) in window coordinates: it stages the tile's input halo (18 x 6 x 10 cells,
-// rows padded to 20) and the layer's weights in LDS, then each wavefront
-// takes one z-plane: 4 rows of 16 cells = 4 MFMA row blocks, times 2 (or 1)
-// blocks of 16 output channels, accumulated over the 27 taps x 32 input
-// channels (one MFMA K-step of 32 per tap).  Layer 3 streams its input from
-// HBM straight into the MFMA operands (k_dn_l3).
+// cells (x, y, z) in window coordinates: it stages the tile's input halo (18 x
+// 6 x 10 cells, rows padded to 20) in LDS.  Layer 1: each wavefront takes one
+// z-plane, 4 rows of 16 cells, and all 32 output channels; layer 2: two planes
+// and 16 channels, accumulated over the 27 taps x 32 input channels (one MFMA
+// K-step of 32 per tap).  Layer 3 streams its input from HBM straight into the
+// MFMA operands (k_dn_l3).
 //
 // MFMA operand layout (16x16x32): lane l holds row l%16 of the first operand,
 // K elements 8(l/16)..8(l/16)+7, and column l%16 of the second with the same K
@@ -28,13 +28,9 @@
 // a lane's results are neighbouring channels of one cell.  (A and B below
 // name the cells' and the weights' fragments.)
 //
-// Weight rows of 64 B are stored in LDS as four 16-byte chunks rotated by
-// rot(r) = ((r >> 1) ^ (r >> 2)) & 3, so that the consecutive rows one B read
-// touches spread over all banks; rot(r + 16 k) = rot(r), so the rows of every
-// tap are the first 16 rows moved by a constant.  The input halo's cell rows
-// are padded to 80 B instead (8 consecutive cells, one 16-byte read each,
-// fall in disjoint bank quadruples), so every A read of a wavefront is one
-// base address plus a constant per tap.
+// The input halo's cell rows are padded to 80 B (8 consecutive cells, one
+// 16-byte read each, fall in disjoint bank quadruples), so every read of a
+// wavefront is one base address plus a constant per tap.
 #pragma once
 
 #include "pic_internal.h"
@@ -52,16 +48,11 @@ constexpr int DN_THREADS = 512;
 constexpr int DN_ROWB = 80;                               // LDS bytes per halo cell row
 constexpr int DN_ACT_LDS = DN_HCELLS * DN_ROWB;
 
-__device__ __forceinline__ int dn_rot(int r) { return ((r >> 1) ^ (r >> 2)) & 3; }
-
-// Byte offset of 16-byte chunk q of 64-byte row r.
-__device__ __forceinline__ int dn_chunk(int r, int q) { return r * 64 + (((q + dn_rot(r)) & 3) << 4); }
-
 // Storage index along one axis of window/box coordinate v, or -1 when the
 // neighbour reads as zero.  bc: 0 periodic, 1 zero outside [0, n), 2 moving
 // window (zero outside [0, n), storage = (v + origin) mod n).
 __device__ __forceinline__ int dn_axis(int v, int n, int bc, int origin) {
-    if (bc == 0) return v < 0 ? v + n : (v >= n ? v - n : v);
+    if (bc == 0) return v < 0 ? v + n : (v >= n ? (v == n ? 0 : -1) : v);   // (no output needs v > n)
     if (v < 0 || v >= n) return -1;
     if (bc == 2) {
         v += origin;
@@ -125,32 +116,29 @@ inline dim3 dn_grid(const int n[3]) {
 
 hipError_t launch_dn_layer(int kind, const DnArgs& a, hipStream_t st);
 
-// Tile origin (window coordinates) of this workgroup.
-__device__ __forceinline__ void dn_tile(int t0[3]) {
-    t0[0] = blockIdx.x * DN_TX;
-    t0[1] = blockIdx.y * DN_TY;
-    t0[2] = blockIdx.z * DN_TZ;
+// Tile of this workgroup in a grid of (nx, ny, nz) tiles.  Workgroups go
+// round-robin over the 8 XCDs; each XCD takes a contiguous run of tiles, x
+// fastest, then 4 rows of tiles along y, then z, so that the halo along z is
+// read while the rows that it shares are still in that XCD's L2.
+__device__ __forceinline__ int3 dn_walk(int nx, int ny, int nz, int nb, int id) {
+    const int k = id % 8, per = nb / 8, rem = nb % 8;
+    const int t = k * per + min(k, rem) + id / 8;
+    const int band = nx * 4 * nz, yb = t / band, r = t - yb * band;
+    const int rows = min(4, ny - 4 * yb), z = r / (nx * rows), q = r - z * (nx * rows);
+    return make_int3(q % nx, 4 * yb + q / nx, z);
 }
 
-// Copy ROWS 64-byte rows of packed weights into LDS (swizzled).  Each thread
-// issues all its global loads before its first LDS store, so the staging
-// waits for one memory latency rather than one per chunk.
-template <int ROWS>
-__device__ __forceinline__ void dn_stage_weights(const __bf16* __restrict__ w, char* lds) {
-    constexpr int N = ROWS * 4, PER = (N + DN_THREADS - 1) / DN_THREADS;
-    const uint4* src = reinterpret_cast<const uint4*>(w);
-    uint4 v[PER];
-#pragma unroll
-    for (int k = 0; k < PER; ++k) {
-        const int g = threadIdx.x + k * DN_THREADS;
-        v[k] = make_uint4(0u, 0u, 0u, 0u);
-        if (g < N) v[k] = src[g];
-    }
-#pragma unroll
-    for (int k = 0; k < PER; ++k) {
-        const int g = threadIdx.x + k * DN_THREADS;
-        if (g < N) *reinterpret_cast<uint4*>(lds + dn_chunk(g >> 2, g & 3)) = v[k];
-    }
+__device__ __forceinline__ int3 dn_walk() {
+    const int id = (int)(blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * blockIdx.z));
+    return dn_walk((int)gridDim.x, (int)gridDim.y, (int)gridDim.z, (int)(gridDim.x * gridDim.y * gridDim.z), id);
+}
+
+// Tile origin (window coordinates) of this workgroup.
+__device__ __forceinline__ void dn_tile(int t0[3]) {
+    const int3 t = dn_walk();
+    t0[0] = t.x * DN_TX;
+    t0[1] = t.y * DN_TY;
+    t0[2] = t.z * DN_TZ;
 }
 
 // Storage cell index of halo cell (hx, hy, hz) of the tile, or -1 for zero.
@@ -164,19 +152,27 @@ __device__ __forceinline__ int dn_halo_src(const DnArgs& a, const int t0[3], int
 
 // A 32-channel bf16 activation halo in two phases: every global load of the
 // thread into registers (they can stay in flight while the previous tile's
-// matrix work runs), then the LDS stores.  The halo coordinates of the
-// thread's chunks do not depend on the tile: dn_halo_coords packs them once
-// (hx | hy << 8 | hz << 16 | chunk << 24, or -1 for no load).
-constexpr int DN_ACT_PER = (DN_HCELLS * 4 + DN_THREADS - 1) / DN_THREADS;
+// matrix work runs), then the LDS stores.  A thread takes one 16-byte chunk of
+// one (x, y) of the halo (DnLane) in all of its planes, so that only the
+// plane, which is uniform, changes between its loads: with the chunks dealt
+// linearly the coordinates of every load were computed per lane, which was
+// two thirds of the layer's vector instructions.
+constexpr int DN_ACT_PER = DN_HZ;
+static_assert(DN_HX * DN_HY * 4 <= DN_THREADS, "a thread per chunk of a halo plane");
 
-__device__ __forceinline__ void dn_halo_coords(int hc[DN_ACT_PER]) {
-#pragma unroll
-    for (int k = 0; k < DN_ACT_PER; ++k) {
-        const int g = threadIdx.x + k * DN_THREADS;
-        const int c = g >> 2, q = g & 3;
-        const int hx = c % DN_HX, r = c / DN_HX, hy = r % DN_HY, hz = r / DN_HY;
-        hc[k] = g < DN_HCELLS * 4 && hx < DN_TX + 2 ? hx | (hy << 8) | (hz << 16) | (q << 24) : -1;
-    }
+struct DnLane {
+    int hx, hy, chunk;
+    bool read;   // reads a cell (x padding is stored as zero)
+};
+
+__device__ __forceinline__ DnLane dn_lane() {
+    DnLane t;
+    const int c = min((int)(threadIdx.x >> 2), DN_HX * DN_HY - 1);   // (the threads over repeat the last cell)
+    t.chunk = threadIdx.x & 3;
+    t.hx = c % DN_HX;
+    t.hy = c / DN_HX;
+    t.read = t.hx < DN_TX + 2;
+    return t;
 }
 
 // Grid and boundary of a layer held in registers for the halo loads.
@@ -195,39 +191,58 @@ __device__ __forceinline__ DnBox dn_box(const DnArgs& a) {
     return b;
 }
 
-// dn_axis for v in [-1, n] without branches (v one cell beyond the box at most).
+// dn_axis without branches (v >= -1).
 __device__ __forceinline__ int dn_axis_sel(int v, int n, int bc, int origin) {
     const bool out = v < 0 || v >= n;
-    const int w = v < 0 ? v + n : (v >= n ? v - n : v);
+    const int w = v < 0 ? v + n : (v >= n ? 0 : v);
     int x = v + origin;
     x = x >= n ? x - n : x;
     const int r = bc == 0 ? w : (bc == 2 ? x : v);
-    return bc != 0 && out ? -1 : r;
+    return (bc != 0 && out) || v > n ? -1 : r;
 }
 
-__device__ __forceinline__ void dn_load_act(const __bf16* __restrict__ act, const DnBox& b, const int t0[3],
-                                            const int hc[DN_ACT_PER], uint4 v[DN_ACT_PER]) {
-    const uint4* src = reinterpret_cast<const uint4*>(act);
-    long long off[DN_ACT_PER];
+// Starts the loads; returns the planes that lie outside the box (bit k), which
+// dn_zero_planes clears once the loads have arrived.
+__device__ __forceinline__ unsigned dn_load_act(const __bf16* __restrict__ act, const DnBox& b, const int t0[3],
+                                            const DnLane& t, uint4 v[DN_ACT_PER]) {
+    const int x = dn_axis_sel(t0[0] - 1 + t.hx, b.n[0], b.bc[0], b.origin);
+    const int y = dn_axis_sel(t0[1] - 1 + t.hy, b.n[1], b.bc[1], 0);
+    const bool ok = t.read && x >= 0 && y >= 0;
+    const uint4* src = reinterpret_cast<const uint4*>(act) + ((size_t)x + (size_t)b.n[0] * y) * 4 + t.chunk;
+    const size_t plane = (size_t)b.n[0] * b.n[1] * 4;
 #pragma unroll
-    for (int k = 0; k < DN_ACT_PER; ++k) {
-        const int x = dn_axis_sel(t0[0] - 1 + (hc[k] & 255), b.n[0], b.bc[0], b.origin);
-        const int y = dn_axis_sel(t0[1] - 1 + ((hc[k] >> 8) & 255), b.n[1], b.bc[1], 0);
-        const int z = dn_axis_sel(t0[2] - 1 + ((hc[k] >> 16) & 255), b.n[2], b.bc[2], 0);
-        const bool ok = hc[k] >= 0 && x >= 0 && y >= 0 && z >= 0;
-        off[k] = ok ? ((long long)x + (long long)b.n[0] * (y + (long long)b.n[1] * z)) * 4 + (hc[k] >> 24) : -1;
+    for (int k = 0; k < DN_ACT_PER; ++k) v[k] = make_uint4(0u, 0u, 0u, 0u);
+    unsigned out = 0;
+    size_t at[DN_ACT_PER];
+    if (t0[2] >= 1 && t0[2] - 1 + DN_HZ <= b.n[2]) {   // every plane inside the box
+        at[0] = plane * (t0[2] - 1);
+#pragma unroll
+        for (int k = 1; k < DN_ACT_PER; ++k) at[k] = at[k - 1] + plane;
+    } else {
+#pragma unroll
+        for (int k = 0; k < DN_ACT_PER; ++k) {
+            const int z = dn_axis_sel(t0[2] - 1 + k, b.n[2], b.bc[2], 0);
+            at[k] = plane * max(z, 0);
+            out |= z < 0 ? 1u << k : 0u;
+        }
     }
+    if (ok)
 #pragma unroll
-    for (int k = 0; k < DN_ACT_PER; ++k) v[k] = off[k] >= 0 ? src[off[k]] : make_uint4(0u, 0u, 0u, 0u);
+        for (int k = 0; k < DN_ACT_PER; ++k) v[k] = src[at[k]];
+    return out;
 }
 
-__device__ __forceinline__ void dn_store_act(const uint4 v[DN_ACT_PER], char* lds) {
-    constexpr int N = DN_HCELLS * 4;
+__device__ __forceinline__ void dn_zero_planes(uint4 v[DN_ACT_PER], unsigned out) {
+    if (out == 0) return;
 #pragma unroll
-    for (int k = 0; k < DN_ACT_PER; ++k) {
-        const int g = threadIdx.x + k * DN_THREADS;
-        if (g < N) *reinterpret_cast<uint4*>(lds + (g >> 2) * DN_ROWB + (g & 3) * 16) = v[k];
-    }
+    for (int k = 0; k < DN_ACT_PER; ++k)
+        if ((out >> k) & 1) v[k] = make_uint4(0u, 0u, 0u, 0u);
+}
+
+__device__ __forceinline__ void dn_store_act(const uint4 v[DN_ACT_PER], const DnLane& t, char* lds) {
+    char* p = lds + (t.hy * DN_HX + t.hx) * DN_ROWB + t.chunk * 16;
+#pragma unroll
+    for (int k = 0; k < DN_ACT_PER; ++k) *reinterpret_cast<uint4*>(p + k * (DN_HX * DN_HY * DN_ROWB)) = v[k];
 }
 
 // Output tiles of the box and the origin of tile t (x fastest).
@@ -256,41 +271,35 @@ __device__ __forceinline__ int dn_out_cell(const DnArgs& a, const int t0[3], int
 // lane group q (4 q ..) of both halves together are channels 8 q .. 8 q + 7.
 __device__ __forceinline__ int dn_co(int r, int h) { return 8 * (r >> 2) + 4 * h + (r & 3); }
 
-// Accumulate the 27 taps x 32 input channels of a 32-channel layer.  Per tap
-// column (dz, dx) the wavefront reads the 6 halo rows its 4 output rows need
-// once and reuses each for the three dy taps (row blk + dy): 6 A reads per 12
-// row-block MFMA steps.  All taps are unrolled, so every LDS address is the
-// lane's base plus a constant.
-template <int NH>
-__device__ __forceinline__ void dn_mma32(const char* act, const char* wl, f32x4 acc[4][NH]) {
-    const int l = threadIdx.x & 63, lz = threadIdx.x >> 6;
+// Accumulate the 27 taps x 32 input channels for 16 output channels of 2
+// planes x 4 rows of 16 cells: per halo plane and x-tap the wavefront reads the
+// 6 halo rows once and uses each for up to 3 dy taps and both output planes,
+// 72 reads for 216 matrix instructions.  All taps are unrolled, so every LDS
+// address is the lane's base plus a constant.
+__device__ __forceinline__ void dn_mma32(const char* act, const bf16x8 W[27], f32x4 acc[2][4]) {
+    const int l = threadIdx.x & 63, lz = (threadIdx.x >> 7) * 2;
     const int m = l & 15, q = l >> 4;
     const char* abase = act + (lz * DN_HY * DN_HX + m) * DN_ROWB + q * 16;
-    // (the 16 rows dn_co(m, h) of a tap also spread over all banks)
-    const char* bbase[NH];
 #pragma unroll
-    for (int h = 0; h < NH; ++h) bbase[h] = wl + dn_chunk(dn_co(m, h), q);
+    for (int pz = 0; pz < 4; ++pz)
 #pragma unroll
-    for (int zx = 0; zx < 9; ++zx) {
-        const int dz = zx / 3, dx = zx % 3;   // 0..2 = offset + 1
-        bf16x8 A[DN_HY];
+        for (int dx = 0; dx < 3; ++dx) {
+            bf16x8 A[DN_HY];
 #pragma unroll
-        for (int r = 0; r < DN_HY; ++r)
-            A[r] = *reinterpret_cast<const bf16x8*>(abase + ((dz * DN_HY + r) * DN_HX + dx) * DN_ROWB);
+            for (int r = 0; r < DN_HY; ++r)
+                A[r] = *reinterpret_cast<const bf16x8*>(abase + ((pz * DN_HY + r) * DN_HX + dx) * DN_ROWB);
 #pragma unroll
-        for (int dy = 0; dy < 3; ++dy) {
-            const int tap = dz * 9 + dy * 3 + dx;
-            bf16x8 B[NH];
+            for (int dy = 0; dy < 3; ++dy)
 #pragma unroll
-            for (int h = 0; h < NH; ++h)
-                B[h] = *reinterpret_cast<const bf16x8*>(bbase[h] + tap * NH * 1024);
+                for (int p = 0; p < 2; ++p) {
+                    const int dz = pz - p;
+                    if (dz < 0 || dz > 2) continue;
 #pragma unroll
-            for (int blk = 0; blk < 4; ++blk)
-#pragma unroll
-                for (int h = 0; h < NH; ++h)
-                    acc[blk][h] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(B[h], A[blk + dy], acc[blk][h], 0, 0, 0);
+                    for (int r = 0; r < 4; ++r)
+                        acc[p][r] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(W[dz * 9 + dy * 3 + dx], A[r + dy],
+                                                                            acc[p][r], 0, 0, 0);
+                }
         }
-    }
 }
 
 }  // namespace pic

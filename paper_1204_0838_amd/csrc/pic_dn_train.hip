@@ -139,12 +139,12 @@ __global__ void __launch_bounds__(DN_THREADS) k_dn_wgrad(WgArgs a) {
         box.bc[d] = 1;   // zero beyond the crop's faces
     }
     box.origin = 0;
-    int hc[DN_ACT_PER];
-    if (!KSPLIT) dn_halo_coords(hc);
+    const DnLane lane = dn_lane();
     constexpr int JPER = (DN_HCELLS + DN_THREADS - 1) / DN_THREADS;
     constexpr int OPER = DC < 16 ? 1 : WG_CELLS * 4 / DN_THREADS;   // pieces of the output gradient per thread
     uint4 hv[KSPLIT ? 1 : DN_ACT_PER], ov[OPER];
     float jv[KSPLIT ? JPER : 1][3];
+    unsigned out = 0;
     auto load = [&](int t) {
         int t0[3];
         dn_tile_of(t, ntx, nty, t0);
@@ -161,7 +161,7 @@ __global__ void __launch_bounds__(DN_THREADS) k_dn_wgrad(WgArgs a) {
                 for (int d = 0; d < 3; ++d) jv[k][d] = ok ? a.J[d][s] : 0.0f;
             }
         } else {
-            dn_load_act(a.in, box, t0, hc, hv);
+            out = dn_load_act(a.in, box, t0, lane, hv);
         }
 #pragma unroll
         for (int k = 0; k < OPER; ++k) {
@@ -192,11 +192,11 @@ __global__ void __launch_bounds__(DN_THREADS) k_dn_wgrad(WgArgs a) {
                 if (c < DN_HCELLS) *reinterpret_cast<bf16x4*>(in_l + c * 8) = v;
             }
         } else {
+            dn_zero_planes(hv, out);
 #pragma unroll
             for (int k = 0; k < DN_ACT_PER; ++k) {
-                const int g = threadIdx.x + k * DN_THREADS, c = g >> 2;
-                if (g < DN_HCELLS * 4)
-                    *reinterpret_cast<uint4*>(in_l + wg_half(c, (g >> 1) & 1) + (g & 1) * 16) = hv[k];
+                const int c = (k * DN_HY + lane.hy) * DN_HX + lane.hx;
+                *reinterpret_cast<uint4*>(in_l + wg_half(c, lane.chunk >> 1) + (lane.chunk & 1) * 16) = hv[k];
             }
         }
 #pragma unroll
