@@ -351,15 +351,7 @@ __global__ void __launch_bounds__(64 * L3_WAVES, 2) k_dn_l3(DnArgs a, int zrun) 
 
 __device__ __forceinline__ float dn_at(const float* __restrict__ F, int s) { return s >= 0 ? F[s] : 0.0f; }
 
-// Output stage in one pass over tiles of 32 x 8 x 4 cells: J' = B(t),
-// t = J + sigma curl(y), curl(y)_a = (y_{a+2} - y_{a+2}[-e_{a+1}]) / d_{a+1} -
-// (y_{a+1} - y_{a+1}[-e_{a+2}]) / d_{a+2}, with t computed in LDS on the tile
-// plus a 1-cell halo (zero outside the box) from y staged with a further cell
-// below (the backward differences).  LOSS: J' is compared with the target
-// (one FP64 atomic per workgroup) and dst takes the loss gradient.
-constexpr int DO_TX = 32, DO_TY = 8, DO_TZ = 4, DO_THREADS = DO_TX * DO_TY * DO_TZ;
-constexpr int DO_YX = DO_TX + 3, DO_YY = DO_TY + 3, DO_YZ = DO_TZ + 3;   // y: cells -2 .. T
-constexpr int DO_SX = DO_TX + 2, DO_SY = DO_TY + 2, DO_SZ = DO_TZ + 2;   // t: cells -1 .. T
+constexpr int DO_TX = 32, DO_TY = 8, DO_TZ = 4, DO_THREADS = DO_TX * DO_TY * DO_TZ;   // (adjoint stage)
 
 __device__ __forceinline__ int do_src(const DnCombine& c, int x, int y, int z) {
     const int sx = dn_axis(x, c.n[0], c.bc[0], c.origin);
@@ -391,91 +383,122 @@ __device__ __forceinline__ float do_binomial(const float* F, int lx, int ly, int
     return acc;
 }
 
+// Output stage J' = B(t), t = J + sigma curl(y), curl(y)_a =
+// (y_{a+2} - y_{a+2}[-e_{a+1}]) / d_{a+1} - (y_{a+1} - y_{a+1}[-e_{a+2}]) / d_{a+2},
+// t zero outside the box.  A workgroup takes a column of 29 x 13 cells and
+// marches along z: a thread owns one (x, y) of the column with the halo that
+// the stencils need (2 below, 1 above: 32 x 16) and keeps the planes below in
+// registers; neighbours along x come from the next lane, along y from LDS, one
+// barrier per plane (the y planes are stored one ahead, both in two buffers).
+// The loads of a plane are in flight for one (y) or two (J) planes.  LOSS: J' is
+// compared with the target (one FP64 atomic per workgroup) and dst takes the
+// loss gradient.  Tiles of 32x8x4 with the 27-point filter taken from LDS
+// needed 532 vector instructions a cell: 384x192x160 cells 215 -> 125 us (HBM: 425 MB, 87 us at the copy rate).
+constexpr int OM_X = 32, OM_Y = 16, OM_TX = OM_X - 3, OM_TY = OM_Y - 3, OM_THREADS = OM_X * OM_Y;
+
+// Value of lane - 1 / lane + 1 (the lanes at a row's ends take part in no output).
+__device__ __forceinline__ float lane_below(float v) {
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x138, 0xf, 0xf, false));   // wave_shr:1
+}
+__device__ __forceinline__ float lane_above(float v) {
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x130, 0xf, 0xf, false));   // wave_shl:1
+}
+
 template <bool LOSS>
-__global__ void __launch_bounds__(DO_THREADS) k_dn_output(DnCombine c) {
-    __shared__ float ys[3][DO_YZ * DO_YY * DO_YX];
-    __shared__ float ts[3][DO_SZ * DO_SY * DO_SX];
+__global__ void __launch_bounds__(OM_THREADS, 6) k_dn_output(DnCombine c, int zrun) {
+    __shared__ float ysh[2][2][OM_THREADS];   // y_x, y_z
+    __shared__ float xsh[2][3][OM_THREADS];   // x-filtered t
     const int3 tile = dn_walk();
-    const int t0[3] = {tile.x * DO_TX, tile.y * DO_TY, tile.z * DO_TZ};
-    // Every global load of a thread is issued before the first of them is
-    // used (the y halo, then the current at the t cells, the latter in flight
-    // while the y halo is stored), so each staging pass waits for one memory
-    // latency rather than one per cell.
-    constexpr int NY = DO_YZ * DO_YY * DO_YX, PY = (NY + DO_THREADS - 1) / DO_THREADS;
-    constexpr int NT = DO_SZ * DO_SY * DO_SX, PT = (NT + DO_THREADS - 1) / DO_THREADS;
-    float yv[PY][3];
+    const int i = threadIdx.x, hx = i % OM_X, hy = i / OM_X;
+    const int x = tile.x * OM_TX - 2 + hx, y = tile.y * OM_TY - 2 + hy;
+    const int z0 = tile.z * zrun, z1 = min(z0 + zrun, c.n[2]);
+    const int sx = dn_axis(x, c.n[0], c.bc[0], c.origin), sy = dn_axis(y, c.n[1], c.bc[1], 0);
+    const bool in = sx >= 0 && sy >= 0;
+    const int at = in ? sx + c.n[0] * sy : 0;
+    const bool mine = hx >= 2 && hx < OM_X - 1 && hy >= 2 && hy < OM_Y - 1 && x < c.n[0] && y < c.n[1];
+    const int below = max(i - OM_X, 0), above = min(i + OM_X, OM_THREADS - 1);
+    const size_t plane = (size_t)c.n[0] * c.n[1];
+    // a plane of three fields at this (x, y); zero outside the box
+    auto load = [&](const float* const F[3], int z, float v[3]) {
+        const int sz = dn_axis(z, c.n[2], c.bc[2], 0);
+        const size_t p = plane * max(sz, 0);
+        const bool ok = in && sz >= 0;
 #pragma unroll
-    for (int q = 0; q < PY; ++q) {
-        const int i = (int)threadIdx.x + q * DO_THREADS;
-        const int hx = i % DO_YX, r = i / DO_YX, hy = r % DO_YY, hz = r / DO_YY;
-        const int s = i < NY ? do_src(c, t0[0] - 2 + hx, t0[1] - 2 + hy, t0[2] - 2 + hz) : -1;
-#pragma unroll
-        for (int d = 0; d < 3; ++d) yv[q][d] = dn_at(c.y[d], s);
-    }
-    int ts_src[PT];
-    float sv[PT][3];
-#pragma unroll
-    for (int q = 0; q < PT; ++q) {
-        const int i = (int)threadIdx.x + q * DO_THREADS;
-        const int hx = i % DO_SX, r = i / DO_SX, hy = r % DO_SY, hz = r / DO_SY;
-        ts_src[q] = i < NT ? do_src(c, t0[0] - 1 + hx, t0[1] - 1 + hy, t0[2] - 1 + hz) : -1;
-#pragma unroll
-        for (int comp = 0; comp < 3; ++comp) sv[q][comp] = dn_at(c.src[comp], ts_src[q]);
-    }
-#pragma unroll
-    for (int q = 0; q < PY; ++q) {
-        const int i = (int)threadIdx.x + q * DO_THREADS;
-        if (i < NY)
-#pragma unroll
-            for (int d = 0; d < 3; ++d) ys[d][i] = yv[q][d];
-    }
-    __syncthreads();
-#pragma unroll
-    for (int q = 0; q < PT; ++q) {
-        const int i = (int)threadIdx.x + q * DO_THREADS;
-        if (i >= NT) continue;
-        const int hx = i % DO_SX, r = i / DO_SX, hy = r % DO_SY, hz = r / DO_SY;
-        const int s = ts_src[q];
-        const int yc = ((hz + 1) * DO_YY + (hy + 1)) * DO_YX + (hx + 1);   // the same cell in ys
-        const int ym[3] = {yc - 1, yc - DO_YX, yc - DO_YX * DO_YY};          // one cell lower along x, y, z
-#pragma unroll
-        for (int comp = 0; comp < 3; ++comp) {
-            const int t1 = (comp + 1) % 3, t2 = (comp + 2) % 3;
-            float v = 0.0f;
-            if (s >= 0) {
-                const float cu = (ys[t2][yc] - ys[t2][ym[t1]]) * c.inv_d[t1] - (ys[t1][yc] - ys[t1][ym[t2]]) * c.inv_d[t2];
-                v = fmaf(c.sigma, cu, sv[q][comp]);
-            }
-            ts[comp][i] = v;
-        }
-    }
-    __syncthreads();
-    const int lx = threadIdx.x % DO_TX, ly = (threadIdx.x / DO_TX) % DO_TY, lz = threadIdx.x / (DO_TX * DO_TY);
-    const int x = t0[0] + lx, y = t0[1] + ly, z = t0[2] + lz;
-    const bool inside = x < c.n[0] && y < c.n[1] && z < c.n[2];
+        for (int d = 0; d < 3; ++d) v[d] = ok ? (F[d] + p)[at] : 0.0f;
+    };
+    const float w0 = 0.25f, w1 = 0.5f;
+    float a0[3] = {}, a1[3] = {};
     double part = 0.0;
-    if (inside) {
-        const int s = do_src(c, x, y, z);
+    // Plane z: t from y (z - 1, z, the neighbours of z in buffer b) and J; y of
+    // z + 1 goes to the other buffer; J of z + 2 and y of z + 2 are requested.
+    auto step = [&](int z, int b, const float (&Yp)[3], const float (&Y)[3], const float (&Yn)[3], float (&Yf)[3],
+                    const float (&J)[3], float (&Jf)[3]) {
+        if (z + 1 < z1) {
+            load(c.y, z + 2, Yf);
+            load(c.src, z + 2, Jf);
+        }
+        const bool inz = in && dn_axis(z, c.n[2], c.bc[2], 0) >= 0;
+        const float yx_y = ysh[b][0][below], yz_y = ysh[b][1][below];
+        const float cu0 = (Y[2] - yz_y) * c.inv_d[1] - (Y[1] - Yp[1]) * c.inv_d[2];
+        const float cu1 = (Y[0] - Yp[0]) * c.inv_d[2] - (Y[2] - lane_below(Y[2])) * c.inv_d[0];
+        const float cu2 = (Y[1] - lane_below(Y[1])) * c.inv_d[0] - (Y[0] - yx_y) * c.inv_d[1];
+        const float t[3] = {inz ? fmaf(c.sigma, cu0, J[0]) : 0.0f, inz ? fmaf(c.sigma, cu1, J[1]) : 0.0f,
+                            inz ? fmaf(c.sigma, cu2, J[2]) : 0.0f};
+        b ^= 1;
+        float ax[3];
 #pragma unroll
-        for (int comp = 0; comp < 3; ++comp) {
-            const float acc = do_binomial<DO_SX, DO_SY>(ts[comp], lx, ly, lz);
-            if (LOSS) {
-                const float e = (acc - c.T[comp][s]) * c.inv_scale[comp];
-                part += (double)e * (double)e;
-                c.dst[comp][s] = c.grad_scale * e * c.inv_scale[comp];
-            } else {
-                c.dst[comp][s] = acc;
+        for (int d = 0; d < 3; ++d) {
+            ax[d] = fmaf(w0, lane_above(t[d]), fmaf(w1, t[d], fmaf(w0, lane_below(t[d]), 0.0f)));
+            xsh[b][d][i] = ax[d];
+        }
+        ysh[b][0][i] = Yn[0];
+        ysh[b][1][i] = Yn[2];
+        __syncthreads();
+#pragma unroll
+        for (int d = 0; d < 3; ++d) {
+            const float ay = fmaf(w0, xsh[b][d][above], fmaf(w1, ax[d], fmaf(w0, xsh[b][d][below], 0.0f)));
+            const float o = fmaf(w0, ay, fmaf(w1, a1[d], fmaf(w0, a0[d], 0.0f)));
+            a0[d] = a1[d];
+            a1[d] = ay;
+            if (z > z0 && mine) {
+                float* out = c.dst[d] + plane * (z - 1);
+                if (LOSS) {
+                    const float e = (o - (c.T[d] + plane * (z - 1))[at]) * c.inv_scale[d];
+                    part += (double)e * (double)e;
+                    out[at] = c.grad_scale * e * c.inv_scale[d];
+                } else {
+                    out[at] = o;
+                }
             }
         }
+    };
+    float Y0[3], Y1[3], Y2[3], Y3[3], J0[3], J1[3], J2[3], J3[3];
+    load(c.y, z0 - 2, Y0);
+    load(c.y, z0 - 1, Y1);
+    load(c.src, z0 - 1, J1);
+    load(c.y, z0, Y2);
+    load(c.src, z0, J2);
+    ysh[0][0][i] = Y1[0];
+    ysh[0][1][i] = Y1[2];
+    __syncthreads();
+    for (int z = z0 - 1;; ++z) {   // (four buffers take turns: no register moves, which would wait for the loads)
+        step(z, 0, Y0, Y1, Y2, Y3, J1, J3);
+        if (++z > z1) break;
+        step(z, 1, Y1, Y2, Y3, Y0, J2, J0);
+        if (++z > z1) break;
+        step(z, 0, Y2, Y3, Y0, Y1, J3, J1);
+        if (++z > z1) break;
+        step(z, 1, Y3, Y0, Y1, Y2, J0, J2);
+        if (z + 1 > z1) break;
     }
     if (LOSS) {
-        __shared__ double ws[DO_THREADS / 64];
+        __shared__ double ws[OM_THREADS / 64];
         for (int o = 32; o > 0; o >>= 1) part += __shfl_xor(part, o, 64);
         if ((threadIdx.x & 63) == 0) ws[threadIdx.x >> 6] = part;
         __syncthreads();
         if (threadIdx.x == 0) {
             double sum = 0.0;
-            for (int k = 0; k < DO_THREADS / 64; ++k) sum += ws[k];
+            for (int k = 0; k < OM_THREADS / 64; ++k) sum += ws[k];
             unsafeAtomicAdd(c.loss, sum * (0.5 * (double)c.grad_scale));
         }
     }
@@ -541,7 +564,15 @@ static dim3 do_grid(const DnCombine& c) {
 }
 
 hipError_t launch_dn_output(const DnCombine& c, bool loss, hipStream_t st) {
-    hipLaunchKernelGGL(loss ? k_dn_output<true> : k_dn_output<false>, do_grid(c), dim3(DO_THREADS), 0, st, c);
+    // planes per march: 16 (3 more are loaded), fewer where that leaves the
+    // chip with less than four workgroups per compute unit.  384x192x160
+    // cells: 122 us with 8, 125 with 16, 140 with 32; 128x64x64: 32 with 16
+    // (100 workgroups), 16 with 4
+    const int tx = (c.n[0] + OM_TX - 1) / OM_TX, ty = (c.n[1] + OM_TY - 1) / OM_TY;
+    int zrun = 16;
+    while (zrun > 4 && (long long)tx * ty * ((c.n[2] + zrun - 1) / zrun) < 1024) zrun /= 2;
+    hipLaunchKernelGGL(loss ? k_dn_output<true> : k_dn_output<false>, dim3(tx, ty, (c.n[2] + zrun - 1) / zrun),
+                       dim3(OM_THREADS), 0, st, c, zrun);
     return hipGetLastError();
 }
 
