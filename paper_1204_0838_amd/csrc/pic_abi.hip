@@ -563,12 +563,12 @@ void dn_bc(const pic_ctx* c, int bc[3]) {
     bc[2] = 0;
 }
 
-// Jin -> Jout through the denoiser (distinct buffers).
-pic_status denoise(pic_ctx* c, float* const Jin[3], float* const Jout[3]) {
+// Jin -> Jout through the denoiser: distinct buffers, or the same one with a third for a copy of Jin.
+pic_status denoise(pic_ctx* c, float* const Jin[3], float* const Jout[3], float* const copy[3] = nullptr) {
     if (!c->has_dn) return fail(c, PIC_ESTATE, "denoiser weights not set");
     int bc[3];
     dn_bc(c, bc);
-    HIPCHK(c, launch_denoise(c->g, bc, c->dn, Jin, Jout, reinterpret_cast<__bf16*>(c->ws + c->L.dn_h1),
+    HIPCHK(c, launch_denoise(c->g, bc, c->dn, Jin, Jout, copy, reinterpret_cast<__bf16*>(c->ws + c->L.dn_h1),
                              reinterpret_cast<__bf16*>(c->ws + c->L.dn_h2), c->stream));
     return PIC_OK;
 }
@@ -587,9 +587,14 @@ pic_status filter_in_place(pic_ctx* c) {
     if (c->desc.jpost == PIC_JPOST_NONE) return PIC_OK;
     float* tmp[3];
     jtmp_of(c, tmp);
-    PICCHK(filter_to(c, tmp));
-    for (int a = 0; a < 3; ++a)
-        HIPCHK(c, hipMemcpyAsync(c->f.J[a], tmp[a], (size_t)c->g.ncell * 4, hipMemcpyDeviceToDevice, c->stream));
+    if (c->desc.jpost == PIC_JPOST_DENOISER) {
+        // (the first layer, which reads J anyway, copies it: 35 us at 384x192x160; copying the result back took 57)
+        PICCHK(denoise(c, c->f.J, c->f.J, tmp));
+    } else {
+        PICCHK(filter_to(c, tmp));
+        for (int a = 0; a < 3; ++a)
+            HIPCHK(c, hipMemcpyAsync(c->f.J[a], tmp[a], (size_t)c->g.ncell * 4, hipMemcpyDeviceToDevice, c->stream));
+    }
     c->j_filtered = true;
     return PIC_OK;
 }

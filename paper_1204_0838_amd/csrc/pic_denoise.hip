@@ -58,45 +58,61 @@ __device__ __forceinline__ void dn_bias32(const float* __restrict__ bias, float 
 // 4-channel input (3 used), 32 output channels.  K = tap * 4 + channel
 // (channel 3 and taps 27..31 zero), 4 K-steps of 32; lane chunk q of step s
 // covers taps 8s + 2q and 8s + 2q + 1.  IN 0: the current J_d / s_d (FP32,
-// rounded to bf16 here); IN 1: a bf16 [cell][4] array.
+// rounded to bf16 here; a.Jcopy, if given, takes the current as it is); IN 1:
+// a bf16 [cell][4] array.
 template <int IN, int EPI>
 __global__ void __launch_bounds__(DN_THREADS) k_dn_c4(DnArgs a) {
     constexpr int WROW = 272;              // bytes of a weight row (256, padded: 16 rows in different banks)
     __shared__ __attribute__((aligned(16))) char lds[DN_HCELLS * 8 + 32 * WROW];
     char* xin = lds;                       // [halo cell][4] bf16
     char* wl = lds + DN_HCELLS * 8;        // [co][128] bf16
-    int t0[3];
-    dn_tile(t0);
+    const int3 tile = dn_walk();
+    const int t0[3] = {tile.x * DN_TX, tile.y * DN_TY, tile.z * DN_TZ};
     {
         const uint4* src = reinterpret_cast<const uint4*>(a.w);
         for (int g = threadIdx.x; g < 32 * 16; g += DN_THREADS)
             *reinterpret_cast<uint4*>(wl + (g >> 4) * WROW + (g & 15) * 16) = src[g];
     }
     {
-        // every global load of the thread first, then the LDS stores
-        constexpr int PER = (DN_HCELLS + DN_THREADS - 1) / DN_THREADS;
+        // a thread takes one (x, y) of the halo in planes pz, pz + 4, pz + 8
+        // (as DnLane: only the plane changes between its loads); every global
+        // load first, then the LDS stores
+        constexpr int PL = DN_HX * DN_HY, PER = (DN_HZ + 3) / 4;
+        static_assert(4 * PL <= DN_THREADS, "four planes at a time");
+        const int pz = threadIdx.x / PL, c = threadIdx.x % PL, hx = c % DN_HX, hy = c / DN_HX;
+        const int x = t0[0] - 1 + hx, y = t0[1] - 1 + hy;
+        const int xs = dn_axis(x, a.n[0], a.bc[0], a.origin), ys = dn_axis(y, a.n[1], a.bc[1], 0);
+        const bool in = pz < 4 && hx < DN_TX + 2 && xs >= 0 && ys >= 0;
+        const bool own = IN == 0 && a.Jcopy[0] && in && hx >= 1 && hx <= DN_TX && hy >= 1 && hy <= DN_TY &&
+                         x < a.n[0] && y < a.n[1];
+        const int at = xs + a.n[0] * ys;
+        float j[IN == 0 ? PER : 1][3];
         bf16x4 v[PER];
 #pragma unroll
         for (int k = 0; k < PER; ++k) {
-            const int c = threadIdx.x + k * DN_THREADS;
-            const int hx = c % DN_HX, r = c / DN_HX, hy = r % DN_HY, hz = r / DN_HY;
-            v[k] = bf16x4{(__bf16)0.0f, (__bf16)0.0f, (__bf16)0.0f, (__bf16)0.0f};
-            if (c < DN_HCELLS && hx < DN_TX + 2) {
-                const int s = dn_halo_src(a, t0, hx, hy, hz);
-                if (s >= 0) {
-                    if (IN == 0) {
+            const int hz = pz + 4 * k, z = dn_axis(t0[2] - 1 + hz, a.n[2], a.bc[2], 0);
+            const bool ok = in && hz < DN_HZ && z >= 0;
+            const int s = ok ? at + a.n[0] * a.n[1] * z : 0;
+            if constexpr (IN == 0) {
 #pragma unroll
-                        for (int d = 0; d < 3; ++d) v[k][d] = (__bf16)(a.J[d][s] * a.inv_scale[d]);
-                    } else {
-                        v[k] = reinterpret_cast<const bf16x4*>(a.c4_in)[s];
-                    }
-                }
+                for (int d = 0; d < 3; ++d) j[k][d] = ok ? a.J[d][s] : 0.0f;
+            } else {
+                v[k] = bf16x4{(__bf16)0.0f, (__bf16)0.0f, (__bf16)0.0f, (__bf16)0.0f};
+                if (ok) v[k] = reinterpret_cast<const bf16x4*>(a.c4_in)[s];
             }
         }
 #pragma unroll
         for (int k = 0; k < PER; ++k) {
-            const int c = threadIdx.x + k * DN_THREADS;
-            if (c < DN_HCELLS) *reinterpret_cast<bf16x4*>(xin + c * 8) = v[k];
+            const int hz = pz + 4 * k, z = t0[2] - 1 + hz;
+            if constexpr (IN == 0) {
+#pragma unroll
+                for (int d = 0; d < 3; ++d) v[k][d] = (__bf16)(j[k][d] * a.inv_scale[d]);
+                v[k][3] = (__bf16)0.0f;
+                if (own && hz >= 1 && hz <= DN_TZ && z < a.n[2])
+#pragma unroll
+                    for (int d = 0; d < 3; ++d) a.Jcopy[d][at + a.n[0] * a.n[1] * z] = j[k][d];
+            }
+            if (pz < 4 && hz < DN_HZ) *reinterpret_cast<bf16x4*>(xin + (hz * PL + c) * 8) = v[k];
         }
     }
     __syncthreads();
@@ -628,12 +644,13 @@ hipError_t launch_dn_layer(int kind, const DnArgs& a, hipStream_t st) {
 }
 
 hipError_t launch_denoise(const Geom& g, const int bc[3], const DenoiseWeights& w, float* const Jin[3],
-                          float* const Jout[3], __bf16* h1, __bf16* h2, hipStream_t st) {
+                          float* const Jout[3], float* const Jcopy[3], __bf16* h1, __bf16* h2, hipStream_t st) {
     DnArgs a{};
     for (int d = 0; d < 3; ++d) {
         a.n[d] = g.n[d];
         a.bc[d] = bc[d];
         a.J[d] = Jin[d];
+        a.Jcopy[d] = Jcopy ? Jcopy[d] : nullptr;
         a.scale[d] = w.scale[d];
         a.inv_scale[d] = 1.0f / w.scale[d];
     }
@@ -659,13 +676,13 @@ hipError_t launch_denoise(const Geom& g, const int bc[3], const DenoiseWeights& 
     for (int d = 0; d < 3; ++d) a.Jout[d] = y + d * N;
     e = launch_dn_layer(DN_L3_Y, a, st);
     if (e != hipSuccess) return e;
-    // J' = B(J + sigma curl(y)) in one pass (Jout must not alias Jin: tiles
-    // read their neighbours' J)
+    // J' = B(J + sigma curl(y)) in one pass (Jout must not alias the J that
+    // it reads: columns read their neighbours' J)
     DnCombine c{};
     for (int d = 0; d < 3; ++d) {
         c.n[d] = g.n[d];
         c.bc[d] = bc[d];
-        c.src[d] = Jin[d];
+        c.src[d] = Jcopy ? Jcopy[d] : Jin[d];
         c.y[d] = y + d * N;
         c.dst[d] = Jout[d];
         c.inv_d[d] = w.inv_d[d];

@@ -66,6 +66,7 @@ struct DnArgs {
     int bc[3];
     int origin;
     const float* J[3];        // layer 1 input; layer 3 residual input
+    float* Jcopy[3];          // (or null) layer 1 writes its J here as well
     float* Jout[3];           // layer 3 output
     const __bf16* act_in;     // 32-channel input [cell][32]
     __bf16* act_out;          // 32-channel output [cell][32]
@@ -131,23 +132,6 @@ __device__ __forceinline__ int3 dn_walk(int nx, int ny, int nz, int nb, int id) 
 __device__ __forceinline__ int3 dn_walk() {
     const int id = (int)(blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * blockIdx.z));
     return dn_walk((int)gridDim.x, (int)gridDim.y, (int)gridDim.z, (int)(gridDim.x * gridDim.y * gridDim.z), id);
-}
-
-// Tile origin (window coordinates) of this workgroup.
-__device__ __forceinline__ void dn_tile(int t0[3]) {
-    const int3 t = dn_walk();
-    t0[0] = t.x * DN_TX;
-    t0[1] = t.y * DN_TY;
-    t0[2] = t.z * DN_TZ;
-}
-
-// Storage cell index of halo cell (hx, hy, hz) of the tile, or -1 for zero.
-__device__ __forceinline__ int dn_halo_src(const DnArgs& a, const int t0[3], int hx, int hy, int hz) {
-    const int x = dn_axis(t0[0] - 1 + hx, a.n[0], a.bc[0], a.origin);
-    const int y = dn_axis(t0[1] - 1 + hy, a.n[1], a.bc[1], 0);
-    const int z = dn_axis(t0[2] - 1 + hz, a.n[2], a.bc[2], 0);
-    if (x < 0 || y < 0 || z < 0) return -1;
-    return x + a.n[0] * (y + a.n[1] * z);
 }
 
 // A 32-channel bf16 activation halo in two phases: every global load of the

@@ -171,9 +171,10 @@ constexpr size_t kDnW1 = 32 * 128, kDnW2 = 27 * 32 * 32, kDnW3 = 9 * 16 * 32;
 constexpr size_t kDnBias = 32 + 32 + 16;                                            // floats
 
 // bc per axis: 0 periodic, 1 zero outside the box, 2 moving window (zero
-// beyond the window's ends).  Jin -> Jout (distinct), h1, h2: [ncell][32] bf16.
+// beyond the window's ends).  Jin -> Jout (distinct, or the same with Jcopy for a copy of
+// Jin); h1, h2: [ncell][32] bf16.
 hipError_t launch_denoise(const Geom& g, const int bc[3], const DenoiseWeights& w, float* const Jin[3],
-                          float* const Jout[3], __bf16* h1, __bf16* h2, hipStream_t st);
+                          float* const Jout[3], float* const Jcopy[3], __bf16* h1, __bf16* h2, hipStream_t st);
 
 // window / injection / laser kernels (pic_window.hip)
 hipError_t launch_clear_plane(const Geom& g, const FieldPtrs& f, int ix, hipStream_t st);
