@@ -288,7 +288,7 @@ def bench_c4(args):
                    "particles": int(npart), "cells": ncell},
         "phase_ms_per_step": {k[:-3]: prof[k] / max(1, prof["steps"]) for k in
                               ("sort_ms", "tile_ms", "loose_ms", "jpost_ms", "field_ms", "window_ms")},
-        "roofline": {"bound": "mfma", "kernel": "denoiser (k_dn_c4, k_dn_conv32<0>, k_dn_conv32<2>, k_dn_output)",
+        "roofline": {"bound": "mfma", "kernel": "denoiser (k_dn_c4, k_dn_conv32<0>, k_dn_l3, k_dn_output)",
                      "achieved": achieved, "peak": BF16_MFMA_PEAK_TFLOPS, "unit": "TFLOP/s",
                      "frac": achieved / BF16_MFMA_PEAK_TFLOPS, "traffic": None,
                      "alg_flop_per_step": DN_FLOP_PER_CELL * ncell, "mean_denoiser_ms": dn_ms},
@@ -601,7 +601,7 @@ def bench_c1(args):
             "cells": ncell,
             "tiling": {"tile": [sim.desc.tile[a] or 8 for a in range(3)],
                        "guard": sim.desc.guard if sim.desc.guard >= 0 else 1,
-                       "threads": sim.desc.threads or 512, "interleave": sim.desc.interleave,
+                       "threads": sim.desc.threads or 1024, "interleave": sim.desc.interleave,
                        "sort_interval": sim.desc.sort_interval or 2,
                        "source": "explicit" if tiling else "autotune cache or library default"},
         },
