@@ -31,6 +31,17 @@ constexpr size_t kDiagWords = 64;                                 // reduction w
 // 43; 160x128x128, where ordering scans 2.6e6 keys, 1.6e4 136 against 171,
 // 3.2e4 240 against 187.
 constexpr int64_t kDepositTilesMin = 8192;
+// It gathers a species of more than kGatherTilesMin + ncell / 8 particles tile
+// by tile where the grid has a tile for every compute unit, otherwise with one
+// thread per particle, whose speed depends on the particles' order in memory
+// (the staged path does not sort: a warm plasma's order decays).  Measured,
+// direct against tile-wise with its list, random order: 75x50x44 cells, 2.56e5
+// particles 214 us against 119, 5.1e5 437 against 208; 160x128x128, 5.1e5 890
+// against 252; sorted by cell: 60 against 68, 106 against 102, 145 against 163
+// (equal at 6.8e5).  32^3 cells (64 tiles), 5.1e5: 325 against 248 and 149
+// against 203; 16^3 (8 tiles): 205 against 1262.
+constexpr int64_t kGatherTilesMin = 262144;
+constexpr int kGatherTiles = 256;
 constexpr size_t kDiagBytesFixed = (2 * kDiagBins + kDiagWords) * 8;
 
 size_t align_up(size_t v) { return (v + kAlign - 1) / kAlign * kAlign; }
@@ -561,6 +572,21 @@ void dn_bc(const pic_ctx* c, int bc[3]) {
     bc[0] = c->g.window ? 2 : 0;
     bc[1] = 0;
     bc[2] = 0;
+}
+
+// The tile-wise index list of species s by the given cells (every particle
+// with a valid one).  Its scratch, all idle between steps: the sort's rank
+// array, histogram (left holding the key offsets) and block sums, and the
+// spare cell array.
+pic_status tile_list(pic_ctx* c, const Species& sp, int s, const TileGeom& t, const int* cell, const int** list) {
+    Geom gl = c->g;
+    gl.window = 0;
+    gl.pml = 0;
+    int* out = reinterpret_cast<int*>(c->ws + c->L.sort_rank) + sp.base;
+    HIPCHK(c, launch_tile_list(gl, t, cell, &small_of(c)->count[s], (int)sp.bound, hist_of(c), out, sp.alt.cell,
+                               reinterpret_cast<int*>(c->ws + c->L.sums), c->stream));
+    *list = out;
+    return PIC_OK;
 }
 
 // Jin -> Jout through the denoiser: distinct buffers, or the same one with a third for a copy of Jin.
@@ -1129,8 +1155,19 @@ pic_status pic_init_species(pic_ctx* c, const pic_species_bufs* bufs, int64_t n,
 pic_status pic_gather_push(pic_ctx* c, int32_t s) {
     PICCHK(check_species(c, s));
     Species& sp = c->sp[s];
-    HIPCHK(c, launch_gather_push(c->g, fields_of(c), dev_of(c, sp), prev_of(c, sp), &small_of(c)->count[s],
-                                 (int)sp.bound, &small_of(c)->err, c->stream));
+    int* count = &small_of(c)->count[s];
+    const TileGeom t = deposit_tiling(c->g.n);
+    if (sp.bound > kGatherTilesMin + c->g.ncell / 8 && t.ntiles >= kGatherTiles) {
+        HIPCHK(c, launch_gather_invalid(c->g, dev_of(c, sp), prev_of(c, sp), count, (int)sp.bound,
+                                        &small_of(c)->err, c->stream));
+        const int* list = nullptr;
+        PICCHK(tile_list(c, sp, s, t, dev_of(c, sp).cell, &list));
+        HIPCHK(c, launch_gather_tiles(c->g, t, fields_of(c), dev_of(c, sp), prev_of(c, sp), list, hist_of(c),
+                                      &small_of(c)->err, c->stream));
+    } else {
+        HIPCHK(c, launch_gather_push(c->g, fields_of(c), dev_of(c, sp), prev_of(c, sp), count, (int)sp.bound,
+                                     &small_of(c)->err, c->stream));
+    }
     sp.prev_valid = true;
     sp.loose = true;
     c->mid_step = true;
@@ -1143,18 +1180,11 @@ pic_status pic_deposit(pic_ctx* c, int32_t s) {
     if (!sp.prev_valid) return fail(c, PIC_ESTATE, "deposit needs a preceding gather_push");
     c->acc_used = true;
     if (sp.bound > kDepositTilesMin + c->g.ncell / 128) {
-        // tile by tile through an index list by the old cells (every particle
-        // with a valid old cell, also one that the window has since left
-        // behind).  The list's scratch, all idle between steps: the sort's
-        // rank array, histogram and block sums, and the spare cell array.
+        // (by the old cells: also a particle that the window has since left behind)
         const TileGeom t = deposit_tiling(c->g.n);
-        Geom gl = c->g;
-        gl.window = 0;
-        gl.pml = 0;
         const PrevDev pv = prev_of(c, sp);
-        int* list = reinterpret_cast<int*>(c->ws + c->L.sort_rank) + sp.base;
-        HIPCHK(c, launch_tile_list(gl, t, pv.cell, &small_of(c)->count[s], (int)sp.bound, hist_of(c), list,
-                                   sp.alt.cell, reinterpret_cast<int*>(c->ws + c->L.sums), c->stream));
+        const int* list = nullptr;
+        PICCHK(tile_list(c, sp, s, t, pv.cell, &list));
         HIPCHK(c, launch_deposit_tiles(c->g, t, dev_of(c, sp), pv, list, hist_of(c), acc_of(c), c->stream));
     } else {
         HIPCHK(c, launch_deposit(c->g, dev_of(c, sp), prev_of(c, sp), &small_of(c)->count[s], (int)sp.bound,

@@ -197,6 +197,12 @@ hipError_t launch_jfinal(const Geom& g, unsigned long long* acc, float* const J[
 TileGeom deposit_tiling(const int n[3]);
 hipError_t launch_deposit_tiles(const Geom& g, const TileGeom& t, const SpeciesDev& s, const PrevDev& prev,
                                 const int* list, const int* off, unsigned long long* acc, hipStream_t st);
+// gather and push likewise, the list by the current cells; launch_gather_invalid
+// (before the list) takes the particles that it leaves out
+hipError_t launch_gather_invalid(const Geom& g, const SpeciesDev& s, const PrevDev& prev, const int* d_count,
+                                 int max_count, int* d_err, hipStream_t st);
+hipError_t launch_gather_tiles(const Geom& g, const TileGeom& t, const FieldPtrs& f, const SpeciesDev& s,
+                               const PrevDev& prev, const int* list, const int* off, int* d_err, hipStream_t st);
 hipError_t launch_tile_list(const Geom& g, const TileGeom& t, const int* cell, const int* d_count, int max_count,
                             int* hist, int* list, int* tmp, int* sums, hipStream_t st);
 
