@@ -673,7 +673,11 @@ __global__ void __launch_bounds__(256) k_circ_jfinal(CircGeom g, unsigned long l
     const double Ah = 2.0 * pi * ((double)j + 0.5) * dr * dz;
     double a[kCircChannels];
 #pragma unroll
-    for (int c = 0; c < kCircChannels; ++c) a[c] = (double)(long long)acc[(size_t)c * g.ncell + idx] * PIC_FIX_INV;
+    for (int c = 0; c < kCircChannels; ++c) {
+        const unsigned long long v = acc[(size_t)c * g.ncell + idx];
+        a[c] = (double)(long long)v * PIC_FIX_INV;
+        if (zero && v) acc[(size_t)c * g.ncell + idx] = 0ull;   // (most of the box holds no current)
+    }
     Jz0[idx] = (float)(a[0] * dz / V);
     Jz1[idx] = (float)(a[1] * dz / V);
     Jz2[idx] = (float)(a[2] * dz / V);
@@ -689,10 +693,6 @@ __global__ void __launch_bounds__(256) k_circ_jfinal(CircGeom g, unsigned long l
         const double rj = (double)j * dr;
         Jt1[idx] = (float)(rj * a[8] / V);    // -i (a + i b) = b - i a
         Jt2[idx] = (float)(-rj * a[7] / V);
-    }
-    if (zero) {
-#pragma unroll
-        for (int c = 0; c < kCircChannels; ++c) acc[(size_t)c * g.ncell + idx] = 0ull;
     }
 }
 
