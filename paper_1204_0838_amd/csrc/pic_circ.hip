@@ -722,6 +722,12 @@ struct CircJ {
     const float* J[9];   // [comp z, r, th][channel]
 };
 
+// A field value that an update leaves as it was (the pulse has not reached it)
+// is not written back.
+__device__ __forceinline__ void put(float& f, float old, float v) {
+    if (__float_as_int(v) != __float_as_int(old)) f = v;
+}
+
 // B -= h curl E for both modes at node (i, j) (storage z).
 __global__ void __launch_bounds__(256) k_circ_bhalf(CircGeom g, CircFieldsRW F, float h) {
     const int idx = blockIdx.x * blockDim.x + threadIdx.x;
@@ -764,9 +770,10 @@ __global__ void __launch_bounds__(256) k_circ_bhalf(CircGeom g, CircFieldsRW F, 
         const float ct = (erp - Er[idx]) / g.dz - (ezu - Ez[idx]) / dr;
         (void)m;
         // defer the writes until every channel's E has been read: E is not written here
-        F.F[1][0][ch][idx] -= h * cz;
-        F.F[1][1][ch][idx] = (j == 0 && ch == 0) ? 0.0f : F.F[1][1][ch][idx] - h * cr;
-        F.F[1][2][ch][idx] -= h * ct;
+        const float bz = F.F[1][0][ch][idx], br = F.F[1][1][ch][idx], bt = F.F[1][2][ch][idx];
+        put(F.F[1][0][ch][idx], bz, bz - h * cz);
+        put(F.F[1][1][ch][idx], br, (j == 0 && ch == 0) ? 0.0f : br - h * cr);
+        put(F.F[1][2][ch][idx], bt, bt - h * ct);
     }
 }
 
@@ -812,9 +819,10 @@ __global__ void __launch_bounds__(256) k_circ_efull(CircGeom g, CircFieldsRW F, 
         float* Er = F.F[0][1][ch];
         float* Et = F.F[0][2][ch];
         const float jz = J[0 * 3 + ch][idx], jr = J[1 * 3 + ch][idx], jt = J[2 * 3 + ch][idx];
-        Ez[idx] = (j == 0 && ch != 0) ? 0.0f : Ez[idx] + g.dt * (cz - jz);
-        Er[idx] = Er[idx] + g.dt * (cr - jr);
-        Et[idx] = (j == 0 && ch == 0) ? 0.0f : Et[idx] + g.dt * (ct - jt);
+        const float ez = Ez[idx], er = Er[idx], et = Et[idx];
+        put(Ez[idx], ez, (j == 0 && ch != 0) ? 0.0f : ez + g.dt * (cz - jz));
+        put(Er[idx], er, er + g.dt * (cr - jr));
+        put(Et[idx], et, (j == 0 && ch == 0) ? 0.0f : et + g.dt * (ct - jt));
     }
 }
 
