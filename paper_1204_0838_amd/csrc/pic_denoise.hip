@@ -206,7 +206,7 @@ __global__ void __launch_bounds__(DN_THREADS) k_dn_conv32(DnArgs a) {
     auto rows = [&](auto&& f) {
         const int x = cur[0] + m;
         if (x >= a.n[0]) return;
-        const unsigned at = (unsigned)dn_axis_sel(x, a.n[0], a.bc[0], a.origin) * 64u + (unsigned)(4 * h + q) * 8u;
+        const size_t at = (size_t)dn_axis_sel(x, a.n[0], a.bc[0], a.origin) * 64 + (4 * h + q) * 8;
         const size_t base = rstep * cur[1] + pstep * (cur[2] + lz);
 #pragma unroll
         for (int p = 0; p < 2; ++p)
@@ -228,7 +228,7 @@ __global__ void __launch_bounds__(DN_THREADS) k_dn_conv32(DnArgs a) {
         dn_zero_planes(v, out);
         dn_store_act(v, lane, act);
         if (have) {
-            rows([&](int p, int r, size_t row, unsigned at) {
+            rows([&](int p, int r, size_t row, size_t at) {
                 bf16x4 o;
 #pragma unroll
                 for (int j = 0; j < 4; ++j)
@@ -242,7 +242,7 @@ __global__ void __launch_bounds__(DN_THREADS) k_dn_conv32(DnArgs a) {
 #pragma unroll
         for (int d = 0; d < 3; ++d) cur[d] = t0[d];
         if (KIND == 1)
-            rows([&](int p, int r, size_t row, unsigned at) {
+            rows([&](int p, int r, size_t row, size_t at) {
                 mk[p][r] = *reinterpret_cast<const bf16x4*>(reinterpret_cast<const char*>(a.mask) + row + at);
             });
         tile += stride;
@@ -289,7 +289,7 @@ __global__ void __launch_bounds__(64 * L3_WAVES, 2) k_dn_l3(DnArgs a, int zrun) 
     const int xw = x0 - 1 + m;
     const int xs = xw <= a.n[0] ? dn_axis_sel(xw, a.n[0], a.bc[0], a.origin) : -1;
     // a column outside the box loads some cell of its row; its partial sums are dropped below
-    const unsigned lane = (unsigned)(xs >= 0 ? xs : min(m, a.n[0] - 1)) * 64u + (unsigned)q * 16u;
+    const size_t lane = (size_t)(xs >= 0 ? xs : min(m, a.n[0] - 1)) * 64 + q * 16;
     const bool ok0 = __shfl(xs, (m + 15) & 15, 64) >= 0, ok2 = __shfl(xs, (m + 1) & 15, 64) >= 0;
     int row[L3_Y + 2];   // storage row of y0 - 1 + r, or -1
 #pragma unroll
@@ -362,6 +362,76 @@ __global__ void __launch_bounds__(64 * L3_WAVES, 2) k_dn_l3(DnArgs a, int zrun) 
         if (++z >= z1) return;
         plane(z, P4, P0, P1, P3);
         if (z + 1 >= z1) return;
+    }
+}
+
+// The 32 -> 3 layer for training: every output is one chain of sums over the
+// taps (dz, dx, dy), as gradients have been computed so far.  (k_dn_l3 adds
+// the x-taps' sums at the end, which moves y by 1e-7; the loss gradient is
+// rounded to bf16, where that shows as up to 3e-5 in the weight gradients of a
+// small crop.)  Row 4 blk + c (c < 3) of one MFMA holds output channel c of
+// row block blk: halo row r of a tap column (dz, dx) is multiplied by the
+// operand (zx, r) whose row (blk, c) carries the weight of tap (dz, r - blk,
+// dx), zero where r - blk is not a tap.  Persistent, as k_dn_conv32; weights
+// and halo in LDS (152 KB).
+constexpr int L3T_ROWS = 9 * DN_HY * 16;   // packed weight rows of 64 B
+
+__global__ void __launch_bounds__(DN_THREADS) k_dn_l3_train(DnArgs a) {
+    extern __shared__ __attribute__((aligned(16))) char act[];
+    char* wl = act + DN_ACT_LDS;
+    // 16-byte chunks of a weight row rotated so that 16 rows spread over the banks
+    auto chunk = [](int r, int c) { return r * 64 + (((c + (((r >> 1) ^ (r >> 2)) & 3)) & 3) << 4); };
+    for (int g = threadIdx.x; g < L3T_ROWS * 4; g += DN_THREADS)
+        *reinterpret_cast<uint4*>(wl + chunk(g >> 2, g & 3)) = reinterpret_cast<const uint4*>(a.w)[g];
+    int ntx, nty;
+    const int ntiles = dn_ntiles(a.n, &ntx, &nty);
+    int tile, stride, end;   // (the walk of k_dn_conv32)
+    if (gridDim.x % 8 == 0) {
+        const int per = (ntiles + 7) / 8, k = blockIdx.x % 8;
+        tile = k * per + blockIdx.x / 8;
+        stride = gridDim.x / 8;
+        end = min(ntiles, (k + 1) * per);
+    } else {
+        tile = blockIdx.x;
+        stride = gridDim.x;
+        end = ntiles;
+    }
+    if (tile >= end) return;
+    const DnLane lane = dn_lane();
+    const DnBox box = dn_box(a);
+    const float b[3] = {a.bias[0], a.bias[1], a.bias[2]};
+    const int l = threadIdx.x & 63, lz = threadIdx.x >> 6, m = l & 15, q = l >> 4;
+    const char* abase = act + (lz * DN_HY * DN_HX + m) * DN_ROWB + q * 16;
+    const char* wbase = wl + chunk(m, q);
+    uint4 v[DN_ACT_PER];
+    int t0[3];
+    dn_tile_of(tile, ntx, nty, t0);
+    unsigned out = dn_load_act(a.act_in, box, t0, lane, v);
+    while (tile < end) {
+        __syncthreads();   // the previous tile's LDS reads are done (first pass: nothing)
+        dn_zero_planes(v, out);
+        dn_store_act(v, lane, act);
+        __syncthreads();   // halo (and, first pass, weights) staged
+        const int cur[3] = {t0[0], t0[1], t0[2]};
+        tile += stride;
+        if (tile < end) {
+            dn_tile_of(tile, ntx, nty, t0);
+            out = dn_load_act(a.act_in, box, t0, lane, v);
+        }
+        f32x4 acc = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+        for (int zx = 0; zx < 9; ++zx)
+#pragma unroll
+            for (int r = 0; r < DN_HY; ++r) {
+                const bf16x8 A =
+                    *reinterpret_cast<const bf16x8*>(abase + ((zx / 3 * DN_HY + r) * DN_HX + zx % 3) * DN_ROWB);
+                const bf16x8 B = *reinterpret_cast<const bf16x8*>(wbase + (zx * DN_HY + r) * 1024);
+                acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(B, A, acc, 0, 0, 0);
+            }
+        const int cell = dn_out_cell(a, cur, lz, q, m);   // lane (m, q): cell m of row block q
+        if (cell >= 0)
+#pragma unroll
+            for (int j = 0; j < 3; ++j) a.Jout[j][cell] = acc[j] + b[j];
     }
 }
 
@@ -628,6 +698,7 @@ hipError_t launch_dn_layer(int kind, const DnArgs& a, hipStream_t st) {
         case DN_L1_C4_MASK: return dn_launch(k_dn_c4<1, 1>, a, st);
         case DN_L2_ACT: return dn_launch_persistent(k_dn_conv32<0>, DN_ACT_LDS, a, st);
         case DN_L2_MASK: return dn_launch_persistent(k_dn_conv32<1>, DN_ACT_LDS, a, st);
+        case DN_L3_TRAIN: return dn_launch_persistent(k_dn_l3_train, DN_ACT_LDS + L3T_ROWS * 64, a, st);
         case DN_L3_Y: {
             const int tx = (a.n[0] + L3_X - 1) / L3_X, ty = (a.n[1] + L3_Y * L3_WAVES - 1) / (L3_Y * L3_WAVES);
             // planes per wavefront: 16 (2 halo planes loaded), fewer where that leaves the chip with less
@@ -651,7 +722,6 @@ hipError_t launch_denoise(const Geom& g, const int bc[3], const DenoiseWeights& 
         a.bc[d] = bc[d];
         a.J[d] = Jin[d];
         a.Jcopy[d] = Jcopy ? Jcopy[d] : nullptr;
-        a.scale[d] = w.scale[d];
         a.inv_scale[d] = 1.0f / w.scale[d];
     }
     a.origin = g.window ? g.origin : 0;

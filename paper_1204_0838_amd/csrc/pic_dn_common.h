@@ -19,7 +19,8 @@
 // z-plane, 4 rows of 16 cells, and all 32 output channels; layer 2: two planes
 // and 16 channels, accumulated over the 27 taps x 32 input channels (one MFMA
 // K-step of 32 per tap).  Layer 3 streams its input from HBM straight into the
-// MFMA operands (k_dn_l3).
+// MFMA operands (k_dn_l3); training keeps one chain of sums per output there
+// (k_dn_l3_train).
 //
 // MFMA operand layout (16x16x32): lane l holds row l%16 of the first operand,
 // K elements 8(l/16)..8(l/16)+7, and column l%16 of the second with the same K
@@ -65,26 +66,22 @@ struct DnArgs {
     int n[3];
     int bc[3];
     int origin;
-    const float* J[3];        // layer 1 input; layer 3 residual input
+    const float* J[3];        // layer 1 input
     float* Jcopy[3];          // (or null) layer 1 writes its J here as well
     float* Jout[3];           // layer 3 output
     const __bf16* act_in;     // 32-channel input [cell][32]
     __bf16* act_out;          // 32-channel output [cell][32]
     const __bf16* w;          // packed weights (see the host packing)
     const float* bias;
-    float scale[3], inv_scale[3];
+    float inv_scale[3];
     // training
     const __bf16* c4_in;      // 4-channel input [cell][4] (output gradient of layer 3)
     const __bf16* mask;       // relu mask source [cell][32] (an activation: > 0 passes)
-    const float* Jt[3];       // target current
-    __bf16* c4_out;           // 4-channel output [cell][4] (loss gradient of y)
-    double* loss;             // += sum of squared errors / (3 N)
-    float grad_scale;         // 2 / (3 N)
 };
 
 // Kernel variants: input of the 4-channel-input shape, and epilogues.
-// DN_L3_Y writes y = conv(a2, W3) + b3 as FP32 components into Jout.
-enum { DN_L1_J_ACT = 0, DN_L1_C4_MASK, DN_L2_ACT, DN_L2_MASK, DN_L3_Y };
+// DN_L3_* write y = conv(a2, W3) + b3 as FP32 components into Jout.
+enum { DN_L1_J_ACT = 0, DN_L1_C4_MASK, DN_L2_ACT, DN_L2_MASK, DN_L3_Y, DN_L3_TRAIN };
 
 // Output stage J' = B(J + sigma curl(y)) (backward-difference curl, binomial
 // filter B), and for training the loss against a target and the gradient.

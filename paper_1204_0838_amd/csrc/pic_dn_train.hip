@@ -277,9 +277,10 @@ constexpr int kP_W1 = 0, kP_W2 = kP_W1 + 32 * 3 * 27, kP_W3 = kP_W2 + 32 * 32 * 
 // Gradient buffers (FP32): dW1 [32][112], dW2 [32][864], dW3 [16][864] (rows < 4 used), db1 [32], db2 [32], db3 [4]
 constexpr int kG_W1 = 0, kG_W2 = kG_W1 + 32 * 112, kG_W3 = kG_W2 + 32 * 864, kG_B1 = kG_W3 + 16 * 864,
               kG_B2 = kG_B1 + 32, kG_B3 = kG_B2 + 32, kG_N = kG_B3 + 4;
-// bf16 packs: forward W1p [32][128], W2p [27][32][32], W3p [9 (dz, dy)][16: 4 dx + co][32];
+// bf16 packs: forward W1p [32][128], W2p [27][32][32], W3p [9 zx][6 r][16: 4 blk + co][32]
+// (operand (zx, r), row 4 blk + co: tap (dz, r - blk, dx));
 // backward W3T [32][128] (k = tap * 4 + c: W3[c][co][26 - tap]), W2T [27][32][32] (W2[ci][co][26 - t])
-constexpr int kK_W1 = 0, kK_W2 = kK_W1 + 32 * 128, kK_W3 = kK_W2 + 27 * 32 * 32, kK_W3T = kK_W3 + 9 * 16 * 32,
+constexpr int kK_W1 = 0, kK_W2 = kK_W1 + 32 * 128, kK_W3 = kK_W2 + 27 * 32 * 32, kK_W3T = kK_W3 + 9 * 6 * 16 * 32,
               kK_W2T = kK_W3T + 32 * 128, kK_N = kK_W2T + 27 * 32 * 32;
 // FP32 biases of the kernels: b1 [32], b2 [32], b3 [16]
 constexpr int kB_N = 80;
@@ -329,7 +330,10 @@ __global__ void k_dn_adam_pack(float* __restrict__ P, float* __restrict__ M, flo
         K[kK_W2T + ((26 - t) * 32 + ci) * 32 + co] = b;
     } else if (i < kP_B1) {
         const int j = i - kP_W3, co = j / 864, r = j % 864, ci = r / 27, t = r % 27;
-        K[kK_W3 + (t / 3 * 16 + t % 3 * 4 + co) * 32 + ci] = b;
+        const int dz = t / 9, dy = (t / 3) % 3, dx = t % 3;
+#pragma unroll
+        for (int blk = 0; blk < 4; ++blk)
+            K[kK_W3 + (((dz * 3 + dx) * 6 + blk + dy) * 16 + blk * 4 + co) * 32 + ci] = b;
         K[kK_W3T + ci * 128 + (26 - t) * 4 + co] = b;
     } else if (i < kP_B2) {
         Bk[i - kP_B1] = p;
@@ -436,20 +440,15 @@ T* at(pic_dn_trainer* t, size_t off) {
     return reinterpret_cast<T*>(t->ws + off);
 }
 
-DnArgs base_args(pic_dn_trainer* t, float* const in[3], float* const target[3]) {
+DnArgs base_args(pic_dn_trainer* t, float* const in[3]) {
     DnArgs a{};
     for (int d = 0; d < 3; ++d) {
         a.n[d] = t->n[d];
         a.bc[d] = 1;
         a.J[d] = in[d];
-        a.Jt[d] = target ? target[d] : nullptr;
-        a.scale[d] = t->scale[d];
         a.inv_scale[d] = 1.0f / t->scale[d];
     }
     a.origin = 0;
-    a.loss = at<double>(t, t->L.loss);
-    const double N = (double)t->n[0] * t->n[1] * t->n[2];
-    a.grad_scale = (float)(2.0 / (3.0 * N));
     return a;
 }
 
@@ -479,7 +478,7 @@ pic_status tr_grad(pic_dn_trainer* t, float* const in[3], float* const target[3]
     __bf16 *a1 = at<__bf16>(t, t->L.a1), *a2 = at<__bf16>(t, t->L.a2), *dy = at<__bf16>(t, t->L.dy);
     __bf16 *dz2 = at<__bf16>(t, t->L.dz2), *dz1 = at<__bf16>(t, t->L.dz1);
     float* G = at<float>(t, t->L.G);
-    DnArgs a = base_args(t, in, target);
+    DnArgs a = base_args(t, in);
     // forward
     a.w = K + kK_W1, a.bias = Bk, a.act_out = a1;
     THIPCHK(t, launch_dn_layer(DN_L1_J_ACT, a, t->st));
@@ -490,7 +489,7 @@ pic_status tr_grad(pic_dn_trainer* t, float* const in[3], float* const target[3]
     float* gJ = at<float>(t, t->L.g);
     a.w = K + kK_W3, a.bias = Bk + 64, a.act_in = a2, a.act_out = nullptr;
     for (int d = 0; d < 3; ++d) a.Jout[d] = y + d * N;
-    THIPCHK(t, launch_dn_layer(DN_L3_Y, a, t->st));
+    THIPCHK(t, launch_dn_layer(DN_L3_TRAIN, a, t->st));
     // J' = B(J + sigma curl(y));  loss;  g = dL/dJ';  dy = sigma curl^T(B g)
     DnCombine c{};
     for (int d = 0; d < 3; ++d) {
@@ -504,8 +503,8 @@ pic_status tr_grad(pic_dn_trainer* t, float* const in[3], float* const target[3]
         c.inv_d[d] = (float)(1.0 / t->cell[d]);
     }
     c.sigma = (float)(t->cell[0] * ((double)t->scale[0] + t->scale[1] + t->scale[2]) / 3.0);
-    c.grad_scale = a.grad_scale;
-    c.loss = a.loss;
+    c.grad_scale = (float)(2.0 / (3.0 * ((double)t->n[0] * t->n[1] * t->n[2])));
+    c.loss = at<double>(t, t->L.loss);
     c.dy = dy;
     THIPCHK(t, launch_dn_output(c, true, t->st));
     if (forward_only) return PIC_OK;
