@@ -269,7 +269,9 @@ pic_status pic_step(pic_ctx *ctx, int32_t nsteps);
 pic_status pic_sort(pic_ctx *ctx, int32_t species);
 
 /* Current device arrays and live count of a species (host struct out).
- * Synchronises the stream and reports device-side errors. */
+ * Synchronises the stream and reports device-side errors.  The arrays that
+ * hold the data may be written between two calls, in stream order (cells
+ * anywhere in the grid): the next call takes the particles as it finds them. */
 pic_status pic_species_view(pic_ctx *ctx, int32_t species, pic_species_bufs *out, int64_t *n_live);
 
 /* Continuity check of the last gather_push/deposit pair (the charge

@@ -18,7 +18,6 @@ using namespace pic;
 
 namespace {
 
-constexpr int kMaxSpecies = 8;
 constexpr size_t kAlign = 256;
 constexpr int kKillMargin = 3;   // window cells behind which particles are removed
 constexpr size_t kMaxLds = 160 * 1024;
@@ -179,8 +178,6 @@ struct Species {
     int64_t sort_step;       // step of the last sort
     bool sorted;             // tile ranges valid
     bool appended = false;   // particles may have been added since the last sort
-    bool loose = false;      // particles may have moved other than by pic_step's steps since then
-                             // (the staged path, or a caller that was handed the arrays)
     bool prev_valid;         // x^n of the last split gather_push kept
 };
 
@@ -288,6 +285,8 @@ struct pic_ctx {
     bool mid_step = false;
     // the accumulator may hold contributions (it is zero between whole steps)
     bool acc_used = false;
+    // the rest lists may have entries (a batch step, or a step that failed; they are empty after a whole step)
+    bool rest_used = false;
     // the J planes hold the post-processed current (binomial or denoiser
     // output) rather than the raw deposit: the continuity check filters rho
     bool j_filtered = false;
@@ -488,7 +487,8 @@ pic_status field_update(pic_ctx* c, float* const J[3], float* const Jcopy[3], un
     const PmlDev* pml = c->g.pml ? &c->pml : nullptr;
     HIPCHK(c, launch_bhalf(c->g, pd, c->pd, f.E, f.B, (float)(0.5 * dt), pml, 1, c->stream));
     if (laser) PICCHK(laser_plane(c, false, 0.5 * dt, t));
-    HIPCHK(c, launch_efull(c->g, f.E, f.B, J, Jcopy, acc, scale, pml, c->stream));
+    HIPCHK(c, launch_efull(c->g, f.E, f.B, J, Jcopy, acc, scale, small_of(c)->rest_n, pml, c->stream));
+    c->rest_used = false;
     if (laser) PICCHK(laser_plane(c, true, dt, t + 0.5 * dt));
     HIPCHK(c, launch_bhalf(c->g, pd, c->pd, f.E, f.B, (float)(0.5 * dt), pml, 0, c->stream));
     if (laser) PICCHK(laser_plane(c, false, 0.5 * dt, t + dt));
@@ -561,7 +561,7 @@ pic_status sort_species(pic_ctx* c, int32_t s, bool copy) {
                           toff_of(c, s), copy, sp.sorted, sp.appended, c->stream));
     std::swap(sp.cur, sp.alt);
     sp.sorted = true;
-    sp.appended = sp.loose = false;
+    sp.appended = false;
     sp.sort_step = c->step;
     sp.prev_valid = false;
     return PIC_OK;
@@ -914,11 +914,11 @@ pic_status batch_one_step(pic_batch* b) {
                 max_tcells = std::max(max_tcells, c->tl.t.tcells);
                 std::swap(sp.cur, sp.alt);
                 sp.sorted = true;
-                sp.appended = sp.loose = false;
+                sp.appended = false;
                 sp.sort_step = c->step;
             }
             sp.prev_valid = false;
-            c->acc_used = true;
+            c->acc_used = c->rest_used = true;
             lds = std::max(lds, tile_lds_bytes(c->tl.t, c->tl.guard));
             all_888g1 = all_888g1 && c->tl.t.T[0] == 8 && c->tl.t.T[1] == 8 && c->tl.t.T[2] == 8 && c->tl.guard == 1;
         }
@@ -1169,7 +1169,6 @@ pic_status pic_gather_push(pic_ctx* c, int32_t s) {
                                      &small_of(c)->err, c->stream));
     }
     sp.prev_valid = true;
-    sp.loose = true;
     c->mid_step = true;
     return PIC_OK;
 }
@@ -1217,6 +1216,7 @@ pic_status pic_field_step(pic_ctx* c) {
 pic_status pic_step(pic_ctx* c, int32_t nsteps) {
     if (!c || nsteps < 0) return PIC_EINVAL;
     for (int32_t it = 0; it < nsteps; ++it) {
+        if (c->rest_used) HIPCHK(c, launch_zero_rest(small_of(c)->rest_n, kMaxSpecies, c->stream));
         for (int32_t s = 0; s < (int32_t)c->sp.size(); ++s) {
             Species& sp = c->sp[s];
             if (sp.bound == 0) {            // no particle can exist: nothing to sort, push or deposit
@@ -1234,24 +1234,23 @@ pic_status pic_step(pic_ctx* c, int32_t nsteps) {
             }
             c->acc_used = true;
             Small* sm = small_of(c);
+            c->rest_used = true;
             PICCHK(prof_mark(c, &t1));
             int* rest_idx = reinterpret_cast<int*>(c->ws + c->L.sort_rank) + sp.base;
             const SpeciesDev pre = dev_from(c, sp, sp.alt);   // the pre-sort set after a sort
-            // a particle moves less than a cell per step, so those in tile ranges
-            // stay within the guard for `guard` steps after a sort; with none
-            // appended either, there is nothing for a rest pass
-            const bool rest = sp.appended || sp.loose || c->step - sp.sort_step > c->tl.guard;
             HIPCHK(c, launch_pic_tile(c->g, c->tl.t, c->tl.guard, c->tl.threads, (int)sp.bound, fields_of(c),
                                       dev_of(c, sp), gather ? &pre : nullptr, toff_of(c, s), acc_of(c), &sm->err,
-                                      &sm->rest_n[s], rest_idx, rest, c->stream));
+                                      &sm->rest_n[s], rest_idx, c->stream));
             PICCHK(prof_end(c, PH_TILE, t1));
             if (c->prof.on) c->prof.tiles += 1;
-            if (rest) {
-                PICCHK(prof_mark(c, &t2));
-                HIPCHK(c, launch_tile_rest(c->g, fields_of(c), dev_of(c, sp), &sm->sorted[s], &sm->count[s],
-                                           &sm->rest_n[s], rest_idx, acc_of(c), &sm->err, c->stream));
-                PICCHK(prof_end(c, PH_LOOSE, t2));
-            }
+            // A particle moves less than a cell per step: with none appended, the rest list is
+            // empty for `guard` steps after a sort, unless the arrays were written meanwhile or
+            // this launch is replayed in a graph (so the pass always runs: 64 workgroups then)
+            const bool few = !sp.appended && c->step - sp.sort_step <= c->tl.guard;
+            PICCHK(prof_mark(c, &t2));
+            HIPCHK(c, launch_tile_rest(c->g, fields_of(c), dev_of(c, sp), &sm->sorted[s], &sm->count[s],
+                                       &sm->rest_n[s], rest_idx, acc_of(c), &sm->err, few, c->stream));
+            PICCHK(prof_end(c, PH_LOOSE, t2));
             sp.prev_valid = false;
         }
         PICCHK(finish_step(c));
@@ -1269,7 +1268,6 @@ pic_status pic_species_view(pic_ctx* c, int32_t s, pic_species_bufs* out, int64_
     int cnt = 0;
     HIPCHK(c, hipMemcpyAsync(&cnt, &small_of(c)->count[s], sizeof(int), hipMemcpyDeviceToHost, c->stream));
     pic_status st = device_errors(c);
-    c->sp[s].loose = true;
     if (out) *out = c->sp[s].cur;
     if (n_live) *n_live = cnt;
     return st;

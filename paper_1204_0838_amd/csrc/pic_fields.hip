@@ -340,6 +340,7 @@ struct JSource {
     unsigned long long* acc;
     float* J[3];
     double scale[3];
+    int* rest_n;   // the species' rest-list counters (their passes are over): emptied on the way
 };
 // (Reading the accumulator here saves a read of J and a launch: 512x256x256
 // cells 634 -> 528 us together, 6.1 TB/s.)
@@ -411,6 +412,7 @@ __global__ void __launch_bounds__(256) k_efull(Geom g, float* __restrict__ Ex, f
                                                PmlDev P) {
     const int idx = blockIdx.x * blockDim.x + threadIdx.x;
     if (idx >= g.ncell) return;
+    if (idx < kMaxSpecies) js.rest_n[idx] = 0;   // (a grid has 64 cells at least)
     efull_cell<PML, SRC>(g, Ex, Ey, Ez, Bx, By, Bz, js, idx, &P);
 }
 
@@ -597,7 +599,7 @@ hipError_t launch_bhalf(const Geom& g, int pd, const PDCoef& c, float* const E[3
 }
 
 hipError_t launch_efull(const Geom& g, float* const E[3], float* const B[3], float* const J[3], float* const Jcopy[3],
-                        unsigned long long* acc, const double* scale, const PmlDev* pml, hipStream_t st) {
+                        unsigned long long* acc, const double* scale, int* rest_n, const PmlDev* pml, hipStream_t st) {
     const int nb = (g.ncell + 255) / 256;
     const PmlDev P = pml ? *pml : PmlDev{};
     JSource js{};
@@ -607,6 +609,7 @@ hipError_t launch_efull(const Geom& g, float* const E[3], float* const B[3], flo
         if (scale) js.scale[a] = scale[a];
     }
     js.acc = acc;
+    js.rest_n = rest_n;
     auto k = acc && scale ? (pml ? k_efull<true, J_ACC> : k_efull<false, J_ACC>)
              : acc        ? (pml ? k_efull<true, J_CLEAR> : k_efull<false, J_CLEAR>)
                  : Jcopy ? (pml ? k_efull<true, J_COPY> : k_efull<false, J_COPY>)

@@ -9,6 +9,8 @@
 
 namespace pic {
 
+constexpr int kMaxSpecies = 8;
+
 struct FieldPtrs {
     float* E[3];
     float* B[3];
@@ -223,21 +225,20 @@ hipError_t launch_sort(const Geom& g, const TileGeom& t, const SpeciesDev& src, 
 // fused tile kernel (pic_tile.hip)
 size_t tile_lds_bytes(const TileGeom& t, int guard);
 // toff: tile ranges of the species' last sort
-// rest_n / rest_idx: the species' rest list (counter zeroed here, indices appended by the kernel)
+// rest_n / rest_idx: the species' rest list (empty before; indices appended by the kernel)
 // src: null, or the pre-sort arrays when the sort ran without its copy pass
 // (s.cell then holds source indices; the step writes every array of s)
 // threads: per workgroup, 0 = by the tiles' population; max_count: the host's bound of the particles
-// rest: a rest pass follows (false: no particle can be beyond the guard)
 hipError_t launch_pic_tile(const Geom& g, const TileGeom& t, int guard, int threads, int max_count,
                            const FieldPtrs& f, const SpeciesDev& s, const SpeciesDev* src, const int* toff,
-                           unsigned long long* acc, int* d_err, int* rest_n, int* rest_idx, bool rest,
-                           hipStream_t st);
+                           unsigned long long* acc, int* d_err, int* rest_n, int* rest_idx, hipStream_t st);
+hipError_t launch_zero_rest(int* rest_n, int n, hipStream_t st);
 // rest pass after the tile kernel: the particles on its rest list (beyond
 // their tile's guard, marked cell -2 - c) and those appended after the last
-// sort (index >= sorted)
+// sort (index >= sorted); few: hardly any are expected
 hipError_t launch_tile_rest(const Geom& g, const FieldPtrs& f, const SpeciesDev& s, const int* d_sorted,
                             const int* d_count, const int* rest_n, const int* rest_idx, unsigned long long* acc,
-                            int* d_err, hipStream_t st);
+                            int* d_err, bool few, hipStream_t st);
 
 // field kernels (pic_fields.hip)
 // pml: nullptr without the absorbing layer; store: the first of a step's two
@@ -245,9 +246,10 @@ hipError_t launch_tile_rest(const Geom& g, const FieldPtrs& f, const SpeciesDev&
 hipError_t launch_bhalf(const Geom& g, int pd, const PDCoef& c, float* const E[3], float* const B[3], float h,
                         const PmlDev* pml, int store, hipStream_t st);
 // Where its current is: J (scale null; with Jcopy it is stored there too), or
-// acc times scale, stored to J.  acc not null: cleared.
+// acc times scale, stored to J.  acc not null: cleared.  rest_n: the kMaxSpecies
+// rest-list counters, set to zero.
 hipError_t launch_efull(const Geom& g, float* const E[3], float* const B[3], float* const J[3], float* const Jcopy[3],
-                        unsigned long long* acc, const double* scale, const PmlDev* pml, hipStream_t st);
+                        unsigned long long* acc, const double* scale, int* rest_n, const PmlDev* pml, hipStream_t st);
 hipError_t launch_clear_pml_plane(const Geom& g, const PmlDev& P, int ix, hipStream_t st);
 // src null: the source is acc times scale (left as it is)
 hipError_t launch_binomial(const Geom& g, float* const src[3], const unsigned long long* acc, const double scale[3],

@@ -450,12 +450,7 @@ __device__ __forceinline__ void tile_body(const Geom& g, const TileGeom& t, int 
                 lc[d] = l;
                 inside = inside && l >= -guard && l < te[d] + guard;
             }
-            if (!inside && rest_idx == nullptr) {   // (only if cells were changed behind the library's back)
-                errs |= ERR_OVERFLOW;
-                if (GATHER) s.cell[p] = cell;
-                keep_particle<GATHER>(s, p, o, u);
-                go = false;
-            } else if (!inside) {   // beyond the guard: the rest pass takes it
+            if (!inside) {   // beyond the guard: the rest pass takes it
                 s.cell[p] = -2 - cell;
                 keep_particle<GATHER>(s, p, o, u);
                 const unsigned long long m = __ballot(1);   // the lanes in this branch
@@ -784,9 +779,9 @@ __global__ void __launch_bounds__(kRestThreads) k_batch_rest(const InstDesc* __r
         rest_item(g, f, s, i, nrest, sorted, d.rank, d.acc, d.err);
 }
 
-// Rest-list counters start at zero before each tile launch (a kernel, not a
-// memset, so that a captured step stays valid).
-__global__ void k_zero_rest(int* rest_n) { *rest_n = 0; }
+// Empty the species' rest lists (a kernel, not a memset, so that a captured
+// step stays valid).
+__global__ void k_zero_rest(int* rest_n) { rest_n[threadIdx.x] = 0; }
 
 __global__ void k_batch_zero_rest(const InstDesc* __restrict__ tab, int n) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
@@ -811,7 +806,6 @@ struct TileLaunch {
     const int* toff;
     unsigned long long* acc;
     int *d_err, *rest_n, *rest_idx;
-    bool rest;   // particles beyond the guard are possible (the rest list starts empty)
     hipStream_t st;
 };
 
@@ -822,10 +816,8 @@ static hipError_t launch_tile_k(const TileLaunch& L) {
     hipError_t e = hipFuncSetAttribute((const void*)k_pic_tile<NT, TX, TY, TZ, GD, GATHER>,
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
-    if (L.rest) hipLaunchKernelGGL(k_zero_rest, dim3(1), dim3(1), 0, L.st, L.rest_n);
     hipLaunchKernelGGL((k_pic_tile<NT, TX, TY, TZ, GD, GATHER>), dim3(nb, L.parts), dim3(NT), lds, L.st, L.g, L.t,
-                       L.guard, L.f, L.s, GATHER ? *L.src : L.s, L.toff, L.acc, L.d_err, L.rest_n,
-                       L.rest ? L.rest_idx : nullptr);
+                       L.guard, L.f, L.s, GATHER ? *L.src : L.s, L.toff, L.acc, L.d_err, L.rest_n, L.rest_idx);
     return hipGetLastError();
 }
 
@@ -868,10 +860,9 @@ static int tile_parts(int ntiles, int64_t count) {
 
 hipError_t launch_pic_tile(const Geom& g, const TileGeom& t, int guard, int threads, int max_count,
                            const FieldPtrs& f, const SpeciesDev& s, const SpeciesDev* src, const int* toff,
-                           unsigned long long* acc, int* d_err, int* rest_n, int* rest_idx, bool rest,
-                           hipStream_t st) {
+                           unsigned long long* acc, int* d_err, int* rest_n, int* rest_idx, hipStream_t st) {
     const int parts = tile_parts(t.ntiles, max_count);
-    const TileLaunch L{g, t, guard, parts, f, s, src, toff, acc, d_err, rest_n, rest_idx, rest, st};
+    const TileLaunch L{g, t, guard, parts, f, s, src, toff, acc, d_err, rest_n, rest_idx, st};
     switch (threads > 0 ? threads : kTileThreads) {
         case 256: return launch_tile_shape<256>(L);
         case 1024: return launch_tile_shape<1024>(L);
@@ -916,11 +907,16 @@ hipError_t launch_batch_rest(const InstDesc* d, int n, hipStream_t st) {
     return hipGetLastError();
 }
 
+hipError_t launch_zero_rest(int* rest_n, int n, hipStream_t st) {
+    hipLaunchKernelGGL(k_zero_rest, dim3(1), dim3(n), 0, st, rest_n);
+    return hipGetLastError();
+}
+
 hipError_t launch_tile_rest(const Geom& g, const FieldPtrs& f, const SpeciesDev& s, const int* d_sorted,
                             const int* d_count, const int* rest_n, const int* rest_idx, unsigned long long* acc,
-                            int* d_err, hipStream_t st) {
-    hipLaunchKernelGGL(k_tile_rest, dim3(1024), dim3(kRestThreads), 0, st, g, f, s, d_sorted, d_count, rest_n,
-                       rest_idx, acc, d_err);
+                            int* d_err, bool few, hipStream_t st) {
+    hipLaunchKernelGGL(k_tile_rest, dim3(few ? 64 : 1024), dim3(kRestThreads), 0, st, g, f, s, d_sorted, d_count,
+                       rest_n, rest_idx, acc, d_err);
     return hipGetLastError();
 }
 
