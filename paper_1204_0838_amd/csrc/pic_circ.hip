@@ -598,8 +598,13 @@ __global__ void __launch_bounds__(NT) k_circ_tile(CircGeom g, CircFields F, Spec
             rest_idx[atomicAdd(rest_n, 1)] = i;
             continue;
         }
-        if (cold && (__float_as_int(p0.u[0]) | __float_as_int(p0.u[1]) | __float_as_int(p0.u[2])) == 0) {
+        // (an offset in [0, 1) and a radius that is a number: anything else goes
+        // through the push, which carries or reports it)
+        if (cold && (__float_as_int(p0.u[0]) | __float_as_int(p0.u[1]) | __float_as_int(p0.u[2])) == 0 &&
+            (unsigned)__float_as_int(p0.oz) < 0x3f800000u && rr == rr) {
             p1 = p0;
+            p1.x = p0.x + 0.0f;   // (as the push: -0 becomes +0)
+            p1.y = p0.y + 0.0f;
             p1.jr = K;
             store_changed(s, i, g, p0, p1, cl, circ_removed(g, p1));
             continue;
