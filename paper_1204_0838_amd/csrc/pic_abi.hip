@@ -283,6 +283,10 @@ struct pic_ctx {
     Prof prof;
     // a split-path step is in progress (pic_gather_push since the last pic_field_step)
     bool mid_step = false;
+    // a call of this context was recorded into a graph: replays change the
+    // device's state without the host's knowledge, so that from then on nothing
+    // is left out because of the flags here and in Species (see recording)
+    bool recorded = false;
     // the accumulator may hold contributions (it is zero between whole steps)
     bool acc_used = false;
     // the rest lists may have entries (a batch step, or a step that failed; they are empty after a whole step)
@@ -504,6 +508,15 @@ pic_status refresh_bound(pic_ctx* c, int32_t s) {
     return PIC_OK;
 }
 
+// Whether this call is being recorded, or an earlier one was.
+bool recording(pic_ctx* c) {
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(c->stream, &st) != hipSuccess)
+        (void)hipGetLastError();   // (the call's own launches report what is wrong)
+    c->recorded = c->recorded || st != hipStreamCaptureStatusNone;
+    return c->recorded;
+}
+
 pic_status inject_slab(pic_ctx* c, int32_t s, int32_t xb, int32_t xe) {
     Species& sp = c->sp[s];
     const PlasmaDev& P = c->plasma[s];
@@ -519,6 +532,7 @@ pic_status inject_slab(pic_ctx* c, int32_t s, int32_t xb, int32_t xe) {
                             (int)sp.user.capacity, &small_of(c)->err, c->stream));
     sp.bound += most;
     sp.appended = true;
+    (void)recording(c);
     return PIC_OK;
 }
 
@@ -558,7 +572,7 @@ pic_status sort_species(pic_ctx* c, int32_t s, bool copy) {
     HIPCHK(c, launch_sort(c->g, c->tl.t, dev_from(c, sp, sp.cur), dev_from(c, sp, sp.alt), &sm->count[s],
                           &sm->sorted[s], (int)sp.bound, hist_of(c), rank, reinterpret_cast<int*>(c->ws + c->L.sums),
                           level_of(c, sp), reinterpret_cast<int*>(c->ws + c->L.sort_lc), c->tl.interleave,
-                          toff_of(c, s), copy, sp.sorted, sp.appended, c->stream));
+                          toff_of(c, s), copy, sp.sorted, sp.appended || recording(c), c->stream));
     std::swap(sp.cur, sp.alt);
     sp.sorted = true;
     sp.appended = false;
@@ -1177,6 +1191,7 @@ pic_status pic_deposit(pic_ctx* c, int32_t s) {
     PICCHK(check_species(c, s));
     Species& sp = c->sp[s];
     if (!sp.prev_valid) return fail(c, PIC_ESTATE, "deposit needs a preceding gather_push");
+    (void)recording(c);
     c->acc_used = true;
     if (sp.bound > kDepositTilesMin + c->g.ncell / 128) {
         // (by the old cells: also a particle that the window has since left behind)
@@ -1207,7 +1222,7 @@ pic_status pic_field_step(pic_ctx* c) {
         PICCHK(field_update(c, tmp, c->f.J, nullptr, nullptr));
         c->j_filtered = true;
     }
-    if (c->acc_used) HIPCHK(c, launch_zero_u64(acc_of(c), 3 * (int64_t)c->g.ncell, c->stream));
+    if (recording(c) || c->acc_used) HIPCHK(c, launch_zero_u64(acc_of(c), 3 * (int64_t)c->g.ncell, c->stream));
     c->acc_used = false;
     c->mid_step = false;
     return end_step(c);
@@ -1216,7 +1231,7 @@ pic_status pic_field_step(pic_ctx* c) {
 pic_status pic_step(pic_ctx* c, int32_t nsteps) {
     if (!c || nsteps < 0) return PIC_EINVAL;
     for (int32_t it = 0; it < nsteps; ++it) {
-        if (c->rest_used) HIPCHK(c, launch_zero_rest(small_of(c)->rest_n, kMaxSpecies, c->stream));
+        if (recording(c) || c->rest_used) HIPCHK(c, launch_zero_rest(small_of(c)->rest_n, kMaxSpecies, c->stream));
         for (int32_t s = 0; s < (int32_t)c->sp.size(); ++s) {
             Species& sp = c->sp[s];
             if (sp.bound == 0) {            // no particle can exist: nothing to sort, push or deposit
