@@ -145,6 +145,34 @@ __device__ __forceinline__ void esirkepov(const Axis5 A[3], float qw, Emit& em) 
     }
 }
 
+// Emitter of deposit contributions into the global fixed-point accumulator.
+struct GlobalEmit {
+    unsigned long long* acc;
+    int ncell;
+    int X[5], Y[5], Z[5];
+    __device__ __forceinline__ void add(int comp, int jx, int jy, int jz, long long k) const {
+        atomicAdd(acc + ((size_t)comp * ncell + X[jx] + Y[jy] + Z[jz]), (unsigned long long)k);
+    }
+};
+
+// One particle's move into the global accumulator.
+__device__ __forceinline__ void deposit_global(const Geom& g, const int c0[3], const int c1[3], const float o0[3],
+                                               const float o1[3], float wq, unsigned long long* acc) {
+    const int stride[3] = {1, g.n[0], g.nxy};
+    Axis5 A[3];
+    GlobalEmit em;
+    em.acc = acc;
+    em.ncell = g.ncell;
+#pragma unroll
+    for (int d = 0; d < 3; ++d) {
+        axis5(unwrap_shift(c1[d] - c0[d], g.n[d]), o0[d], o1[d], A[d]);
+        int* dst = d == 0 ? em.X : (d == 1 ? em.Y : em.Z);
+#pragma unroll
+        for (int j = 0; j < 5; ++j) dst[j] = wrapi(c0[d] + A[d].base + j, g.n[d]) * stride[d];
+    }
+    esirkepov(A, wq, em);
+}
+
 // The same contributions in slots relative to the old cell, for the LDS
 // deposits.  Along an axis transverse to the component, core slots 0..3 are
 // the nodes at cell - 1 .. cell + 2 whatever the crossing, and slot 4 is the

@@ -51,16 +51,6 @@ __global__ void __launch_bounds__(256) k_gather_push(Geom g, FieldPtrs f, Specie
     s.cell[p] = c[0] + g.n[0] * (c[1] + g.n[1] * c[2]);
 }
 
-// Emitter of deposit contributions into the global fixed-point accumulator.
-struct GlobalEmit {
-    unsigned long long* acc;
-    int ncell;
-    int X[5], Y[5], Z[5];
-    __device__ __forceinline__ void add(int comp, int jx, int jy, int jz, long long k) const {
-        atomicAdd(acc + ((size_t)comp * ncell + X[jx] + Y[jy] + Z[jz]), (unsigned long long)k);
-    }
-};
-
 __global__ void __launch_bounds__(256) k_deposit(Geom g, SpeciesDev s, PrevDev prev,
                                                  const int* __restrict__ d_count,
                                                  unsigned long long* __restrict__ acc) {
@@ -74,20 +64,7 @@ __global__ void __launch_bounds__(256) k_deposit(Geom g, SpeciesDev s, PrevDev p
     const float o0[3] = {prev.off[0][p], prev.off[1][p], prev.off[2][p]};
     const float o1[3] = {s.off[0][p], s.off[1][p], s.off[2][p]};
     if (!moved(c0, c1, o0, o1)) return;
-    Axis5 A[3];
-    GlobalEmit em;
-    em.acc = acc;
-    em.ncell = g.ncell;
-    const int stride[3] = {1, g.n[0], g.nxy};
-#pragma unroll
-    for (int d = 0; d < 3; ++d) {
-        const int di = unwrap_shift(c1[d] - c0[d], g.n[d]);
-        axis5(di, o0[d], o1[d], A[d]);
-        int* dst = d == 0 ? em.X : (d == 1 ? em.Y : em.Z);
-#pragma unroll
-        for (int j = 0; j < 5; ++j) dst[j] = wrapi(c0[d] + A[d].base + j, g.n[d]) * stride[d];
-    }
-    esirkepov(A, s.mq * s.w[p], em);
+    deposit_global(g, c0, c1, o0, o1, s.mq * s.w[p], acc);
 }
 
 __global__ void k_jfinal(unsigned long long* __restrict__ acc, float* J0, float* J1, float* J2, int ncell,

@@ -67,15 +67,6 @@ struct LdsCrossing {
     }
 };
 
-struct GlobalEmitT {
-    unsigned long long* acc;
-    int ncell;
-    int X[5], Y[5], Z[5];
-    __device__ __forceinline__ void add(int comp, int jx, int jy, int jz, long long k) const {
-        atomicAdd(acc + ((size_t)comp * ncell + X[jx] + Y[jy] + Z[jz]), (unsigned long long)k);
-    }
-};
-
 // Tile of workgroup b when chunks of `chunk` consecutive tiles are dealt
 // round-robin to the 8 XCDs (>= ntiles: no tile; grid = xcd_blocks).
 // v mod n in [0, n) for any v; a single compare when v is already inside
@@ -126,19 +117,7 @@ __device__ __forceinline__ int push_deposit_global(const Geom& g, const FieldPtr
         s.off[d][p] = o[d];
     }
     s.cell[p] = c1[0] + g.n[0] * (c1[1] + g.n[1] * c1[2]);
-    if (!moved(c, c1, o0, o)) return errs;
-    Axis5 A[3];
-    GlobalEmitT em;
-    em.acc = acc;
-    em.ncell = g.ncell;
-#pragma unroll
-    for (int d = 0; d < 3; ++d) {
-        axis5(unwrap_shift(c1[d] - c[d], g.n[d]), o0[d], o[d], A[d]);
-        int* dst = d == 0 ? em.X : (d == 1 ? em.Y : em.Z);
-#pragma unroll
-        for (int j = 0; j < 5; ++j) dst[j] = wrapi(c[d] + A[d].base + j, g.n[d]) * gstride[d];
-    }
-    esirkepov(A, s.mq * s.w[p], em);
+    if (moved(c, c1, o0, o)) deposit_global(g, c, c1, o0, o, s.mq * s.w[p], acc);
     return errs;
 }
 
@@ -557,10 +536,15 @@ __global__ void __launch_bounds__(NT) k_batch_tile(const InstDesc* __restrict__ 
 // LDS bound it now).
 constexpr int kDepTile = 8, kDepThreads = 512;
 
-__global__ void __launch_bounds__(kDepThreads) k_deposit_tiles(Geom g, TileGeom t, SpeciesDev s, PrevDev prev,
-                                                               const int* __restrict__ list,
-                                                               const int* __restrict__ off,
-                                                               unsigned long long* __restrict__ acc) {
+// More than one cell along some axis.
+__device__ __forceinline__ bool far_move(const int di[3]) {
+    return max(max(abs(di[0]), abs(di[1])), abs(di[2])) > 1;
+}
+
+__global__ void __launch_bounds__(kDepThreads, 4) k_deposit_tiles(Geom g, TileGeom t, SpeciesDev s, PrevDev prev,
+                                                                  const int* __restrict__ list,
+                                                                  const int* __restrict__ off,
+                                                                  unsigned long long* __restrict__ acc) {
     constexpr int jx = kDepTile + 5, jpl = cur_plane(jx, jx), jr = jpl * jx;
     __shared__ unsigned long long Jl[3 * jr];
     const int tile = xcd_tile(blockIdx.x, t.ntiles, t.nt[0]);
@@ -575,6 +559,7 @@ __global__ void __launch_bounds__(kDepThreads) k_deposit_tiles(Geom g, TileGeom 
     __syncthreads();
     TileDeposit dep;
     dep.init(Jl, 0, jx, jpl, jr);
+    bool far = false;
     const int q_first = __builtin_amdgcn_readfirstlane((int)threadIdx.x & ~63);
     for (int q0 = q_first; q0 < n; q0 += kDepThreads) {
         const int q = q0 + (int)__lane_id();
@@ -598,13 +583,32 @@ __global__ void __launch_bounds__(kDepThreads) k_deposit_tiles(Geom g, TileGeom 
                     lc[d] = c0[d] - t0[d];
                     di[d] = unwrap_shift(c1[d] - c0[d], g.n[d]);
                 }
-                dep.core(lc, di, o0, o1, wq);
+                if (far_move(di)) {
+                    far = true;
+                    di[0] = di[1] = di[2] = 0;
+                } else {
+                    dep.core(lc, di, o0, o1, wq);
+                }
             }
         }
         dep.cross((di[0] | di[1] | di[2]) != 0, lc, di, o0, o1, wq);
     }
     dep.finish();
-    __syncthreads();
+    // (a push moves a particle into a neighbouring cell at most, which is all that
+    // the region holds; a caller may have moved it further since)
+    if (__syncthreads_or(far))
+        for (int q = threadIdx.x; q < n; q += kDepThreads) {
+            const int p = list[pb + q], cell1 = s.cell[p];
+            int c0[3], c1[3], di[3];
+            decompose(g, prev.cell[p], c0);
+            decompose(g, cell1, c1);
+#pragma unroll
+            for (int d = 0; d < 3; ++d) di[d] = unwrap_shift(c1[d] - c0[d], g.n[d]);
+            if ((unsigned)cell1 >= (unsigned)g.ncell || !far_move(di)) continue;
+            const float o0[3] = {prev.off[0][p], prev.off[1][p], prev.off[2][p]};
+            const float o1[3] = {s.off[0][p], s.off[1][p], s.off[2][p]};
+            deposit_global(g, c0, c1, o0, o1, s.mq * s.w[p], acc);
+        }
     flush_current<kDepThreads>(g, t0, 2, jx, jpl, jr, Jl, acc);
 }
 
