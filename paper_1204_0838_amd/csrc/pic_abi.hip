@@ -34,11 +34,14 @@ constexpr int64_t kDepositTilesMin = 8192;
 // by tile where the grid has a tile for every compute unit, otherwise with one
 // thread per particle, whose speed depends on the particles' order in memory
 // (the staged path does not sort: a warm plasma's order decays).  Measured,
-// direct against tile-wise with its list, random order: 75x50x44 cells, 2.56e5
-// particles 214 us against 119, 5.1e5 437 against 208; 160x128x128, 5.1e5 890
-// against 252; sorted by cell: 60 against 68, 106 against 102, 145 against 163
-// (equal at 6.8e5).  32^3 cells (64 tiles), 5.1e5: 325 against 248 and 149
-// against 203; 16^3 (8 tiles): 205 against 1262.
+// direct against tile-wise with its list, 75x50x44 cells: 3.3e5 particles in
+// cell order 132 us against 84, after a sort of the library (level order) 146
+// against 73, random 205 against 131; 6.6e5 in decayed order 234 against 129.
+// 160x128x128, 2.6e6: 4736 against 976, after a sort 970 against 293.  Beams
+// (normal, 1.5 cells, random order), the least gain: 2.9e5 particles 135 against
+// 151, 3.3e5 167 against 169, 1e6 438 against 381 (the deposit of the same step
+// takes 7.6 ms directly, 0.34 tile-wise).  32^3 cells (64 tiles), 5.1e5: 325
+// against 248 and 149 against 203; 16^3 (8 tiles): 205 against 1262.
 constexpr int64_t kGatherTilesMin = 262144;
 constexpr int kGatherTiles = 256;
 constexpr size_t kDiagBytesFixed = (2 * kDiagBins + kDiagWords) * 8;
@@ -592,14 +595,14 @@ void dn_bc(const pic_ctx* c, int bc[3]) {
 // with a valid one).  Its scratch, all idle between steps: the sort's rank
 // array, histogram (left holding the key offsets) and block sums, and the
 // spare cell array.
-pic_status tile_list(pic_ctx* c, const Species& sp, int s, const TileGeom& t, const int* cell, const int** list) {
+pic_status tile_list(pic_ctx* c, const Species& sp, int s, const TileGeom& t, const int* cell, TileList* list) {
     Geom gl = c->g;
     gl.window = 0;
     gl.pml = 0;
     int* out = reinterpret_cast<int*>(c->ws + c->L.sort_rank) + sp.base;
     HIPCHK(c, launch_tile_list(gl, t, cell, &small_of(c)->count[s], (int)sp.bound, hist_of(c), out, sp.alt.cell,
                                reinterpret_cast<int*>(c->ws + c->L.sums), c->stream));
-    *list = out;
+    *list = TileList{out, sp.alt.cell, hist_of(c), (int)sp.bound};
     return PIC_OK;
 }
 
@@ -1174,9 +1177,9 @@ pic_status pic_gather_push(pic_ctx* c, int32_t s) {
     if (sp.bound > kGatherTilesMin + c->g.ncell / 8 && t.ntiles >= kGatherTiles) {
         HIPCHK(c, launch_gather_invalid(c->g, dev_of(c, sp), prev_of(c, sp), count, (int)sp.bound,
                                         &small_of(c)->err, c->stream));
-        const int* list = nullptr;
+        TileList list;
         PICCHK(tile_list(c, sp, s, t, dev_of(c, sp).cell, &list));
-        HIPCHK(c, launch_gather_tiles(c->g, t, fields_of(c), dev_of(c, sp), prev_of(c, sp), list, hist_of(c),
+        HIPCHK(c, launch_gather_tiles(c->g, t, fields_of(c), dev_of(c, sp), prev_of(c, sp), list,
                                       &small_of(c)->err, c->stream));
     } else {
         HIPCHK(c, launch_gather_push(c->g, fields_of(c), dev_of(c, sp), prev_of(c, sp), count, (int)sp.bound,
@@ -1197,9 +1200,9 @@ pic_status pic_deposit(pic_ctx* c, int32_t s) {
         // (by the old cells: also a particle that the window has since left behind)
         const TileGeom t = deposit_tiling(c->g.n);
         const PrevDev pv = prev_of(c, sp);
-        const int* list = nullptr;
+        TileList list;
         PICCHK(tile_list(c, sp, s, t, pv.cell, &list));
-        HIPCHK(c, launch_deposit_tiles(c->g, t, dev_of(c, sp), pv, list, hist_of(c), acc_of(c), c->stream));
+        HIPCHK(c, launch_deposit_tiles(c->g, t, dev_of(c, sp), pv, list, acc_of(c), c->stream));
     } else {
         HIPCHK(c, launch_deposit(c->g, dev_of(c, sp), prev_of(c, sp), &small_of(c)->count[s], (int)sp.bound,
                                  acc_of(c), c->stream));

@@ -64,6 +64,17 @@ struct PrevDev {
     float* off[3];
 };
 
+// Whether some cell of a tile holds more than kListLevels particles (off: the
+// tile's key offsets; a barrier, every thread of the workgroup calls it): the
+// index list leaves such a tile in cell order.
+constexpr int kListLevels = 24;
+
+__device__ __forceinline__ bool crowded_tile(const int* __restrict__ off, int tcells) {
+    bool many = false;
+    for (int k = threadIdx.x; k < tcells; k += blockDim.x) many = many || off[k + 1] - off[k] > kListLevels;
+    return __syncthreads_or(many) != 0;
+}
+
 // device error flags (bit set)
 enum { ERR_CFL = 1, ERR_NONFINITE = 2, ERR_OVERFLOW = 4 };
 

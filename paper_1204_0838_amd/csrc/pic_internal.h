@@ -194,19 +194,23 @@ hipError_t launch_jfinal(const Geom& g, unsigned long long* acc, float* const J[
                          int zero_acc, hipStream_t st);
 
 // tile-wise deposit of the split path (pic_tile.hip): particles in any memory
-// order, visited through `list`, an index list of the tiling t by the old
-// cells (launch_tile_list; off: its key offsets)
+// order, visited through an index list of the tiling t by the old cells
+struct TileList {
+    const int *level, *plain;   // launch_tile_list's two orders
+    const int* off;             // its key offsets
+    int max_count;              // the host's bound of the entries
+};
 TileGeom deposit_tiling(const int n[3]);
 hipError_t launch_deposit_tiles(const Geom& g, const TileGeom& t, const SpeciesDev& s, const PrevDev& prev,
-                                const int* list, const int* off, unsigned long long* acc, hipStream_t st);
+                                const TileList& l, unsigned long long* acc, hipStream_t st);
 // gather and push likewise, the list by the current cells; launch_gather_invalid
 // (before the list) takes the particles that it leaves out
 hipError_t launch_gather_invalid(const Geom& g, const SpeciesDev& s, const PrevDev& prev, const int* d_count,
                                  int max_count, int* d_err, hipStream_t st);
 hipError_t launch_gather_tiles(const Geom& g, const TileGeom& t, const FieldPtrs& f, const SpeciesDev& s,
-                               const PrevDev& prev, const int* list, const int* off, int* d_err, hipStream_t st);
+                               const PrevDev& prev, const TileList& l, int* d_err, hipStream_t st);
 hipError_t launch_tile_list(const Geom& g, const TileGeom& t, const int* cell, const int* d_count, int max_count,
-                            int* hist, int* list, int* tmp, int* sums, hipStream_t st);
+                            int* hist, int* list, int* plain, int* sums, hipStream_t st);
 
 // sort (pic_sort.hip): src -> dst, new count into d_count and d_sorted, tile
 // ranges into toff (t.ntiles + 1 entries); hist, rank, sums are scratch.

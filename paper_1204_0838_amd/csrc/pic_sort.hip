@@ -140,6 +140,64 @@ __global__ void __launch_bounds__(256) k_sort_count(Geom g, TileGeom t, SortDiv 
     count_column(g, t, sd, cell, p0, stride, foreign != 0, n, hist, rank);
 }
 
+// Histogram and ranks for an index list (launch_tile_list), whose particles lie
+// in any order.  A workgroup takes kChunk of them, counts them in a table of
+// their keys in LDS (open addressing, twice as many slots) and adds each key's
+// count to the histogram once: where a beam's particles share a few cells, an
+// atomic per particle on their counters serialises (1e6 particles within some
+// cells: 716 us in random order, 522 by cell; 80 and 17 here.  3.3e5 anywhere in
+// 75x50x44 cells: 21 and 14; 24 and 8 here).  Twice the chunk: 73 us on the beam,
+// but its table takes twice the LDS (3.3e5 anywhere: 26).
+constexpr int kChunk = 2048, kChunkThreads = 512, kSlots = 2 * kChunk;
+
+__global__ void __launch_bounds__(kChunkThreads) k_list_count(Geom g, TileGeom t, SortDiv sd,
+                                                              const int* __restrict__ cell,
+                                                              const int* __restrict__ d_count,
+                                                              int* __restrict__ hist, int* __restrict__ rank) {
+    __shared__ int keys[kSlots], cnt[kSlots];   // cnt: the chunk's particles of the key, then the first one's rank
+    constexpr int PER = kChunk / kChunkThreads;
+    const int n = *d_count;
+    const int64_t p0 = (int64_t)blockIdx.x * kChunk + threadIdx.x;
+    if (p0 - threadIdx.x >= n) return;
+    for (int i = threadIdx.x; i < kSlots; i += kChunkThreads) {
+        keys[i] = -1;
+        cnt[i] = 0;
+    }
+    int key[PER], slot[PER], r[PER];
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+        const int64_t p = p0 + u * kChunkThreads;
+        key[u] = p < n ? cell[p] : -1;
+    }
+#pragma unroll
+    for (int u = 0; u < PER; ++u) key[u] = sort_key(g, t, sd, key[u]);
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+        slot[u] = r[u] = 0;
+        if (key[u] < 0) continue;
+        int s = (int)((unsigned)key[u] * 2654435761u >> 16) % kSlots;
+        for (int k = keys[s]; k != key[u]; s = (s + 1) % kSlots, k = keys[s]) {   // (half the slots stay free)
+            if (k < 0) k = atomicCAS(&keys[s], -1, key[u]);
+            if (k < 0 || k == key[u]) break;
+        }
+        slot[u] = s;
+        r[u] = atomicAdd(&cnt[s], 1);
+    }
+    __syncthreads();
+    // (by the key's first particle, so that neighbouring cells' counts go out in
+    // one request where the particles are in some order)
+#pragma unroll
+    for (int u = 0; u < PER; ++u)
+        if (key[u] >= 0 && r[u] == 0) cnt[slot[u]] = atomicAdd(hist + key[u], cnt[slot[u]]);
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+        const int64_t p = p0 + u * kChunkThreads;
+        if (p < n) rank[p] = key[u] < 0 ? -1 : cnt[slot[u]] + r[u];
+    }
+}
+
 // Count pass of a re-sort over the particles that the last sort put in tile
 // ranges: workgroup b takes tile b's old range [toff[b], toff[b + 1]).  Most
 // of them are still in that tile (they move less than a cell per step): they
@@ -324,6 +382,18 @@ __device__ __forceinline__ void sort_levels_tile(const int* __restrict__ off, in
 
 __global__ void __launch_bounds__(kLevelThreads) k_sort_levels(const int* __restrict__ off, int tcells,
                                                                int* __restrict__ src, int* __restrict__ out) {
+    sort_levels_tile(off, tcells, src, out, blockIdx.x);
+}
+
+// The same for an index list (launch_tile_list).  A level costs a barrier, and
+// a cell of a beam can hold thousands of particles (1e6 particles within some
+// cells: 10.4 ms for this pass alone): a tile with more than kListLevels in a
+// cell is left in cell order, for its readers to spread (see crowded_tile).
+// 16 or 32 levels: within 6% on beams; 8 particles per cell (at most 22 in one)
+// are better off in level order (32^3 cells: deposit 130 us against 138).
+__global__ void __launch_bounds__(kLevelThreads) k_list_levels(const int* __restrict__ off, int tcells,
+                                                               int* __restrict__ src, int* __restrict__ out) {
+    if (crowded_tile(off + (size_t)blockIdx.x * tcells, tcells)) return;
     sort_levels_tile(off, tcells, src, out, blockIdx.x);
 }
 
@@ -699,19 +769,19 @@ hipError_t launch_sort(const Geom& g, const TileGeom& t, const SpeciesDev& src, 
 
 // The tile-wise order of particles by the cells in `cell`, as a list of
 // indices: list[off[t tcells] .. off[(t + 1) tcells]) are tile t's particles
-// in level order (hist is left holding off).  Nothing else is moved.
+// in level order, plain[..] in cell order (hist is left holding off; list is
+// not written for a crowded tile).  Nothing else is moved.
 hipError_t launch_tile_list(const Geom& g, const TileGeom& t, const int* cell, const int* d_count, int max_count,
-                            int* hist, int* list, int* tmp, int* sums, hipStream_t st) {
+                            int* hist, int* list, int* plain, int* sums, hipStream_t st) {
     const int n = t.ntiles * t.tcells + 1;
-    const int stride = count_stride(t, 0), ncol = count_threads(max_count, stride);
     const SortDiv sd = make_sortdiv(g, t);
     hipLaunchKernelGGL(k_zero_hist, dim3((n + 255) / 256), dim3(256), 0, st, hist, n);
-    hipLaunchKernelGGL(k_sort_count, dim3((ncol + 255) / 256), dim3(256), 0, st, g, t, sd, cell, nullptr, d_count,
-                       stride, 0, hist, list);
+    hipLaunchKernelGGL(k_list_count, dim3((max_count + kChunk - 1) / kChunk), dim3(kChunkThreads), 0, st, g, t, sd,
+                       cell, d_count, hist, list);
     scan_hist(hist, nullptr, n, sums, st);
-    hipLaunchKernelGGL(k_sort_scatter, dim3((max_count + 255) / 256), dim3(256), 0, st, g, t, sd, cell, tmp, d_count,
+    hipLaunchKernelGGL(k_sort_scatter, dim3((max_count + 255) / 256), dim3(256), 0, st, g, t, sd, cell, plain, d_count,
                        list, hist, nullptr, 0);
-    hipLaunchKernelGGL(k_sort_levels, dim3(t.ntiles), dim3(kLevelThreads), 0, st, hist, t.tcells, tmp, list);
+    hipLaunchKernelGGL(k_list_levels, dim3(t.ntiles), dim3(kLevelThreads), 0, st, hist, t.tcells, plain, list);
     return hipGetLastError();
 }
 

@@ -82,7 +82,7 @@ __device__ __forceinline__ int xcd_tile(int b, int ntiles, int chunk) {
     return tile < ntiles ? (int)tile : ntiles;
 }
 
-static int xcd_blocks(int ntiles, int chunk) {
+static __host__ __device__ int xcd_blocks(int ntiles, int chunk) {
     const int nchunks = (ntiles + chunk - 1) / chunk;
     return 8 * ((nchunks + 7) / 8) * chunk;
 }
@@ -527,7 +527,7 @@ __global__ void __launch_bounds__(NT) k_batch_tile(const InstDesc* __restrict__ 
 
 // Deposit of the split path, tile by tile.  The particles stay in the
 // caller's memory order; `list` names each tile's particles by their old
-// cells (so the LDS region needs no guard: 8x8x8 cells, 59 KB, two
+// cells (so the LDS region needs no guard: 8x8x8 cells, 57 KB, two
 // workgroups per CU).  A particle's 144-300 contributions go to LDS, and the
 // tile's region to the global accumulator once: global 64-bit atomics, which
 // bound the one-thread-per-particle form (k_deposit), drop from ~200 to ~3
@@ -536,27 +536,81 @@ __global__ void __launch_bounds__(NT) k_batch_tile(const InstDesc* __restrict__ 
 // LDS bound it now).
 constexpr int kDepTile = 8, kDepThreads = 512;
 
+// A tile of up to kWhole list entries (8 particles per cell) is one workgroup's.
+// Of a larger one its own workgroup takes the first kWindow + 1 .. 2 kWindow,
+// and one more workgroup per kWindow entries of the whole list takes those
+// that start at its multiple of kWindow if their tile's own workgroup does not
+// reach them: the tiles that hold a beam are shared by many workgroups.
+// Smaller windows fill the chip for a smaller beam; splitting ordinary tiles
+// stages their fields twice.  75x50x44 cells, 3.3e5 particles within some cells
+// (normal, 1.5 cells): deposit 907 us with windows of 4096, 572 with 2048, 367
+// with 1024; 64x64x64 cells, 6 per cell in level order: gather 140 us with whole
+// tiles, 168 with them split at 2048.
+constexpr int kWhole = 4608, kWindow = 1024;
+
+struct TileWindow {
+    int tile, begin, n;   // list entries [begin, begin + n) are particles of this tile
+};
+
+__device__ __forceinline__ bool tile_window(const TileGeom& t, const TileList& l, TileWindow& w) {
+    const int* __restrict__ off = l.off;
+    const int own = xcd_blocks(t.ntiles, t.nt[0]);
+    // entries of a tile [a, e) from here on are not its own workgroup's
+    auto reach = [](int a, int e) {
+        return e - a <= kWhole ? (unsigned)e : min((unsigned)e, ((unsigned)a / kWindow + 2) * kWindow);
+    };
+    if ((int)blockIdx.x < own) {
+        w.tile = xcd_tile(blockIdx.x, t.ntiles, t.nt[0]);
+        if (w.tile >= t.ntiles) return false;
+        w.begin = off[w.tile * t.tcells];
+        w.n = (int)reach(w.begin, off[(w.tile + 1) * t.tcells]) - w.begin;
+        return w.n > 0;
+    }
+    const int64_t begin = (int64_t)((int)blockIdx.x - own) * kWindow;
+    if (begin >= off[t.ntiles * t.tcells]) return false;
+    w.begin = (int)begin;
+    // last tile that starts at or before the window, which holds the window's start (64 tiles compared at a time)
+    int lo = 0, count = t.ntiles;
+    while (count > 1) {
+        const int step = (count + 63) / 64, k = (int)__lane_id() * step;
+        const int last = 63 - __clzll(__ballot(k < count && off[(lo + k) * t.tcells] <= w.begin));
+        lo += last * step;
+        count = min(step, count - last * step);
+    }
+    const int a = off[lo * t.tcells], e = off[(lo + 1) * t.tcells];
+    w.tile = lo;
+    w.n = min(e - w.begin, kWindow);
+    return (unsigned)w.begin >= reach(a, e);
+}
+
+static int list_blocks(const TileGeom& t, const TileList& l) {
+    return xcd_blocks(t.ntiles, t.nt[0]) + l.max_count / kWindow + 1;
+}
+
 // More than one cell along some axis.
 __device__ __forceinline__ bool far_move(const int di[3]) {
     return max(max(abs(di[0]), abs(di[1])), abs(di[2])) > 1;
 }
 
 __global__ void __launch_bounds__(kDepThreads, 4) k_deposit_tiles(Geom g, TileGeom t, SpeciesDev s, PrevDev prev,
-                                                                  const int* __restrict__ list,
-                                                                  const int* __restrict__ off,
+                                                                  const TileList l,
                                                                   unsigned long long* __restrict__ acc) {
     constexpr int jx = kDepTile + 5, jpl = cur_plane(jx, jx), jr = jpl * jx;
     __shared__ unsigned long long Jl[3 * jr];
-    const int tile = xcd_tile(blockIdx.x, t.ntiles, t.nt[0]);
-    if (tile >= t.ntiles) return;
-    const int pb = off[tile * t.tcells], n = off[(tile + 1) * t.tcells] - pb;
-    if (n == 0) return;
-    const int tz = tile / (t.nt[0] * t.nt[1]);
-    const int tr = tile - tz * t.nt[0] * t.nt[1];
+    TileWindow w;
+    if (!tile_window(t, l, w)) return;
+    const int n = w.n;
+    const int tz = w.tile / (t.nt[0] * t.nt[1]);
+    const int tr = w.tile - tz * t.nt[0] * t.nt[1];
     const int ty = tr / t.nt[0];
     const int t0[3] = {(tr - ty * t.nt[0]) * t.T[0], ty * t.T[1], tz * t.T[2]};
     for (int i = threadIdx.x; i < 3 * jr; i += kDepThreads) Jl[i] = 0ull;
-    __syncthreads();
+    // A crowded tile's entries are in cell order: lane k takes the k-th of 64
+    // runs of them, so that the lanes of an atomic are in different cells
+    const bool crowded = crowded_tile(l.off + w.tile * t.tcells, t.tcells);   // (the barrier after the clearing)
+    const int* __restrict__ list = (crowded ? l.plain : l.level) + w.begin;
+    const int run = (n + 63) / 64, longer = n - 64 * (run - 1), lane = __lane_id();
+    const int first = crowded ? (lane < longer ? lane * run : longer * run + (lane - longer) * (run - 1)) : 0;
     TileDeposit dep;
     dep.init(Jl, 0, jx, jpl, jr);
     bool far = false;
@@ -566,7 +620,7 @@ __global__ void __launch_bounds__(kDepThreads, 4) k_deposit_tiles(Geom g, TileGe
         int lc[3] = {0, 0, 0}, di[3] = {0, 0, 0};
         float o0[3] = {0.f, 0.f, 0.f}, o1[3] = {0.f, 0.f, 0.f}, wq = 0.f;
         if (q < n) {
-            const int p = list[pb + q];
+            const int p = list[crowded ? first + (q0 >> 6) : q];
             const int cell0 = prev.cell[p], cell1 = s.cell[p];   // (cell0 is valid: it has a key)
             int c0[3], c1[3];
             decompose(g, cell0, c0);
@@ -598,7 +652,7 @@ __global__ void __launch_bounds__(kDepThreads, 4) k_deposit_tiles(Geom g, TileGe
     // the region holds; a caller may have moved it further since)
     if (__syncthreads_or(far))
         for (int q = threadIdx.x; q < n; q += kDepThreads) {
-            const int p = list[pb + q], cell1 = s.cell[p];
+            const int p = list[q], cell1 = s.cell[p];
             int c0[3], c1[3], di[3];
             decompose(g, prev.cell[p], c0);
             decompose(g, cell1, c1);
@@ -614,22 +668,20 @@ __global__ void __launch_bounds__(kDepThreads, 4) k_deposit_tiles(Geom g, TileGe
 
 // Gather and push of the split path, tile by tile as k_deposit_tiles (the
 // list by the current cells): E and B of the tile and its two-cell halo in
-// LDS (43 KB, three workgroups per CU).  The one-thread-per-particle form
+// LDS (48 KB, three workgroups per CU).  The one-thread-per-particle form
 // (k_gather_push) reads its 384 field values from global memory, where the
 // particles' memory order decides how many lines a wavefront's load touches.
 // 75x50x44 cells, 3.3e5 particles of a warm plasma: 205 -> 75 us, plus 56 us
 // for the list; the particles' scattered loads and stores bound it now.
 __global__ void __launch_bounds__(kDepThreads) k_gather_tiles(Geom g, TileGeom t, FieldPtrs f, SpeciesDev s,
-                                                              PrevDev prev, const int* __restrict__ list,
-                                                              const int* __restrict__ off, int* __restrict__ d_err) {
+                                                              PrevDev prev, const TileList l,
+                                                              int* __restrict__ d_err) {
     constexpr int fx = kDepTile + 4, fpl = field_plane(fx, fx), fr = fpl * fx;
     __shared__ float Fl[6 * fr];
-    const int tile = xcd_tile(blockIdx.x, t.ntiles, t.nt[0]);
-    if (tile >= t.ntiles) return;
-    const int pb = off[tile * t.tcells], n = off[(tile + 1) * t.tcells] - pb;
-    if (n == 0) return;
-    const int tz = tile / (t.nt[0] * t.nt[1]);
-    const int tr = tile - tz * t.nt[0] * t.nt[1];
+    TileWindow w;
+    if (!tile_window(t, l, w)) return;
+    const int tz = w.tile / (t.nt[0] * t.nt[1]);
+    const int tr = w.tile - tz * t.nt[0] * t.nt[1];
     const int ty = tr / t.nt[0];
     const int t0[3] = {(tr - ty * t.nt[0]) * t.T[0], ty * t.T[1], tz * t.T[2]};
     for (int i = threadIdx.x; i < fx * fx * fx; i += kDepThreads) {
@@ -642,13 +694,14 @@ __global__ void __launch_bounds__(kDepThreads) k_gather_tiles(Geom g, TileGeom t
             Fl[(3 + c) * fr + lz * fpl + rr] = f.B[c][gi];
         }
     }
-    __syncthreads();
+    const bool crowded = crowded_tile(l.off + w.tile * t.tcells, t.tcells);   // (the barrier after the staging)
+    const int* __restrict__ list = (crowded ? l.plain : l.level) + w.begin;
     float* const El[3] = {Fl, Fl + fr, Fl + 2 * fr};
     float* const Bl[3] = {Fl + 3 * fr, Fl + 4 * fr, Fl + 5 * fr};
     constexpr int fstride[3] = {1, fx, fpl};
     int errs = 0;
-    for (int q = threadIdx.x; q < n; q += kDepThreads) {
-        const int p = list[pb + q], cell = s.cell[p];
+    for (int q = threadIdx.x; q < w.n; q += kDepThreads) {
+        const int p = list[q], cell = s.cell[p];
         int c[3];
         decompose(g, cell, c);
         float o[3] = {s.off[0][p], s.off[1][p], s.off[2][p]};
@@ -707,9 +760,9 @@ hipError_t launch_gather_invalid(const Geom& g, const SpeciesDev& s, const PrevD
 }
 
 hipError_t launch_gather_tiles(const Geom& g, const TileGeom& t, const FieldPtrs& f, const SpeciesDev& s,
-                               const PrevDev& prev, const int* list, const int* off, int* d_err, hipStream_t st) {
-    hipLaunchKernelGGL(k_gather_tiles, dim3(xcd_blocks(t.ntiles, t.nt[0])), dim3(kDepThreads), 0, st, g, t, f, s,
-                       prev, list, off, d_err);
+                               const PrevDev& prev, const TileList& l, int* d_err, hipStream_t st) {
+    hipLaunchKernelGGL(k_gather_tiles, dim3(list_blocks(t, l)), dim3(kDepThreads), 0, st, g, t, f, s,
+                       prev, l, d_err);
     return hipGetLastError();
 }
 
@@ -725,9 +778,9 @@ TileGeom deposit_tiling(const int n[3]) {
 }
 
 hipError_t launch_deposit_tiles(const Geom& g, const TileGeom& t, const SpeciesDev& s, const PrevDev& prev,
-                                const int* list, const int* off, unsigned long long* acc, hipStream_t st) {
-    hipLaunchKernelGGL(k_deposit_tiles, dim3(xcd_blocks(t.ntiles, t.nt[0])), dim3(kDepThreads), 0, st, g, t, s, prev,
-                       list, off, acc);
+                                const TileList& l, unsigned long long* acc, hipStream_t st) {
+    hipLaunchKernelGGL(k_deposit_tiles, dim3(list_blocks(t, l)), dim3(kDepThreads), 0, st, g, t, s, prev,
+                       l, acc);
     return hipGetLastError();
 }
 
