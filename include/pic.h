@@ -98,8 +98,9 @@ enum { PIC_JPOST_NONE = 0, PIC_JPOST_BINOMIAL = 1, PIC_JPOST_DENOISER = 2 };
  *                PJ = (Tx + 2 guard + 5)(Ty + 2 guard + 5) and
  *                PF = (Tx + 2 guard + 4)(Ty + 2 guard + 4) are padded up to
  *                8 mod 16 and 8 mod 32 words (150,720 B for 8x8x8, guard 1).
- *   threads      threads per tile workgroup (256, 512 or 1024; 0 = chosen by
- *                the tiles' population; no result depends on it).
+ *   threads      threads per tile workgroup (256, 512 or 1024; 0 = 1024, or
+ *                512 where the LDS of two tiles fits 160 KiB; no result
+ *                depends on it).
  *   interleave   order of the particles inside a tile after a sort.
  *                0 (default): level order -- level r holds the (r+1)-th
  *                particle of every cell that has one, cells in key order,

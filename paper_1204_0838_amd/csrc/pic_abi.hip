@@ -20,7 +20,6 @@ namespace {
 
 constexpr size_t kAlign = 256;
 constexpr int kKillMargin = 3;   // window cells behind which particles are removed
-constexpr size_t kMaxLds = 160 * 1024;
 constexpr int kDiagBins = 2048;                                   // most spectrum bins
 constexpr size_t kDiagWords = 64;                                 // reduction words of the diagnostics (after the bins)
 // The split path deposits a species of more than kDepositTilesMin + ncell / 128
@@ -131,7 +130,7 @@ const char* validate_tiling(const int32_t n[3], const int32_t tile[3], int32_t g
     }
     tmp.guard = guard;
     const Tiling tl = tiling_of(&tmp);
-    if (tile_lds_bytes(tl.t, tl.guard) > kMaxLds) return "tile and guard exceed the 160 KiB of LDS";
+    if (tile_lds_bytes(tl.t, tl.guard) > kLdsBytes) return "tile and guard exceed the 160 KiB of LDS";
     return nullptr;
 }
 

@@ -10,6 +10,7 @@
 namespace pic {
 
 constexpr int kMaxSpecies = 8;
+constexpr size_t kLdsBytes = 160 * 1024;   // LDS of a compute unit
 
 struct FieldPtrs {
     float* E[3];
@@ -232,7 +233,7 @@ size_t tile_lds_bytes(const TileGeom& t, int guard);
 // rest_n / rest_idx: the species' rest list (empty before; indices appended by the kernel)
 // src: null, or the pre-sort arrays when the sort ran without its copy pass
 // (s.cell then holds source indices; the step writes every array of s)
-// threads: per workgroup, 0 = by the tiles' population; max_count: the host's bound of the particles
+// threads: per workgroup, 0 = by the tile's LDS (tile_threads); max_count: the host's bound of the particles
 hipError_t launch_pic_tile(const Geom& g, const TileGeom& t, int guard, int threads, int max_count,
                            const FieldPtrs& f, const SpeciesDev& s, const SpeciesDev* src, const int* toff,
                            unsigned long long* acc, int* d_err, int* rest_n, int* rest_idx, hipStream_t st);

@@ -484,8 +484,9 @@ __device__ __forceinline__ void tile_body(const Geom& g, const TileGeom& t, int 
     flush_current<NT>(g, t0, guard + 2, jx, jpl, jr, Jl, acc);
 }
 
-template <int NT, int TX = 0, int TY = 0, int TZ = 0, int GD = -1, bool GATHER = false>
-__global__ void __launch_bounds__(NT) k_pic_tile(Geom g, TileGeom t, int guard, FieldPtrs f, SpeciesDev s,
+// WAVES: wavefronts per SIMD that the kernel leaves registers for (see tile_packed).
+template <int NT, int WAVES, int TX = 0, int TY = 0, int TZ = 0, int GD = -1, bool GATHER = false>
+__global__ void __launch_bounds__(NT, WAVES) k_pic_tile(Geom g, TileGeom t, int guard, FieldPtrs f, SpeciesDev s,
                                                  SpeciesDev src, const int* __restrict__ toff,
                                                  unsigned long long* __restrict__ acc, int* __restrict__ d_err,
                                                  int* __restrict__ rest_n, int* __restrict__ rest_idx) {
@@ -500,8 +501,8 @@ __global__ void __launch_bounds__(NT) k_pic_tile(Geom g, TileGeom t, int guard, 
 // (member m owns flat tiles [tile_begin[m], tile_begin[m+1])), mapped XCD by
 // XCD like the single-instance launch.  TX..GD > 0 (>= 0): every member has
 // that tile shape and guard (the compile-time body of the single launch).
-template <int NT, int TX = 0, int TY = 0, int TZ = 0, int GD = -1>
-__global__ void __launch_bounds__(NT) k_batch_tile(const InstDesc* __restrict__ tab,
+template <int NT, int WAVES, int TX = 0, int TY = 0, int TZ = 0, int GD = -1>
+__global__ void __launch_bounds__(NT, WAVES) k_batch_tile(const InstDesc* __restrict__ tab,
                                                    const int* __restrict__ tile_begin, int n, int total) {
     extern __shared__ unsigned long long lds_u64[];
     const int ft = xcd_tile(blockIdx.x, total, kBatchChunk);
@@ -852,6 +853,24 @@ size_t tile_lds_bytes(const TileGeom& t, int guard) {
     return 3 * jr * 8 + 6 * fr * 4;
 }
 
+// Tiles so small that more than two wavefronts per SIMD fit by their LDS take
+// the general body in 128 registers, four wavefronts per SIMD; in larger
+// ones, one workgroup per CU, that limit would only spill.  Measured, two steps
+// of 64x64x64 cells, 2.1e6 particles of a warm plasma, 4x4x4 tiles (61 KB), 512
+// threads: 812 us, 1118 with the 172 registers it takes otherwise (one
+// workgroup per CU); batch of 3 96x64x64 members, 8x8x4 tiles (109 KB), 512
+// threads: 3957 us without the limit, 4093 with it.
+static bool tile_packed(int threads, size_t lds) { return (int)(kLdsBytes / lds) * threads / 256 > 2; }
+
+// Threads per workgroup where the caller leaves them to the library (0).
+// 1024: also where a share holds few particles, the staging, clearing and flush
+// of the tile's LDS gain from them (12 tiles of 1050 particles in four parts: 72
+// us a step, 73 with 512, 84 with 256; 7200 tiles of 4096: 4.60 ms per two
+// steps, 5.05 with 512, 7.5 with 256).  512 where two workgroups fit a CU by
+// their LDS, whose phases then overlap (the 4x4x4 tiles above: 812 us, 1103 with
+// 1024, 939 with 256; as a batch of 3 96x64x64: 4.45 ms, 6.67, 5.39).
+static int tile_threads(int threads, size_t lds) { return threads > 0 ? threads : (2 * lds <= kLdsBytes ? 512 : 1024); }
+
 // One tile launch: parts workgroups of NT threads per tile.
 struct TileLaunch {
     const Geom& g;
@@ -866,22 +885,22 @@ struct TileLaunch {
     hipStream_t st;
 };
 
-template <int NT, int TX, int TY, int TZ, int GD, bool GATHER>
+template <int NT, int WAVES, int TX, int TY, int TZ, int GD, bool GATHER>
 static hipError_t launch_tile_k(const TileLaunch& L) {
     const size_t lds = tile_lds_bytes(L.t, L.guard);
     const int nb = xcd_blocks(L.t.ntiles, L.t.nt[0]);
-    hipError_t e = hipFuncSetAttribute((const void*)k_pic_tile<NT, TX, TY, TZ, GD, GATHER>,
+    hipError_t e = hipFuncSetAttribute((const void*)k_pic_tile<NT, WAVES, TX, TY, TZ, GD, GATHER>,
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((k_pic_tile<NT, TX, TY, TZ, GD, GATHER>), dim3(nb, L.parts), dim3(NT), lds, L.st, L.g, L.t,
+    hipLaunchKernelGGL((k_pic_tile<NT, WAVES, TX, TY, TZ, GD, GATHER>), dim3(nb, L.parts), dim3(NT), lds, L.st, L.g, L.t,
                        L.guard, L.f, L.s, GATHER ? *L.src : L.s, L.toff, L.acc, L.d_err, L.rest_n, L.rest_idx);
     return hipGetLastError();
 }
 
-template <int NT, int TX = 0, int TY = 0, int TZ = 0, int GD = -1>
+template <int NT, int WAVES, int TX = 0, int TY = 0, int TZ = 0, int GD = -1>
 static hipError_t launch_tile_nt(const TileLaunch& L) {
-    if (L.src) return launch_tile_k<NT, TX, TY, TZ, GD, true>(L);
-    return launch_tile_k<NT, TX, TY, TZ, GD, false>(L);
+    if (L.src) return launch_tile_k<NT, WAVES, TX, TY, TZ, GD, true>(L);
+    return launch_tile_k<NT, WAVES, TX, TY, TZ, GD, false>(L);
 }
 
 // Tile shapes with a compile-time specialisation (the library default and
@@ -889,26 +908,23 @@ static hipError_t launch_tile_nt(const TileLaunch& L) {
 template <int NT>
 static hipError_t launch_tile_shape(const TileLaunch& L) {
     const int* T = L.t.T;
+    constexpr int W = NT / 256;
     if (T[0] == 8 && T[1] == 8 && T[2] == 8) {
-        if (L.guard == 1) return launch_tile_nt<NT, 8, 8, 8, 1>(L);
-        if (L.guard == 0) return launch_tile_nt<NT, 8, 8, 8, 0>(L);
+        if (L.guard == 1) return launch_tile_nt<NT, W, 8, 8, 8, 1>(L);
+        if (L.guard == 0) return launch_tile_nt<NT, W, 8, 8, 8, 0>(L);
     }
-    if (T[0] == 8 && T[1] == 8 && T[2] == 4 && L.guard == 1) return launch_tile_nt<NT, 8, 8, 4, 1>(L);
-    return launch_tile_nt<NT>(L);
+    if (T[0] == 8 && T[1] == 8 && T[2] == 4 && L.guard == 1) return launch_tile_nt<NT, W, 8, 8, 4, 1>(L);
+    if (tile_packed(NT, tile_lds_bytes(L.t, L.guard))) return launch_tile_nt<NT, 4>(L);
+    return launch_tile_nt<NT, W>(L);
 }
 
-// Launch shape for tiles of `population` particles on average.
-// Parts: a tile's LDS leaves room for one workgroup per CU, so a grid of
-// fewer tiles than CUs shares each tile's particles between workgroups (each
-// stages the fields and adds its own current: sums are integers, so J is the
-// same), as long as each gets kPartMin particles.
-// Measured, 128 tiles of 4096 particles: 113 us per launch with one part, 67
-// with two; 12 tiles of 1050: 48 us, 21 with four.
-// Threads (0: chosen here) 1024: also where a share holds fewer particles, the
-// staging, clearing and flush of the tile's LDS gain from them (12 tiles of
-// 1050 particles in four parts: 72 us a step, 73 with 512, 84 with 256; 7200
-// tiles of 4096: 4.60 ms per two steps, 5.05 with 512, 7.5 with 256).
-constexpr int kCUs = 256, kPartMin = 256, kTileThreads = 1024;
+// Workgroups that share a tile.  A tile's LDS leaves room for one or two
+// workgroups per CU, so a grid of fewer tiles than CUs shares each tile's
+// particles between workgroups (each stages the fields and adds its own
+// current: sums are integers, so J is the same), as long as each gets kPartMin
+// particles on average.  Measured, 128 tiles of 4096 particles: 113 us per launch
+// with one part, 67 with two; 12 tiles of 1050: 48 us, 21 with four.
+constexpr int kCUs = 256, kPartMin = 256;
 
 static int tile_parts(int ntiles, int64_t count) {
     const int64_t fill = kCUs / ntiles, most = count / ((int64_t)ntiles * kPartMin);
@@ -920,36 +936,38 @@ hipError_t launch_pic_tile(const Geom& g, const TileGeom& t, int guard, int thre
                            unsigned long long* acc, int* d_err, int* rest_n, int* rest_idx, hipStream_t st) {
     const int parts = tile_parts(t.ntiles, max_count);
     const TileLaunch L{g, t, guard, parts, f, s, src, toff, acc, d_err, rest_n, rest_idx, st};
-    switch (threads > 0 ? threads : kTileThreads) {
+    switch (tile_threads(threads, tile_lds_bytes(t, guard))) {
         case 256: return launch_tile_shape<256>(L);
         case 1024: return launch_tile_shape<1024>(L);
         default: return launch_tile_shape<512>(L);
     }
 }
 
-template <int NT, int TX = 0, int TY = 0, int TZ = 0, int GD = -1>
+template <int NT, int WAVES, int TX = 0, int TY = 0, int TZ = 0, int GD = -1>
 static hipError_t launch_batch_tile_k(const InstDesc* d, const int* tile_begin, int n, int total, size_t lds,
                                       hipStream_t st) {
     const int nb = xcd_blocks(total, kBatchChunk);
-    hipError_t e = hipFuncSetAttribute((const void*)k_batch_tile<NT, TX, TY, TZ, GD>,
+    hipError_t e = hipFuncSetAttribute((const void*)k_batch_tile<NT, WAVES, TX, TY, TZ, GD>,
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k_batch_zero_rest, dim3((n + 63) / 64), dim3(64), 0, st, d, n);
-    hipLaunchKernelGGL((k_batch_tile<NT, TX, TY, TZ, GD>), dim3(nb), dim3(NT), lds, st, d, tile_begin, n, total);
+    hipLaunchKernelGGL((k_batch_tile<NT, WAVES, TX, TY, TZ, GD>), dim3(nb), dim3(NT), lds, st, d, tile_begin, n, total);
     return hipGetLastError();
 }
 
 template <int NT>
 static hipError_t launch_batch_tile_nt(const InstDesc* d, const int* tile_begin, int n, int total, size_t lds,
                                        bool all_888g1, hipStream_t st) {
-    if (all_888g1) return launch_batch_tile_k<NT, 8, 8, 8, 1>(d, tile_begin, n, total, lds, st);
-    return launch_batch_tile_k<NT>(d, tile_begin, n, total, lds, st);
+    constexpr int W = NT / 256;
+    if (all_888g1) return launch_batch_tile_k<NT, W, 8, 8, 8, 1>(d, tile_begin, n, total, lds, st);
+    if (tile_packed(NT, lds)) return launch_batch_tile_k<NT, 4>(d, tile_begin, n, total, lds, st);
+    return launch_batch_tile_k<NT, W>(d, tile_begin, n, total, lds, st);
 }
 
 hipError_t launch_batch_tile(const InstDesc* d, const int* tile_begin, int n, int total_tiles, int threads,
                              size_t lds_bytes, bool all_888g1, hipStream_t st) {
     if (n <= 0 || total_tiles <= 0) return hipSuccess;
-    switch (threads > 0 ? threads : kTileThreads) {
+    switch (tile_threads(threads, lds_bytes)) {
         case 256: return launch_batch_tile_nt<256>(d, tile_begin, n, total_tiles, lds_bytes, all_888g1, st);
         case 1024: return launch_batch_tile_nt<1024>(d, tile_begin, n, total_tiles, lds_bytes, all_888g1, st);
         default: return launch_batch_tile_nt<512>(d, tile_begin, n, total_tiles, lds_bytes, all_888g1, st);
