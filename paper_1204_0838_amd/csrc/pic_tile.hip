@@ -201,17 +201,23 @@ __device__ __forceinline__ void flush_current(const Geom& g, const int t0[3], in
 // contributions that a cell crossing adds (up to 156 more) concern a third of
 // the particles at most, but nearly every wavefront has a lane among them,
 // and a wavefront that runs them for a few lanes pays for all 64.  So `cross`
-// only queues the crossing lanes' particles in eight registers per lane
-// (moved there by ds_permute), and their contributions are added when 64 are
-// waiting, and at the tile's end (`finish`).  Sums are integers: the order
-// does not matter.  Every lane of the wavefront calls cross and finish.
+// only queues the crossing lanes' particles, in five registers per lane (old
+// offsets, index, cell and crossings; moved there by ds_permute), and their
+// contributions are added when 64 are waiting, and at the tile's end
+// (`finish`); new offsets and weights are read back from s, where they are
+// stored by then.  (Kept in the queue as well, eight registers, they made the
+// 1024-thread kernels spill up to 11: two steps of a 512x256x256 wakefield
+// 26.46 ms against 26.03.)  Sums are integers: the order does not matter.
+// Every lane of the wavefront calls cross and finish.
 // An LDS atomic costs a wavefront 6 cycles however few lanes are active, 8
-// with two-way bank conflicts.  Measured (tile launch, 512 threads): wakefield
-// 256x120x120 cells 2596 -> 2341 us, warm plasma of 5.7e6 particles 824 -> 781.
+// with two-way bank conflicts.  Measured against running the crossings with the
+// rest (tile launch, 512 threads): wakefield 256x120x120 cells 2596 -> 2341 us,
+// warm plasma of 5.7e6 particles 824 -> 781.
 struct TileDeposit {
     unsigned long long* Jl;
     int guard, jx, jpl, jr;
-    float q[7];    // the queued particle of this lane: old offsets, new offsets, charge factor
+    float q[3];    // the queued particle of this lane: old offsets
+    int qp;        // its index
     int qkey;      // its local cell (+ guard, 5 bits per axis) and crossings (+ 1, 2 bits per axis)
     int waiting;   // queued particles: lanes 0 .. waiting - 1 (the same in every lane)
 
@@ -224,7 +230,8 @@ struct TileDeposit {
         waiting = 0;
         qkey = 0;
 #pragma unroll
-        for (int k = 0; k < 7; ++k) q[k] = 0.0f;
+        for (int k = 0; k < 3; ++k) q[k] = 0.0f;
+        qp = 0;
     }
 
     // lc: old cell relative to the tile; di: cells crossed (-1, 0, 1)
@@ -240,7 +247,9 @@ struct TileDeposit {
         emit_slots<2>(A, wq, 0, 3, 0, 4, 0, 4, em);
     }
 
-    __device__ __forceinline__ void extra() const {
+    // (the lanes' stores of new offsets and weights come before the reads: a
+    // workgroup's stores and loads go through one L1)
+    __device__ __forceinline__ void extra(const SpeciesDev& s) const {
         AxisSlots A[3];
         int di[3], lc[3];
         bool x[3];
@@ -249,7 +258,7 @@ struct TileDeposit {
             lc[d] = (qkey >> (5 * d)) & 31;
             di[d] = ((qkey >> (15 + 2 * d)) & 3) - 1;
             x[d] = di[d] != 0;
-            axis_slots(di[d], q[d], q[3 + d], A[d]);
+            axis_slots(di[d], q[d], s.off[d][qp], A[d]);
         }
         LdsCrossing em;
         em.base = Jl + ((lc[0] + 1) + (lc[1] + 1) * jx + (lc[2] + 1) * jpl);
@@ -262,52 +271,50 @@ struct TileDeposit {
         em.dyp = di[1] < 0 ? -4 * jx : 0;
         em.dzm = di[2] < 0 ? -5 * jpl : 0;
         em.dzp = di[2] < 0 ? -4 * jpl : 0;
-        emit_crossing<0>(A, q[6], x, em);
-        emit_crossing<1>(A, q[6], x, em);
-        emit_crossing<2>(A, q[6], x, em);
+        const float wq = s.mq * s.w[qp];
+        emit_crossing<0>(A, wq, x, em);
+        emit_crossing<1>(A, wq, x, em);
+        emit_crossing<2>(A, wq, x, em);
     }
 
     // Queue the lanes with `crossed`; when the queue fills, add its 64.
-    __device__ __forceinline__ void cross(bool crossed, const int lc[3], const int di[3], const float o0[3],
-                                          const float o1[3], float wq) {
+    __device__ __forceinline__ void cross(const SpeciesDev& s, bool crossed, const int lc[3], const int di[3],
+                                          const float o0[3], int p) {
         const unsigned long long m = __ballot(crossed);
         if (m == 0ull) return;
         const int lane = __lane_id(), k = __popcll(m);
         const unsigned long long below = (1ull << lane) - 1ull;
         // crossing lanes go to places waiting, waiting + 1, ... (mod 64), the others to the rest
         const int to = (waiting + (crossed ? __popcll(m & below) : k + __popcll(~m & below))) & 63;
-        float r[7];
+        float r[3];
 #pragma unroll
-        for (int d = 0; d < 3; ++d) {
-            r[d] = permute(to, o0[d]);
-            r[3 + d] = permute(to, o1[d]);
-        }
-        r[6] = permute(to, wq);
+        for (int d = 0; d < 3; ++d) r[d] = __int_as_float(__builtin_amdgcn_ds_permute(to << 2, __float_as_int(o0[d])));
+        const int rp = __builtin_amdgcn_ds_permute(to << 2, p);
         int key = 0;
 #pragma unroll
         for (int d = 0; d < 3; ++d) key |= ((lc[d] + guard) << (5 * d)) | ((di[d] + 1) << (15 + 2 * d));
         const int rkey = __builtin_amdgcn_ds_permute(to << 2, key);
         int end = waiting + k;
-        take(lane >= waiting && lane < end, r, rkey);
+        take(lane >= waiting && lane < end, r, rp, rkey);
         if (end >= 64) {
-            extra();
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
+            extra(s);
             end -= 64;
-            take(lane < end, r, rkey);
+            take(lane < end, r, rp, rkey);
         }
         waiting = end;
     }
 
-    __device__ __forceinline__ void finish() const {
-        if ((int)__lane_id() < waiting) extra();
+    __device__ __forceinline__ void finish(const SpeciesDev& s) const {
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
+        if ((int)__lane_id() < waiting) extra(s);
     }
 
   private:
-    static __device__ __forceinline__ float permute(int to, float v) {
-        return __int_as_float(__builtin_amdgcn_ds_permute(to << 2, __float_as_int(v)));
-    }
-    __device__ __forceinline__ void take(bool mine, const float r[7], int rkey) {
+    __device__ __forceinline__ void take(bool mine, const float r[3], int rp, int rkey) {
 #pragma unroll
-        for (int k = 0; k < 7; ++k) q[k] = mine ? r[k] : q[k];
+        for (int k = 0; k < 3; ++k) q[k] = mine ? r[k] : q[k];
+        qp = mine ? rp : qp;
         qkey = mine ? rkey : qkey;
     }
 };
@@ -476,9 +483,9 @@ __device__ __forceinline__ void tile_body(const Geom& g, const TileGeom& t, int 
             // a particle that did not move contributes zeros only
             if (moved(c, c1, o0, o)) dep.core(lc, di, o0, o, wq);
         }
-        dep.cross((di[0] | di[1] | di[2]) != 0, lc, di, o0, o, wq);
+        dep.cross(s, (di[0] | di[1] | di[2]) != 0, lc, di, o0, p);
     }
-    dep.finish();
+    dep.finish(s);
     if (errs) atomicOr(d_err, errs);
     __syncthreads();
     flush_current<NT>(g, t0, guard + 2, jx, jpl, jr, Jl, acc);
@@ -619,9 +626,10 @@ __global__ void __launch_bounds__(kDepThreads, 4) k_deposit_tiles(Geom g, TileGe
     for (int q0 = q_first; q0 < n; q0 += kDepThreads) {
         const int q = q0 + (int)__lane_id();
         int lc[3] = {0, 0, 0}, di[3] = {0, 0, 0};
+        int p = 0;
         float o0[3] = {0.f, 0.f, 0.f}, o1[3] = {0.f, 0.f, 0.f}, wq = 0.f;
         if (q < n) {
-            const int p = list[crowded ? first + (q0 >> 6) : q];
+            p = list[crowded ? first + (q0 >> 6) : q];
             const int cell0 = prev.cell[p], cell1 = s.cell[p];   // (cell0 is valid: it has a key)
             int c0[3], c1[3];
             decompose(g, cell0, c0);
@@ -646,9 +654,9 @@ __global__ void __launch_bounds__(kDepThreads, 4) k_deposit_tiles(Geom g, TileGe
                 }
             }
         }
-        dep.cross((di[0] | di[1] | di[2]) != 0, lc, di, o0, o1, wq);
+        dep.cross(s, (di[0] | di[1] | di[2]) != 0, lc, di, o0, p);
     }
-    dep.finish();
+    dep.finish(s);
     // (a push moves a particle into a neighbouring cell at most, which is all that
     // the region holds; a caller may have moved it further since)
     if (__syncthreads_or(far))
