@@ -30,7 +30,8 @@ import time
 HERE = os.path.dirname(os.path.abspath(__file__))
 CACHE = os.path.join(HERE, "autotune_cache.json")
 
-DEFAULT = {"tile": (8, 8, 8), "guard": 1, "threads": 512, "interleave": 0, "sort_interval": 2}
+# the library's own choices (threads = 0 is 1024 for tiles of which one fits a compute unit)
+DEFAULT = {"tile": (8, 8, 8), "guard": 1, "threads": 1024, "interleave": 0, "sort_interval": 2}
 SPACE = {
     "tile": [(8, 8, 8), (8, 8, 4), (8, 4, 4), (16, 8, 4), (16, 4, 4), (4, 4, 4), (16, 8, 8)],
     "guard": [0, 1, 2],
