@@ -71,7 +71,7 @@ __device__ __forceinline__ int at(const Geom& g, int i, int j, int k) { return i
 // t2 = axis + 2 cyclically.  y and z are periodic; with the moving window,
 // x neighbours across the window seam read as zero.
 //
-// A workgroup takes BT_X x BT_Y columns and marches along z, one plane at a
+// A workgroup takes 64 x 8 columns and marches along z, one plane at a
 // time: plane z + 1 of E (with its one-cell halo, in window coordinates, zeros
 // beyond the window's two ends, or periodic images without a window) is
 // staged in LDS while the values of planes z - 1 and z that the stencils need
@@ -82,9 +82,19 @@ __device__ __forceinline__ int at(const Geom& g, int i, int j, int k) { return i
 // added in the stencil's own order: the results are the same bit for bit.
 // HBM bounds it: 36 B per cell, 512x256x256 cells 327 -> 264 us (4.6 TB/s);
 // with the layer, 288x152x136 cells, 84 -> 73 us.
-constexpr int BT_X = 64, BT_Y = 8, BT_THREADS = BT_X * BT_Y;
-constexpr int BS_X = BT_X + 2, BS_Y = BT_Y + 2, BS_N = BS_X * BS_Y;
-constexpr int BS_PER = (BS_N + BT_THREADS - 1) / BT_THREADS;
+// A grid narrower than 64 cells takes columns of 16 x 32 or 32 x 16 where they
+// hold its x axis: 64 x 8 leaves most of their threads idle.  A field step, in
+// tiles of 32 x 8 x 4, columns of 64 x 8, and these: 8x256x256 cells 58.5, 62.5
+// and 36.3 us, with the layer 68.8, 77.2 and 42.0; 20x192x192 48.2, 49.0 and
+// 34.6, with the layer 57.6, 59.1 and 43.4.
+constexpr int BT_THREADS = 512;
+template <int W>
+struct BTile {
+    static constexpr int X = W, Y = BT_THREADS / W;         // columns of a workgroup
+    static constexpr int SX = X + 2, SY = Y + 2, N = SX * SY;   // staged cells of a plane
+    static constexpr int PER = (N + BT_THREADS - 1) / BT_THREADS;
+};
+constexpr int kWide = 64;   // (the batch's columns for every member)
 
 // Smoothed value from the centre, the sums over the +-t1 and +-t2 neighbours
 // and over the four corners (in the order the terms are added).
@@ -136,22 +146,23 @@ __device__ __forceinline__ float pml_stretch(float* __restrict__ psi, size_t q, 
 }
 
 // Columns (bx, by), planes [z0, z1) of the B half step.
-template <bool PD, bool PML>
+template <bool PD, bool PML, int W>
 __device__ __forceinline__ void bhalf_columns(const Geom& g, const PDCoef& c, const float* __restrict__ Ex,
                                               const float* __restrict__ Ey, const float* __restrict__ Ez,
                                               float* __restrict__ Bx, float* __restrict__ By, float* __restrict__ Bz,
-                                              float h, int bx, int by, int z0, int z1, float (*El)[3][BS_N],
+                                              float h, int bx, int by, int z0, int z1, float (*El)[3][BTile<W>::N],
                                               const PmlDev& P, bool store) {
-    const int x0 = bx * BT_X, y0 = by * BT_Y;
+    using T = BTile<W>;
+    const int x0 = bx * T::X, y0 = by * T::Y;
     const int origin = g.window ? g.origin : 0;
     // the plane offsets of this thread's staged cells (the same on every plane)
-    int so[BS_PER];
-    bool ok[BS_PER];
+    int so[T::PER];
+    bool ok[T::PER];
 #pragma unroll
-    for (int q = 0; q < BS_PER; ++q) {
+    for (int q = 0; q < T::PER; ++q) {
         const int i = threadIdx.x + q * BT_THREADS;
-        int xw = x0 - 1 + i % BS_X, y = y0 - 1 + i / BS_X;
-        ok[q] = i < BS_N;
+        int xw = x0 - 1 + i % T::SX, y = y0 - 1 + i / T::SX;
+        ok[q] = i < T::N;
         if (PML) ok[q] = ok[q] && y >= 0 && y < g.n[1];   // zero beyond the edges
         y = ((y % g.n[1]) + g.n[1]) % g.n[1];
         if (g.window)
@@ -162,12 +173,12 @@ __device__ __forceinline__ void bhalf_columns(const Geom& g, const PDCoef& c, co
         xs = xs >= g.n[0] ? xs - g.n[0] : xs;
         so[q] = ok[q] ? xs + g.n[0] * y : 0;
     }
-    float v[BS_PER][3];
+    float v[T::PER][3];
     auto load = [&](int z) {
         const bool zok = !PML || (z >= 0 && z < g.n[2]);
         const int zw = z < 0 ? z + g.n[2] : (z >= g.n[2] ? z - g.n[2] : z);
 #pragma unroll
-        for (int q = 0; q < BS_PER; ++q) {
+        for (int q = 0; q < T::PER; ++q) {
             const int s = so[q] + g.nxy * zw;
             const bool in = ok[q] && zok;
             v[q][0] = in ? Ex[s] : 0.0f;
@@ -175,14 +186,14 @@ __device__ __forceinline__ void bhalf_columns(const Geom& g, const PDCoef& c, co
             v[q][2] = in ? Ez[s] : 0.0f;
         }
     };
-    const int x = threadIdx.x % BT_X, y = threadIdx.x / BT_X;
+    const int x = threadIdx.x % T::X, y = threadIdx.x / T::X;
     const int xw = x0 + x, yy = y0 + y;
     const bool mine = xw < g.n[0] && yy < g.n[1];
     int xs = xw + origin;
     xs = xs >= g.n[0] ? xs - g.n[0] : xs;
     const int col = xs + g.n[0] * yy;
-    constexpr int X = 1, Y = BS_X;
-    const int o = (y + 1) * BS_X + (x + 1);
+    constexpr int X = 1, Y = T::SX;
+    const int o = (y + 1) * T::SX + (x + 1);
     // legs: S_y of E_x and E_z at y and y + 1, S_x of E_y and E_z at x and x + 1;
     // S_z of E_x and E_y on plane z
     Leg ex[2] = {}, ey[2] = {}, ezx[2] = {}, ezy[2] = {};
@@ -219,11 +230,11 @@ __device__ __forceinline__ void bhalf_columns(const Geom& g, const PDCoef& c, co
     };
     load(z0 - 1);
     for (int z = z0 - 1, buf = 0; z <= z1; ++z, buf ^= 1) {
-        float(*L)[BS_N] = El[buf];
+        float(*L)[T::N] = El[buf];
 #pragma unroll
-        for (int q = 0; q < BS_PER; ++q) {
+        for (int q = 0; q < T::PER; ++q) {
             const int i = threadIdx.x + q * BT_THREADS;
-            if (i < BS_N) {
+            if (i < T::N) {
                 L[0][i] = v[q][0];
                 L[1][i] = v[q][1];
                 L[2][i] = v[q][2];
@@ -318,17 +329,18 @@ static int march_planes(int64_t columns, int nz, int resident) {
 }
 constexpr int kMarchResident = 4 * 256;   // workgroups of 8 wavefronts: 32 wavefronts per CU
 
-template <bool PD, bool PML>
+template <bool PD, bool PML, int W>
 __global__ void __launch_bounds__(BT_THREADS) k_bhalf_march(Geom g, PDCoef c, const float* __restrict__ Ex,
                                                             const float* __restrict__ Ey,
                                                             const float* __restrict__ Ez, float* __restrict__ Bx,
                                                             float* __restrict__ By, float* __restrict__ Bz, float h,
                                                             int planes, PmlDev P, int store) {
-    __shared__ float El[2][3][BS_N];
+    using T = BTile<W>;
+    __shared__ float El[2][3][T::N];
     const int t = xcd_run(blockIdx.x, gridDim.x);
-    const int tx = (g.n[0] + BT_X - 1) / BT_X, ty = (g.n[1] + BT_Y - 1) / BT_Y;
+    const int tx = (g.n[0] + T::X - 1) / T::X, ty = (g.n[1] + T::Y - 1) / T::Y;
     const int bx = t % tx, by = (t / tx) % ty, z0 = (t / (tx * ty)) * planes;
-    bhalf_columns<PD, PML>(g, c, Ex, Ey, Ez, Bx, By, Bz, h, bx, by, z0, min(z0 + planes, g.n[2]), El, P, store != 0);
+    bhalf_columns<PD, PML, W>(g, c, Ex, Ey, Ez, Bx, By, Bz, h, bx, by, z0, min(z0 + planes, g.n[2]), El, P, store != 0);
 }
 
 // Where the E update takes its current from: the J planes (clearing the
@@ -532,10 +544,11 @@ constexpr int kBatchPlanes = 8;   // planes per workgroup of the batched marches
 
 // Grid x = workgroup (x fastest, then y, then plane chunk) of the member's grid.
 __global__ void __launch_bounds__(BT_THREADS) k_batch_bhalf(const InstDesc* __restrict__ tab) {
-    __shared__ float El[2][3][BS_N];
+    using T = BTile<kWide>;
+    __shared__ float El[2][3][T::N];
     const InstDesc& d = tab[blockIdx.y];
     const Geom g = d.g;
-    const int tx = (g.n[0] + BT_X - 1) / BT_X, ty = (g.n[1] + BT_Y - 1) / BT_Y;
+    const int tx = (g.n[0] + T::X - 1) / T::X, ty = (g.n[1] + T::Y - 1) / T::Y;
     const int t = blockIdx.x;
     if (t >= tx * ty * ((g.n[2] + kBatchPlanes - 1) / kBatchPlanes)) return;
     const PDCoef c = d.c;
@@ -543,10 +556,10 @@ __global__ void __launch_bounds__(BT_THREADS) k_batch_bhalf(const InstDesc* __re
     const int z1 = min(z0 + kBatchPlanes, g.n[2]);
     const PmlDev none{};
     if (d.pd)
-        bhalf_columns<true, false>(g, c, d.f.E[0], d.f.E[1], d.f.E[2], d.f.B[0], d.f.B[1], d.f.B[2], d.hdt, bx, by,
+        bhalf_columns<true, false, kWide>(g, c, d.f.E[0], d.f.E[1], d.f.E[2], d.f.B[0], d.f.B[1], d.f.B[2], d.hdt, bx, by,
                                    z0, z1, El, none, false);
     else
-        bhalf_columns<false, false>(g, c, d.f.E[0], d.f.E[1], d.f.E[2], d.f.B[0], d.f.B[1], d.f.B[2], d.hdt, bx, by,
+        bhalf_columns<false, false, kWide>(g, c, d.f.E[0], d.f.E[1], d.f.E[2], d.f.B[0], d.f.B[1], d.f.B[2], d.hdt, bx, by,
                                     z0, z1, El, none, false);
 }
 
@@ -586,16 +599,25 @@ __global__ void k_zero_u64(unsigned long long* p, int64_t n) {
     if (i < n) p[i] = 0ull;
 }
 
-hipError_t launch_bhalf(const Geom& g, int pd, const PDCoef& c, float* const E[3], float* const B[3], float h,
-                        const PmlDev* pml, int store, hipStream_t st) {
-    const int bx = (g.n[0] + BT_X - 1) / BT_X, by = (g.n[1] + BT_Y - 1) / BT_Y;
+template <int W>
+static hipError_t launch_bhalf_w(const Geom& g, int pd, const PDCoef& c, float* const E[3], float* const B[3], float h,
+                                 const PmlDev* pml, int store, hipStream_t st) {
+    using T = BTile<W>;
+    const int bx = (g.n[0] + T::X - 1) / T::X, by = (g.n[1] + T::Y - 1) / T::Y;
     const int planes = march_planes((int64_t)bx * by, g.n[2], kMarchResident);
     const dim3 nb(bx * by * ((g.n[2] + planes - 1) / planes));
     const PmlDev P = pml ? *pml : PmlDev{};
-    auto k = pd ? (pml ? k_bhalf_march<true, true> : k_bhalf_march<true, false>)
-                : (pml ? k_bhalf_march<false, true> : k_bhalf_march<false, false>);
+    auto k = pd ? (pml ? k_bhalf_march<true, true, W> : k_bhalf_march<true, false, W>)
+                : (pml ? k_bhalf_march<false, true, W> : k_bhalf_march<false, false, W>);
     hipLaunchKernelGGL(k, nb, dim3(BT_THREADS), 0, st, g, c, E[0], E[1], E[2], B[0], B[1], B[2], h, planes, P, store);
     return hipGetLastError();
+}
+
+hipError_t launch_bhalf(const Geom& g, int pd, const PDCoef& c, float* const E[3], float* const B[3], float h,
+                        const PmlDev* pml, int store, hipStream_t st) {
+    return g.n[0] <= 16   ? launch_bhalf_w<16>(g, pd, c, E, B, h, pml, store, st)
+           : g.n[0] <= 32 ? launch_bhalf_w<32>(g, pd, c, E, B, h, pml, store, st)
+                          : launch_bhalf_w<kWide>(g, pd, c, E, B, h, pml, store, st);
 }
 
 hipError_t launch_efull(const Geom& g, float* const E[3], float* const B[3], float* const J[3], float* const Jcopy[3],
@@ -647,7 +669,8 @@ hipError_t launch_batch_bhalf(const InstDesc* d, int n, int max_tiles, hipStream
 }
 
 int bhalf_tiles(const int n[3]) {
-    return ((n[0] + BT_X - 1) / BT_X) * ((n[1] + BT_Y - 1) / BT_Y) * ((n[2] + kBatchPlanes - 1) / kBatchPlanes);
+    using T = BTile<kWide>;
+    return ((n[0] + T::X - 1) / T::X) * ((n[1] + T::Y - 1) / T::Y) * ((n[2] + kBatchPlanes - 1) / kBatchPlanes);
 }
 
 int binomial_tiles(const int n[3]) {
