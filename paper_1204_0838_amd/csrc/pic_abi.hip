@@ -1346,7 +1346,8 @@ pic_status pic_continuity_noalloc(pic_ctx* c, int32_t s, double* resid, double* 
                                 c->desc.d[0] / c->desc.d[2], c->j_filtered, &head->contmax,
                                 c->stream));
     FieldPtrs f = fields_of(c);
-    HIPCHK(c, launch_diag_fields(c->g, f.E, f.B, c->f.J, 1.0, head->red, &head->jmax, diag_partials(c), c->stream));
+    // (the density is read by now: its array takes the sums' partials, not the workspace)
+    HIPCHK(c, launch_diag_fields(c->g, f.E, f.B, c->f.J, 1.0, head->red, &head->jmax, rho, c->stream));
     unsigned long long cm = 0;
     unsigned int jm = 0;
     HIPCHK(c, hipMemcpyAsync(&cm, &head->contmax, 8, hipMemcpyDeviceToHost, c->stream));
