@@ -1708,12 +1708,12 @@ pic_status pic_spectrum(pic_ctx* c, int32_t s, int32_t quantity, double lo, doub
     HIPCHK(c, launch_spectrum(c->g, dev_of(c, sp), &small_of(c)->count[s], (int)sp.bound, quantity, lo, hi, nbins,
                               fabs(sp.user.q) * dv, charge, count, c->stream));
     HIPCHK(c, launch_flag_word(&small_of(c)->err, count + nbins, c->stream));
-    std::vector<uint64_t> h(2 * (size_t)nbins + 1);
-    HIPCHK(c, hipMemcpyAsync(h.data(), charge, h.size() * 8, hipMemcpyDeviceToHost, c->stream));
+    uint64_t h[2 * kDiagBins + 1];   // (no allocation: it could throw)
+    HIPCHK(c, hipMemcpyAsync(h, charge, (2 * (size_t)nbins + 1) * 8, hipMemcpyDeviceToHost, c->stream));
     HIPCHK(c, hipStreamSynchronize(c->stream));
-    memcpy(host_charge, h.data(), (size_t)nbins * 8);
-    if (host_count) memcpy(host_count, h.data() + nbins, (size_t)nbins * 8);
-    return h.back() ? device_errors(c) : PIC_OK;
+    memcpy(host_charge, h, (size_t)nbins * 8);
+    if (host_count) memcpy(host_count, h + nbins, (size_t)nbins * 8);
+    return h[2 * nbins] ? device_errors(c) : PIC_OK;
 }
 
 pic_status pic_beam_moments(pic_ctx* c, int32_t s, double ux_min, pic_beam_diag* out) {

@@ -13,7 +13,6 @@ namespace pic {
 
 constexpr int kSumThreads = 1024;   // 16 wavefronts: one workgroup fills a CU's queue of loads
 constexpr int kSumBlocks = 256;     // one per CU; kSumBlocks x K partials fit the diagnostics' 4096 words (K <= 16)
-constexpr int kSumMaxWords = 16;
 
 inline int sum_blocks(int64_t n) {
     const int64_t b = (n + kSumThreads - 1) / kSumThreads;
