@@ -539,9 +539,12 @@ __global__ void __launch_bounds__(NT, WAVES) k_batch_tile(const InstDesc* __rest
 // workgroups per CU).  A particle's 144-300 contributions go to LDS, and the
 // tile's region to the global accumulator once: global 64-bit atomics, which
 // bound the one-thread-per-particle form (k_deposit), drop from ~200 to ~3
-// per particle at 4 particles per cell (75x50x44 cells, 6.6e5 particles: 3827
-// -> 68 us, plus 75 us for the index list; atomics and deposit arithmetic in
-// LDS bound it now).
+// per particle at 4 particles per cell (75x50x44 cells, 6.6e5 particles of a
+// warm plasma: 2880 us -> 119 with the index list; atomics and deposit
+// arithmetic in LDS bound it now).  Moves of more than one cell, which the
+// region does not hold, are added straight to the accumulator after the loop;
+// kept out of it, they cost it no registers (162 with them, 128 for two
+// workgroups per CU: staged step of two species 729 us against 711).
 constexpr int kDepTile = 8, kDepThreads = 512;
 
 // A tile of up to kWhole list entries (8 particles per cell) is one workgroup's.
@@ -657,8 +660,8 @@ __global__ void __launch_bounds__(kDepThreads, 4) k_deposit_tiles(Geom g, TileGe
         dep.cross(s, (di[0] | di[1] | di[2]) != 0, lc, di, o0, p);
     }
     dep.finish(s);
-    // (a push moves a particle into a neighbouring cell at most, which is all that
-    // the region holds; a caller may have moved it further since)
+    // (a push moves a particle into a neighbouring cell at most; a caller may have
+    // moved it further since)
     if (__syncthreads_or(far))
         for (int q = threadIdx.x; q < n; q += kDepThreads) {
             const int p = list[q], cell1 = s.cell[p];
@@ -680,8 +683,8 @@ __global__ void __launch_bounds__(kDepThreads, 4) k_deposit_tiles(Geom g, TileGe
 // LDS (48 KB, three workgroups per CU).  The one-thread-per-particle form
 // (k_gather_push) reads its 384 field values from global memory, where the
 // particles' memory order decides how many lines a wavefront's load touches.
-// 75x50x44 cells, 3.3e5 particles of a warm plasma: 205 -> 75 us, plus 56 us
-// for the list; the particles' scattered loads and stores bound it now.
+// 75x50x44 cells, 3.3e5 particles of a warm plasma: 205 -> 131 us with its
+// list; the particles' scattered loads and stores bound it now.
 __global__ void __launch_bounds__(kDepThreads) k_gather_tiles(Geom g, TileGeom t, FieldPtrs f, SpeciesDev s,
                                                               PrevDev prev, const TileList l,
                                                               int* __restrict__ d_err) {
