@@ -39,8 +39,11 @@ constexpr int64_t kDepositTilesMin = 8192;
 // 160x128x128, 2.6e6: 4736 against 976, after a sort 970 against 293.  Beams
 // (normal, 1.5 cells, random order), the least gain: 2.9e5 particles 135 against
 // 151, 3.3e5 167 against 169, 1e6 438 against 381 (the deposit of the same step
-// takes 7.6 ms directly, 0.34 tile-wise).  32^3 cells (64 tiles), 5.1e5: 325
-// against 248 and 149 against 203; 16^3 (8 tiles): 205 against 1262.
+// takes 7.6 ms directly, 0.34 tile-wise).  The line at 256 tiles was set with an
+// earlier, slower list (16^3 cells, 8 tiles, 5.1e5 random: 205 against 1262).
+// With the present one tile-wise is the faster form on the smaller grids measured
+// too: in cell order and random, 32^3 (64 tiles), 5.1e5: 175 against 64 and 344
+// against 199; 16^3: 137 against 67 and 211 against 202.
 constexpr int64_t kGatherTilesMin = 262144;
 constexpr int kGatherTiles = 256;
 constexpr size_t kDiagBytesFixed = (2 * kDiagBins + kDiagWords) * 8;
